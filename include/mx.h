@@ -446,8 +446,8 @@ mx_status mx_map_map_reduce_plain_f32(int ta, int tb, int64_t M, int64_t N, int6
  *   a_i = G sum_j m_j d_ij (|d_ij|^2 + eps2)^(-3/2),  d_ij = x_j - x_i,
  * a map over bodies of a reduce over bodies (the j = i term is zero).
  * Forward Euler: x_{t+1} = x_t + dt v_t, v_{t+1} = v_t + dt a(x_t).
- * The pair loop is split into slices of j; slice partials are added in slice
- * order, so results are deterministic and independent of the device.
+ * The pair sums have a bracketing fixed by n alone, so results are
+ * deterministic and independent of the device.
  * Pair entry points need a workspace of mx_nbody_pair_workspace_bytes(n). */
 size_t mx_nbody_pair_workspace_bytes(int64_t n);
 
@@ -455,7 +455,7 @@ size_t mx_nbody_pair_workspace_bytes(int64_t n);
 mx_status mx_nbody_accel_f32(const float *pos4_dev, int64_t n, float eps2, float G, float *acc4_dev,
                              void *ws, size_t ws_bytes, hipStream_t stream);
 
-/* One fused Euler step (pair loop, slice sum and update).  Outputs must not
+/* One fused Euler step (pair sums and update).  Outputs must not
  * alias inputs.  Errors as mx_nbody_accel_f32. */
 mx_status mx_nbody_step_f32(const float *pos4_dev, const float *vel4_dev, int64_t n, float eps2, float G,
                             float dt, float *pos4_out_dev, float *vel4_out_dev, void *ws, size_t ws_bytes,
@@ -490,10 +490,10 @@ mx_status mx_nbody_kinetic_f32(const float *pos4_dev, const float *vel4_dev, int
  * the final kinetic energy to ke_dev, and the gradients of that energy with
  * respect to the initial positions (gx4) and velocities (gv4) by the reverse
  * sweep of the discrete adjoint, storing states only every ckpt_every steps
- * and recomputing each segment forward before its reverse sweep.  The
- * recomputation reproduces the forward states bit for bit.  Launches only
- * (no allocation, no host synchronisation), so the call can be captured in a
- * HIP graph.  1 <= ckpt_every <= 64.  Workspace: mx_nbody_workspace_bytes. */
+ * and recomputing each segment but the last, whose positions are kept, forward
+ * before its reverse sweep.  The recomputation reproduces the forward states
+ * bit for bit.  Launches only (no allocation, no host synchronisation), so the
+ * call can be captured in a HIP graph.  1 <= ckpt_every <= 64.  Workspace: mx_nbody_workspace_bytes. */
 size_t mx_nbody_workspace_bytes(int64_t n, int nsteps, int ckpt_every);
 mx_status mx_nbody_ke_grad_f32(const float *pos4_dev, const float *vel4_dev, int64_t n, float eps2, float G,
                                float dt, int nsteps, int ckpt_every, float *ke_dev, float *gx4_dev,
