@@ -338,48 +338,131 @@ __global__ void __launch_bounds__(NT) k_stencil7(const float *__restrict__ in, f
 // ---------------------------------------------------------------- mri-q
 // Qr_i = sum_k phi_k cos(2 pi t_ik), Qi_i = sum_k phi_k sin(2 pi t_ik) with
 // t_ik = kx_k x_i + ky_k y_i + kz_k z_i.  The samples go through LDS in tiles
-// (every lane reads the same sample: a broadcast); each thread owns two
-// voxels.  sin and cos of 2 pi t come from the hardware sine and cosine,
-// whose argument is in revolutions, so the angle is never multiplied by pi
-// in floating point: t is first reduced to r = t - rint(t) in [-1/2, 1/2]
-// (exact for every float) and v_sin / v_cos take r.  Their absolute error,
-// measured against binary64 over 2^24 arguments in [-24, 24], is at most
-// 1.26e-7 (2.1 units of 2^-24), against 5.1e-8 for the library sincospi,
-// which costs about 30 more instructions per pair.
+// (every lane reads the same sample: a broadcast).  sin and cos of 2 pi t come
+// from the hardware sine and cosine, whose argument is in revolutions, so the
+// angle is never multiplied by pi in floating point.  Up to 256 revolutions
+// the hardware takes the fraction itself, exactly: over 2^24 arguments the
+// absolute error against binary64 is at most 1.25e-7 (2.1 units of 2^-24) for
+// |t| <= 24 and for |t| <= 255, with t reduced to t - rint(t) first or not.  So t is
+// reduced (exact for every float) only in tiles whose largest |k| allows a
+// larger angle in some lane.  (The library sincospi, 5.1e-8, costs about 30
+// more instructions per pair.)
+//
+// Bound by issue: two transcendental instructions of 8 cycles and five others
+// per pair of sample and voxel.
+//
+// Work split: a block covers 64 V voxels, V per lane; its WS waves take the
+// samples of a tile by fours in turn and their sums are added in wave order
+// through LDS (which V and WS: mx_mriq_f32).
 constexpr int kMriTile = 1024;
+constexpr float kMriRaw = 250.f;
 
-__global__ void __launch_bounds__(NT) k_mriq(const float *__restrict__ kx, const float *__restrict__ ky,
-                                             const float *__restrict__ kz, const float *__restrict__ phi,
-                                             int64_t nk, const float *__restrict__ x, const float *__restrict__ y,
-                                             const float *__restrict__ z, int64_t nv, float *__restrict__ qr,
-                                             float *__restrict__ qi) {
+// sin and cos of 2 pi u, K of each.  Transcendental instructions knock the two
+// waves whose FP32 instructions a SIMD issues together out of step for dozens
+// of instructions; raised priority for the wave issuing them keeps the pairing.
+template <int K> __device__ __forceinline__ void sincos_group(const float (&u)[K], float (&sn)[K], float (&cs)[K]) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        sn[k] = __builtin_amdgcn_sinf(u[k]);
+        cs[k] = __builtin_amdgcn_cosf(u[k]);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int V, int WS>
+__global__ void __launch_bounds__(WS *kWave) k_mriq(const float *__restrict__ kx, const float *__restrict__ ky,
+                                                    const float *__restrict__ kz, const float *__restrict__ phi,
+                                                    int64_t nk, const float *__restrict__ x,
+                                                    const float *__restrict__ y, const float *__restrict__ z,
+                                                    int64_t nv, float *__restrict__ qr, float *__restrict__ qi) {
+    constexpr int BT = WS * kWave;
+    constexpr int U = 4;  // samples at a time
     __shared__ float4 ks[kMriTile];
-    const int64_t v0 = (int64_t)blockIdx.x * NT * 2 + threadIdx.x, v1 = v0 + NT;
-    const bool h0 = v0 < nv, h1 = v1 < nv;
-    const float x0 = h0 ? x[v0] : 0.f, y0 = h0 ? y[v0] : 0.f, z0 = h0 ? z[v0] : 0.f;
-    const float x1 = h1 ? x[v1] : 0.f, y1 = h1 ? y[v1] : 0.f, z1 = h1 ? z[v1] : 0.f;
-    float r0 = 0.f, i0 = 0.f, r1 = 0.f, i1 = 0.f;
+    __shared__ float red[BT * V * 2];
+    __shared__ float kmax[BT / kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t v0 = (int64_t)blockIdx.x * (kWave * V) + lane;
+    float xv[V], yv[V], zv[V], r[V], i[V];
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+        const int64_t v = v0 + q * kWave;
+        xv[q] = v < nv ? x[v] : 0.f;
+        yv[q] = v < nv ? y[v] : 0.f;
+        zv[q] = v < nv ? z[v] : 0.f;
+        r[q] = i[q] = 0.f;
+    }
     for (int64_t k0 = 0; k0 < nk; k0 += kMriTile) {
         const int cnt = (int)(nk - k0 < kMriTile ? nk - k0 : kMriTile);
+        const int pad = (cnt + U - 1) / U * U;  // samples of zero magnitude fill the last four
         __syncthreads();
-        for (int j = threadIdx.x; j < cnt; j += NT)
-            ks[j] = make_float4(kx[k0 + j], ky[k0 + j], kz[k0 + j], phi[k0 + j]);
+        float mx = 0.f;
+        for (int j = threadIdx.x; j < pad; j += BT) {
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j < cnt) s = make_float4(kx[k0 + j], ky[k0 + j], kz[k0 + j], phi[k0 + j]);
+            ks[j] = s;
+            mx = fmaxf(fmaxf(mx, fabsf(s.x)), fmaxf(fabsf(s.y), fabsf(s.z)));
+        }
+        mx = wave_reduce<Red<MX_MAX, float>>(mx);
+        if (lane == 0) kmax[w] = mx;
         __syncthreads();
-        for (int j = 0; j < cnt; ++j) {
-            const float4 s = ks[j];
-            const float t0 = s.x * x0 + s.y * y0 + s.z * z0;
-            const float t1 = s.x * x1 + s.y * y1 + s.z * z1;
-            const float u0 = t0 - rintf(t0), u1 = t1 - rintf(t1);
-            const float sn0 = __builtin_amdgcn_sinf(u0), cs0 = __builtin_amdgcn_cosf(u0);
-            const float sn1 = __builtin_amdgcn_sinf(u1), cs1 = __builtin_amdgcn_cosf(u1);
-            r0 += s.w * cs0;
-            i0 += s.w * sn0;
-            r1 += s.w * cs1;
-            i1 += s.w * sn1;
+#pragma unroll
+        for (int o = 0; o < BT / kWave; ++o) mx = fmaxf(mx, kmax[o]);
+        // no angle of the tile passes kMriRaw revolutions in any lane
+        bool raw = true;
+#pragma unroll
+        for (int q = 0; q < V; ++q) raw = raw && mx * (fabsf(xv[q]) + fabsf(yv[q]) + fabsf(zv[q])) <= kMriRaw;
+        auto tile = [&](auto reduce) {
+            for (int j = w * U; j < pad; j += WS * U) {
+                float u[U * V], sn[U * V], cs[U * V], m[U];
+#pragma unroll
+                for (int e = 0; e < U; ++e) {
+                    const float4 s = ks[j + e];
+                    m[e] = s.w;
+#pragma unroll
+                    for (int q = 0; q < V; ++q) {
+                        const float t = s.x * xv[q] + s.y * yv[q] + s.z * zv[q];
+                        u[e * V + q] = decltype(reduce)::value ? t - rintf(t) : t;
+                    }
+                }
+                sincos_group(u, sn, cs);
+#pragma unroll
+                for (int e = 0; e < U; ++e)
+#pragma unroll
+                    for (int q = 0; q < V; ++q) {
+                        r[q] += m[e] * cs[e * V + q];
+                        i[q] += m[e] * sn[e * V + q];
+                    }
+            }
+        };
+        if (__all(raw)) tile(std::false_type{});
+        else tile(std::true_type{});
+    }
+    // red[wave][2 V][lane]; the first wave adds the waves in order
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+        red[(w * 2 * V + 2 * q) * kWave + lane] = r[q];
+        red[(w * 2 * V + 2 * q + 1) * kWave + lane] = i[q];
+    }
+    __syncthreads();
+    if (w != 0) return;
+#pragma unroll
+    for (int q = 0; q < V; ++q)
+        for (int o = 1; o < WS; ++o) {
+            r[q] += red[(o * 2 * V + 2 * q) * kWave + lane];
+            i[q] += red[(o * 2 * V + 2 * q + 1) * kWave + lane];
+        }
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+        const int64_t v = v0 + q * kWave;
+        if (v < nv) {
+            qr[v] = r[q];
+            qi[v] = i[q];
         }
     }
-    if (h0) { qr[v0] = r0; qi[v0] = i0; }
-    if (h1) { qr[v1] = r1; qi[v1] = i1; }
 }
 
 // ---------------------------------------------------------------- tpacf
@@ -631,10 +714,20 @@ mx_status mx_mriq_f32(const float *kx_dev, const float *ky_dev, const float *kz_
     if (nv == 0) return MX_OK;
     MX_REQUIRE(x_dev && y_dev && z_dev && qr_dev && qi_dev, MX_ERR_INVALID, "%s: null voxel array", who);
     MX_REQUIRE(nk == 0 || (kx_dev && ky_dev && kz_dev && phi_dev), MX_ERR_INVALID, "%s: null sample array", who);
-    const int64_t grid = ceil_div(nv, (int64_t)NT * 2);
-    MX_REQUIRE(grid <= 0x7fffffff, MX_ERR_SHAPE, "%s: too many voxels", who);
-    hipLaunchKernelGGL(k_mriq, dim3((unsigned)grid), dim3(NT), 0, stream, kx_dev, ky_dev, kz_dev, phi_dev, nk, x_dev,
-                       y_dev, z_dev, nv, qr_dev, qi_dev);
+    MX_REQUIRE(ceil_div(nv, (int64_t)kWave) <= 0x7fffffff, MX_ERR_SHAPE, "%s: too many voxels", who);
+    // Split by voxels: four per lane once that fills the chip (a 16-byte LDS
+    // read then serves four), two below, and with few voxels one per lane and
+    // the samples dealt to 16 waves, whose sums cost more than they save where
+    // the chip is full.  us at 2048 samples, (voxels per lane, waves): 2^18
+    // voxels (4,4) 106, (2,4) 116, (1,16) 124, and 160 for two voxels per lane,
+    // one wave and no raised priority; 2^16: 46, 32, 34; 2^14: 44, 27, 12.
+#define MX_MRIQ(V, WS)                                                                                             \
+    hipLaunchKernelGGL((k_mriq<V, WS>), dim3((unsigned)ceil_div(nv, (int64_t)kWave * V)), dim3(WS > 4 ? WS * kWave : NT), \
+                       0, stream, kx_dev, ky_dev, kz_dev, phi_dev, nk, x_dev, y_dev, z_dev, nv, qr_dev, qi_dev)
+    if (nv >= 3 << 16) MX_MRIQ(4, 4);
+    else if (nv > 1 << 15) MX_MRIQ(2, 4);
+    else MX_MRIQ(1, 16);
+#undef MX_MRIQ
     return last_launch(who);
 }
 
