@@ -239,6 +239,18 @@ template <class Op, class T> __device__ __forceinline__ T wave_reduce(T v) {
     return read_lane(v, 63);
 }
 
+// The operator over the G lanes of a group (a 16-lane DPP row or the wave), in
+// every lane.  All 64 lanes must be active.
+template <class R, int G, class T> __device__ __forceinline__ T group_reduce(T v) {
+    static_assert(G == 16 || G == 64, "a DPP row or a wave");
+    if constexpr (G == 64) return wave_reduce<R>(v);
+    const T id = R::id();
+    v = R::ap(v, dpp_move<0xB1, 0xF>(v, id));
+    v = R::ap(v, dpp_move<0x4E, 0xF>(v, id));
+    v = R::ap(v, dpp_move<0x141, 0xF>(v, id));
+    return R::ap(v, dpp_move<0x140, 0xF>(v, id));
+}
+
 // Block reduction for NT threads (a multiple of 64); result valid in every
 // thread.  smem must hold NT/64 values.
 template <class Op, int NT, class T> __device__ __forceinline__ T block_reduce(T v, T *smem) {

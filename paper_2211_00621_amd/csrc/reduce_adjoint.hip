@@ -122,23 +122,64 @@ __global__ void __launch_bounds__(NT) k_arg_finish(const float *__restrict__ pv,
 }
 
 // One wave per ragged row (rows grid-strided over the waves): the row's best
-// pair, then the row written as g at the arg and 0 elsewhere.
-template <int OP>
+// pair, then the row written as g at the arg and 0 elsewhere.  Reads and writes
+// go in 16-byte vectors at 4-byte alignment, four per lane in flight; the best
+// value by the DPP tree, then the lowest index among the lanes that hold it.
+// HBM bound at 65 536 rows of mean length 490 (32 M values, 256 MB in and out):
+// 40 us (6.4 TB/s, the last-level cache serving part); 89 us with one element
+// per lane and pass and 64-bit pairs shuffled.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int OP, int G>  // G lanes per row: a wave, or a 16-lane DPP row where rows are short
 __global__ void __launch_bounds__(NT) k_seg_arg(const float *__restrict__ values, const int64_t *__restrict__ offsets,
                                                 int64_t nseg, float ne, const float *__restrict__ gout,
                                                 float *__restrict__ gvalues) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t nw = (int64_t)gridDim.x * (NT / kWave);
-    for (int64_t r = (int64_t)blockIdx.x * (NT / kWave) + threadIdx.x / kWave; r < nseg; r += nw) {
-        const int64_t s = offsets[r], e = offsets[r + 1];
+    constexpr int U = 4;
+    const int lane = threadIdx.x % G;
+    const int64_t ng = (int64_t)gridDim.x * (NT / G);
+    // the groups of a wave stay together (their rows may differ): all lanes
+    // take part in the reductions
+    for (int64_t r0 = (int64_t)blockIdx.x * (NT / G) + threadIdx.x / kWave * (kWave / G); r0 < nseg; r0 += ng) {
+        const int64_t r = r0 + threadIdx.x % kWave / G;
+        const bool has = r < nseg;
+        const int64_t s = has ? offsets[r] : 0, e = has ? offsets[r + 1] : 0;
+        const float g = has ? gout[r] : 0.f;
+        const int64_t n = e - s, nv = n / 4;
+        const float *x = values + s;
         float bv = ident<OP>();
         int64_t bi = kNone;
-        for (int64_t p = s + lane; p < e; p += kWave) take<OP>(values[p], p, bv, bi);
-        wave_argreduce<OP>(bv, bi);
-        take<OP>(ne, -1, bv, bi);
-        if (ne != ne) bi = -1;  // a NaN ne is never improved on by the fold
-        const float g = gout[r];
-        for (int64_t p = s + lane; p < e; p += kWave) gvalues[p] = p == bi ? g : 0.f;
+        for (int64_t i = lane; i < nv; i += U * G) {
+            f4u q[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + u * G < nv) q[u] = *reinterpret_cast<const f4u *>(x + 4 * (i + u * G));
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + u * G < nv) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) take<OP>(q[u][c], 4 * (i + u * G) + c, bv, bi);
+                }
+        }
+        if (4 * nv + lane < n) take<OP>(x[4 * nv + lane], 4 * nv + lane, bv, bi);
+        using B = Red<OP, float>;
+        using I = Red<MX_MIN, int64_t>;
+        const float best = group_reduce<B, G>(bv);
+        int64_t at = group_reduce<I, G>(bv == best ? bi : kNone);
+        // ne stands at index -1; a NaN ne is never improved on by the fold
+        if (!better<OP>(best, 0, ne, -1)) at = kNone;
+        float *y = gvalues + s;
+        for (int64_t i = lane; i < nv; i += G) {
+            f4u z = f4u{0.f, 0.f, 0.f, 0.f};
+            const int64_t c = at - 4 * i;
+            if (c >= 0 && c < 4) {
+                z.x = c == 0 ? g : 0.f;
+                z.y = c == 1 ? g : 0.f;
+                z.z = c == 2 ? g : 0.f;
+                z.w = c == 3 ? g : 0.f;
+            }
+            *reinterpret_cast<f4u *>(y + 4 * i) = z;
+        }
+        if (4 * nv + lane < n) y[4 * nv + lane] = 4 * nv + lane == at ? g : 0.f;
     }
 }
 
@@ -213,15 +254,19 @@ mx_status mx_segmented_reduce_adjoint_f32(mx_redop op, const float *values_dev, 
     if (mx_status st = check_offsets_debug(who, offsets_dev, nseg, stream)) return st;
     const DeviceInfo *d;
     if (mx_status st = device_info(&d)) return st;
-    int64_t grid = ceil_div(nseg, NT / kWave);
+    // lanes per row by mean length; with few rows a wave each costs nothing (4000
+    // rows of mean 143: 3.9 us against 5.7 us with 16 lanes; 65 536 of mean 79:
+    // 20.4 us against 10)
+    const int group = nvalues <= 64 * nseg || (nvalues <= 160 * nseg && nseg >= 16384) ? 16 : kWave;
+    int64_t grid = ceil_div(nseg, NT / group);
     if (grid > (int64_t)d->num_cus * 16) grid = (int64_t)d->num_cus * 16;
     const float ne = *ne_host;
-    if (op == MX_MIN)
-        hipLaunchKernelGGL(k_seg_arg<MX_MIN>, dim3((unsigned)grid), dim3(NT), 0, stream, values_dev, offsets_dev, nseg,
-                           ne, gout_dev, gvalues_dev);
-    else
-        hipLaunchKernelGGL(k_seg_arg<MX_MAX>, dim3((unsigned)grid), dim3(NT), 0, stream, values_dev, offsets_dev, nseg,
-                           ne, gout_dev, gvalues_dev);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NT), 0, stream, values_dev, offsets_dev, nseg, ne, gout_dev,
+                           gvalues_dev);
+    };
+    if (op == MX_MIN) group == 16 ? go(k_seg_arg<MX_MIN, 16>) : go(k_seg_arg<MX_MIN, kWave>);
+    else group == 16 ? go(k_seg_arg<MX_MAX, 16>) : go(k_seg_arg<MX_MAX, kWave>);
     return last_launch(who);
 }
 

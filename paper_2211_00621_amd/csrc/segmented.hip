@@ -114,7 +114,7 @@ mx_status validate_lengths(const char *who, const int64_t *len, int64_t n, hipSt
 // slots and the counter.
 constexpr int kChunkBytes = 16384;
 // a chunk with more rows than this folds its short segments one lane each
-constexpr int kWaveRows = 32;
+constexpr int kWaveRowsMax = 32;
 constexpr int kShortSeg = 32;  // longest segment one lane folds
 constexpr int kMaxChunks = 48;  // chunks one block streams, at most (q + 1 <= kMaxChunks)
 
@@ -711,7 +711,7 @@ k_seg_blocks(const typename DT<D>::In *__restrict__ values, const int64_t *__res
             // rows with both bounds in the window, as window indices [i_lo, i_hi)
             const int64_t r_hi = rb < cwb + cnwin - 1 ? rb : cwb + cnwin - 1;
             const int i_lo = (int)(r_lo - cwb), i_hi = (int)(r_hi - cwb);
-            if (i_hi - i_lo <= kWaveRows) {  // a wave per row
+            if (i_hi - i_lo <= kWaveRowsMax) {  // a wave per row
                 for (int i = i_lo + w; i < i_hi; i += NW) {
                     const int32_t sa = uniform(rw.s(i)), ea = uniform(rw.e(i));
                     int s, e;
@@ -1077,7 +1077,7 @@ k_bcast_blocks(const float *__restrict__ gout, const int64_t *__restrict__ offse
             const FillBounds rw{s_w, PEr};
             const int64_t r_hi = rb < cwb + cnwin - 1 ? rb : cwb + cnwin - 1;
             const int i_lo = (int)(r_lo - cwb), i_hi = (int)(r_hi - cwb);
-            if (i_hi - i_lo <= kWaveRows) {
+            if (i_hi - i_lo <= kWaveRowsMax) {
                 for (int i = i_lo + w; i < i_hi; i += NW) {
                     int s, e;
                     seg_in_chunk(uniform(rw.s(i)), uniform(rw.e(i)), C0, n, &s, &e);
@@ -1132,6 +1132,126 @@ k_bcast_blocks(const float *__restrict__ gout, const int64_t *__restrict__ offse
         }
         __syncthreads();
     }
+}
+
+// ---------------------------------------------------------------- rows by lane groups
+// Small inputs (up to kSmallVals values), where the search and staging of the
+// chunked kernels are all latency, and many rows of short to ordinary length,
+// where a block of the row-span kernel has little to stream between its round
+// trips (offsets, values, store).  A group of G lanes takes one row, every load
+// of a row of up to U G vectors in flight at once; longer rows are then taken by
+// the whole block, U vectors per thread in flight, so that a single long row
+// streams as in the kernels this one replaces.
+//
+// us before and now (sum, launches replayed from a graph): 300 rows, 23 001
+// values 10.1, 2.5; 1000 rows, 12 357 values 18.8, 2.5; 65 536 rows of mean
+// length 5, 21, 37 and 79 10.7, 12.1, 12.5 and 13.4, now 4.3, 4.3, 4.5 and 5.7;
+// 20 000 rows of mean length 143 and 489 9.5 and 12.4, now 5.0 and (row-span)
+// the same.  The lines between them, by mean length: 16 lanes and four vectors
+// up to 48, 16 lanes and eight up to 100, a wave and four up to 300 while the
+// row-span grid would not fill the chip several times (at 65 536 rows of mean
+// 143 15.1 against its 14.7).
+constexpr int64_t kSmallVals = 131072, kSmallRows = 32768;
+constexpr int64_t kShortAvg = 48, kMidAvg = 100, kWaveAvg = 300, kWaveRows = 32768;
+constexpr int64_t kBcastAvg = 200;  // the reverse, 16 lanes per row: 65 536 rows of mean 79, 143 10.0, 11.8 us, now 6.8, 9.4
+constexpr int NTS = 1024;
+
+// V consecutive elements at element alignment
+template <class In, class Vec> __device__ __forceinline__ Vec load_vec(const In *p) {
+    Vec v;
+    typedef In Unaligned __attribute__((ext_vector_type(sizeof(Vec) / sizeof(In)), aligned(sizeof(In))));
+    const Unaligned u = *reinterpret_cast<const Unaligned *>(p);
+    __builtin_memcpy(&v, &u, sizeof v);
+    return v;
+}
+
+template <mx_dtype D, int OP, int NTB, int G, int U>
+__global__ void __launch_bounds__(NTB) k_seg_groups(const typename DT<D>::In *__restrict__ values,
+                                                    const int64_t *__restrict__ offsets, int64_t nseg,
+                                                    typename DT<D>::Acc ne, typename DT<D>::Acc *__restrict__ out) {
+    using In = typename DT<D>::In;
+    using Acc = typename DT<D>::Acc;
+    using Vec = typename DT<D>::Vec;
+    using R = Red<OP, Acc>;
+    constexpr int V = DT<D>::kVec, ROWS = NTB / G;
+    __shared__ int64_t soff[ROWS + 1];
+    __shared__ Acc part[NTB / kWave];
+    const int t = threadIdx.x;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
+    const int nrows = (int)(nseg - r0 < ROWS ? nseg - r0 : ROWS);
+    if (t <= nrows) soff[t] = offsets[r0 + t];
+    __syncthreads();
+    // lane l of L folds the vectors l, l + L, ... of [s, e), then the remainder
+    auto fold = [&](int64_t s, int64_t e, int l, int L) {
+        Acc a = R::id();
+        const int64_t nv = (e - s) / V;
+        const In *p = values + s;
+        for (int64_t i = l; i < nv; i += (int64_t)U * L) {
+            Vec x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + (int64_t)u * L < nv) x[u] = load_vec<In, Vec>(p + (i + (int64_t)u * L) * V);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + (int64_t)u * L < nv) {
+#pragma unroll
+                    for (int j = 0; j < V; ++j) a = R::ap(a, Acc(vget<Vec, In>(x[u], j)));
+                }
+        }
+        if (s + nv * V + l < e) a = R::ap(a, Acc(p[nv * V + l]));
+        return a;
+    };
+    constexpr int64_t kCap = (int64_t)G * U * V;  // longest row a group takes
+    const int k = t / G, l = t % G;
+    const int64_t s = k < nrows ? soff[k] : 0, e = k < nrows ? soff[k + 1] : 0;
+    const bool mine = e - s <= kCap;
+    const Acc v = group_reduce<R, G>(mine ? fold(s, e, l, G) : R::id());
+    if (l == 0 && k < nrows && mine) out[r0 + k] = s < e ? R::ap(ne, v) : ne;
+    if (!__syncthreads_or(!mine)) return;
+    for (int q = 0; q < nrows; ++q) {
+        const int64_t qs = soff[q], qe = soff[q + 1];
+        if (qe - qs <= kCap) continue;  // alike in every thread
+        const Acc a = wave_reduce<R>(fold(qs, qe, t, NTB));
+        if ((t & (kWave - 1)) == 0) part[t / kWave] = a;
+        __syncthreads();
+        if (t == 0) {
+            Acc z = part[0];
+            for (int o = 1; o < NTB / kWave; ++o) z = R::ap(z, part[o]);
+            out[r0 + q] = R::ap(ne, z);
+        }
+        __syncthreads();
+    }
+}
+
+// The reverse of the row sums for the same inputs: a group writes its row, the
+// whole block the longer ones.
+template <int G>
+__global__ void __launch_bounds__(NT) k_bcast_groups(const float *__restrict__ gout,
+                                                     const int64_t *__restrict__ offsets, int64_t nseg,
+                                                     float *__restrict__ gval) {
+    constexpr int ROWS = NT / G;
+    __shared__ int64_t soff[ROWS + 1];
+    __shared__ float sg[ROWS];
+    const int t = threadIdx.x;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
+    const int nrows = (int)(nseg - r0 < ROWS ? nseg - r0 : ROWS);
+    if (t <= nrows) soff[t] = offsets[r0 + t];
+    if (t < nrows) sg[t] = gout[r0 + t];
+    __syncthreads();
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    auto fill = [&](int64_t s, int64_t e, float g, int l, int L) {
+        const int64_t nv = (e - s) / 4;
+        for (int64_t i = l; i < nv; i += L) *reinterpret_cast<f4u *>(gval + s + 4 * i) = f4u{g, g, g, g};
+        if (s + 4 * nv + l < e) gval[s + 4 * nv + l] = g;
+    };
+    constexpr int64_t kCap = (int64_t)G * 64;
+    const int k = t / G;
+    const int64_t s = k < nrows ? soff[k] : 0, e = k < nrows ? soff[k + 1] : 0;
+    const bool mine = e - s <= kCap;
+    if (mine && s < e) fill(s, e, sg[k], t % G, G);
+    if (!__syncthreads_or(!mine)) return;
+    for (int q = 0; q < nrows; ++q)
+        if (soff[q + 1] - soff[q] > kCap) fill(soff[q], soff[q + 1], sg[q], t, NT);
 }
 
 // Rows per block of the row-chunked schedule the generated map-body kernels
@@ -1372,6 +1492,21 @@ mx_status launch_seg(bool plain, const void *values, int64_t nval, const int64_t
         const DeviceInfo *d;
         if (mx_status st = device_info(&d)) return st;
         const bool vec = aligned16(values);
+        const bool small = nval <= kSmallVals && nseg <= kSmallRows;
+        const bool wave = nval <= kWaveAvg * nseg && nseg <= kWaveRows;
+        if (small || (seg_span_path(nseg, nval, d) && (nval <= kMidAvg * nseg || wave))) {
+            MX_REQUIRE(ceil_div(nseg, NT / 16) <= 0x7fffffff, MX_ERR_SHAPE, "mx_segmented_reduce: too many rows");
+            auto go = [&](auto kernel, int threads, int group) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(nseg, threads / group)), dim3(threads), 0, s,
+                                   (const In *)values, off, nseg, ne, (Acc *)out);
+            };
+            if (small && nval <= kShortAvg * nseg) go(k_seg_groups<D, OP, NTS, 16, 4>, NTS, 16);
+            else if (small) go(k_seg_groups<D, OP, NTS, kWave, 4>, NTS, kWave);
+            else if (nval <= kShortAvg * nseg) go(k_seg_groups<D, OP, NT, 16, 4>, NT, 16);
+            else if (nval <= kMidAvg * nseg) go(k_seg_groups<D, OP, NT, 16, 8>, NT, 16);
+            else go(k_seg_groups<D, OP, NT, kWave, 4>, NT, kWave);
+            return last_launch("mx_segmented_reduce");
+        }
         if (seg_span_path(nseg, nval, d)) {
             const int rb = span_rows(nseg, d);
             const int64_t grid = ceil_div(nseg, rb);
@@ -1475,6 +1610,16 @@ mx_status segmented_broadcast(const float *gout, const int64_t *off, int64_t nse
     MX_REQUIRE(nch <= 0x7fffffff, MX_ERR_SHAPE, "mx_segmented_sum_adjoint_f32: too many values");
     const DeviceInfo *d;
     if (mx_status st = device_info(&d)) return st;
+    const bool few = nval <= kBcastAvg * nseg;
+    if ((nval <= kSmallVals && nseg <= kSmallRows) || (few && seg_span_path(nseg, nval, d))) {
+        const int64_t grid = ceil_div(nseg, NT / (few ? 16 : kWave));
+        MX_REQUIRE(grid <= 0x7fffffff, MX_ERR_SHAPE, "mx_segmented_sum_adjoint_f32: too many rows");
+        if (few)
+            hipLaunchKernelGGL(k_bcast_groups<16>, dim3((unsigned)grid), dim3(NT), 0, s, gout, off, nseg, gval);
+        else
+            hipLaunchKernelGGL(k_bcast_groups<kWave>, dim3((unsigned)grid), dim3(NT), 0, s, gout, off, nseg, gval);
+        return last_launch("mx_segmented_sum_adjoint_f32");
+    }
     if (seg_span_path(nseg, nval, d)) {
         const int rb = span_rows(nseg, d);
         const int64_t grid = ceil_div(nseg, rb);
