@@ -85,6 +85,17 @@ constexpr int kRegs = 16, kMaxInsn = 64, kMaxIn = 4;
 constexpr int NT = 256;          // threads per block of every generated kernel
 constexpr int kGroupsPerIt = 4;  // vector groups per thread and loop iteration
 constexpr int kMaxRedBlocks = 2048;  // eight per CU resident at once: one round, longer-lived threads
+constexpr int kOneBlockChunks = 4;   // chunks folded by a single block, whose call is one launch
+constexpr int kMaxPassBlocks = 65536;
+// The memory-side cache.  A pass over less keeps its inputs there for the next
+// reader (64 MB of inputs, then read again: 32.6 us the two, 36.9 us with loads
+// past it); of a larger one little would be left (1 GB: 542 us and 521 us).
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+
+// 16-byte groups per array and thread that an element-wise pass holds in
+// flight: four were the fastest with two inputs, and with four inputs, a seed
+// and their results two are what fits the registers of eight waves per SIMD
+int chunk_groups(int nin) { return nin >= 3 ? 2 : 4; }
 
 bool reads_a(int op) { return op >= MX_X_ADD; }
 bool reads_b(int op) { return op >= MX_X_ADD && op <= MX_X_MAX; }
@@ -224,9 +235,12 @@ std::string gen_source(const mx_expr &e) {
 
     std::string s;
     s += "// generated by the mx library from a straight-line map body\n";
-    s += f32 ? "typedef float T;\ntypedef float4 VT;\n#define VW 4\n" : "typedef double T;\ntypedef double2 VT;\n#define VW 2\n";
+    s += f32 ? "typedef float T;\n#define VW 4\n" : "typedef double T;\n#define VW 2\n";
+    // element alignment is enough for 16-byte accesses: any slice of an array takes the vector path
+    s += "typedef T VT __attribute__((ext_vector_type(VW), aligned(sizeof(T))));\n";
     s += "#define NT " + std::to_string(NT) + "\n#define GPI " + std::to_string(kGroupsPerIt) + "\n";
     s += "#define NIN " + std::to_string(e.nin) + "\n";
+    s += "#define CG " + std::to_string(chunk_groups(e.nin)) + "\n";
     s += "#define SU (NIN >= 4 ? 2 : NIN >= 2 ? 4 : 8)\n";  // 16-byte groups per input in flight per lane
     s += "__device__ __forceinline__ T mx_body(" + in_params + ") {\n#pragma clang fp contract(off)\n" + fwd +
          "    return v" + std::to_string(os) + ";\n}\n";
@@ -234,105 +248,141 @@ std::string gen_source(const mx_expr &e) {
          ", const T seed, T &gi0, T &gi1, T &gi2, T &gi3) {\n#pragma clang fp contract(off)\n" + fwd +
          "    gi0 = (T)0; gi1 = (T)0; gi2 = (T)0; gi3 = (T)0;\n" + rev + "}\n";
     s += R"(
-__device__ __forceinline__ T mx_vget(const VT &v, int j) { return reinterpret_cast<const T *>(&v)[j]; }
-__device__ __forceinline__ void mx_vset(VT &v, int j, T x) { reinterpret_cast<T *>(&v)[j] = x; }
 #define MX_PTRS const T *__restrict__ p0, const T *__restrict__ p1, const T *__restrict__ p2, const T *__restrict__ p3
 #define MX_VPTRS const VT *q0 = (const VT *)p0, *q1 = (const VT *)p1, *q2 = (const VT *)p2, *q3 = (const VT *)p3
 
+// one group of VW elements; STREAM: past the caches (the pass is larger than they are)
+template <bool STREAM> __device__ __forceinline__ VT mx_ld(const VT *q) {
+    if constexpr (STREAM) return __builtin_nontemporal_load(q);
+    else return *q;
+}
 // group j of VW elements of every input, read only for the inputs that exist
-__device__ __forceinline__ void mx_load_group(MX_PTRS, long long j, VT (&a)[4]) {
+template <bool STREAM = false> __device__ __forceinline__ void mx_load_group(MX_PTRS, long long j, VT (&a)[4]) {
     MX_VPTRS;
-    if (NIN > 0) a[0] = q0[j];
-    if (NIN > 1) a[1] = q1[j];
-    if (NIN > 2) a[2] = q2[j];
-    if (NIN > 3) a[3] = q3[j];
+    if (NIN > 0) a[0] = mx_ld<STREAM>(q0 + j);
+    if (NIN > 1) a[1] = mx_ld<STREAM>(q1 + j);
+    if (NIN > 2) a[2] = mx_ld<STREAM>(q2 + j);
+    if (NIN > 3) a[3] = mx_ld<STREAM>(q3 + j);
 }
 __device__ __forceinline__ T mx_body_at(const VT (&a)[4], int e) {
-    return mx_body(NIN > 0 ? mx_vget(a[0], e) : (T)0, NIN > 1 ? mx_vget(a[1], e) : (T)0,
-                   NIN > 2 ? mx_vget(a[2], e) : (T)0, NIN > 3 ? mx_vget(a[3], e) : (T)0);
+    return mx_body(NIN > 0 ? a[0][e] : (T)0, NIN > 1 ? a[1][e] : (T)0, NIN > 2 ? a[2][e] : (T)0,
+                   NIN > 3 ? a[3][e] : (T)0);
 }
 __device__ __forceinline__ T mx_body_i(MX_PTRS, long long i) {
     return mx_body(NIN > 0 ? p0[i] : (T)0, NIN > 1 ? p1[i] : (T)0, NIN > 2 ? p2[i] : (T)0, NIN > 3 ? p3[i] : (T)0);
 }
 
-// out[i] = body(x_i).  vec: every pointer 16-byte aligned; then groups of VW
-// elements, GPI groups in flight per thread, the tail element by element.
-extern "C" __global__ void __launch_bounds__(NT) mx_xmap(MX_PTRS, T *__restrict__ out, long long n, int vec) {
-    const long long tid = (long long)blockIdx.x * NT + threadIdx.x, nt = (long long)gridDim.x * NT;
-    long long done = 0;
-    if (vec) {
-        const long long nv = n / VW;
-        VT *qo = (VT *)out;
-        long long j = tid;
-        for (; j + (GPI - 1) * nt < nv; j += GPI * nt) {
-            VT a[GPI][4];
+// The element-wise passes.  A block takes contiguous chunks of CG x NT groups of
+// every array, all its loads in flight together, and with up to 65536 blocks
+// a chunk is all it does: the blocks that run together then walk each array as
+// one front, where a grid-wide stride made every wave touch CG distant pages.
+// The stores go past the caches, and so do the loads of a pass larger than
+// they are (stream != 0).  Bound by HBM: the reverse of a two-input body over
+// 2^26 elements (1.07 GB) went from 194 us to 172 us (6.2 TB/s; four groups
+// with plain loads and stores 189 us, one group 181 us, two 178 us); at 2^20
+// from 4.1 us to 3.0 us.
+#define CHUNK (CG * NT)
+template <bool STREAM> __device__ __forceinline__ void mx_map_chunk(MX_PTRS, VT *__restrict__ qo, long long j) {
+    VT a[CG][4];
 #pragma unroll
-            for (int u = 0; u < GPI; ++u) mx_load_group(p0, p1, p2, p3, j + u * nt, a[u]);
+    for (int u = 0; u < CG; ++u) mx_load_group<STREAM>(p0, p1, p2, p3, j + u * NT, a[u]);
 #pragma unroll
-            for (int u = 0; u < GPI; ++u) {
-                VT r;
+    for (int u = 0; u < CG; ++u) {
+        VT r;
 #pragma unroll
-                for (int e = 0; e < VW; ++e) mx_vset(r, e, mx_body_at(a[u], e));
-                qo[j + u * nt] = r;
+        for (int e = 0; e < VW; ++e) r[e] = mx_body_at(a[u], e);
+        __builtin_nontemporal_store(r, qo + j + u * NT);
+    }
+}
+
+// out[i] = body(x_i)
+extern "C" __global__ void __launch_bounds__(NT) mx_xmap(MX_PTRS, T *__restrict__ out, long long n, int stream) {
+    const long long nv = n / VW;
+    VT *qo = (VT *)out;
+    for (long long c = (long long)blockIdx.x * CHUNK; c < nv; c += (long long)gridDim.x * CHUNK) {
+        const long long j = c + threadIdx.x;
+        if (c + CHUNK <= nv) {
+            if (stream) mx_map_chunk<true>(p0, p1, p2, p3, qo, j);
+            else mx_map_chunk<false>(p0, p1, p2, p3, qo, j);
+        } else {
+            for (long long i = j; i < nv; i += NT) {
+                VT a[4], r;
+                mx_load_group(p0, p1, p2, p3, i, a);
+#pragma unroll
+                for (int e = 0; e < VW; ++e) r[e] = mx_body_at(a, e);
+                qo[i] = r;
             }
         }
-        for (; j < nv; j += nt) {
-            VT a[4];
-            mx_load_group(p0, p1, p2, p3, j, a);
-            VT r;
-#pragma unroll
-            for (int e = 0; e < VW; ++e) mx_vset(r, e, mx_body_at(a, e));
-            qo[j] = r;
-        }
-        done = nv * VW;
     }
-    for (long long i = done + tid; i < n; i += nt) out[i] = mx_body_i(p0, p1, p2, p3, i);
+    const long long i = nv * VW + threadIdx.x;  // the last n % VW elements
+    if (blockIdx.x == gridDim.x - 1 && i < n) out[i] = mx_body_i(p0, p1, p2, p3, i);
 }
 
 // Reverse mode: gk[i] = seed_i * d body / d input k (null outputs skipped).
+__device__ __forceinline__ void mx_vjp_group(const VT (&a)[4], const VT &go, bool hg, bool hs, T gs, VT *r0, VT *r1,
+                                             VT *r2, VT *r3) {
+    VT o0, o1, o2, o3;
+#pragma unroll
+    for (int e = 0; e < VW; ++e) {
+        const T seed = hg ? (hs ? go[e] * gs : go[e]) : gs;
+        T d0, d1, d2, d3;
+        mx_body_vjp(NIN > 0 ? a[0][e] : (T)0, NIN > 1 ? a[1][e] : (T)0, NIN > 2 ? a[2][e] : (T)0,
+                    NIN > 3 ? a[3][e] : (T)0, seed, d0, d1, d2, d3);
+        o0[e] = d0; o1[e] = d1; o2[e] = d2; o3[e] = d3;
+    }
+    if (NIN > 0 && r0) __builtin_nontemporal_store(o0, r0);
+    if (NIN > 1 && r1) __builtin_nontemporal_store(o1, r1);
+    if (NIN > 2 && r2) __builtin_nontemporal_store(o2, r2);
+    if (NIN > 3 && r3) __builtin_nontemporal_store(o3, r3);
+}
+#define MX_VJP_OUT(i) r0 ? r0 + (i) : r0, r1 ? r1 + (i) : r1, r2 ? r2 + (i) : r2, r3 ? r3 + (i) : r3
+template <bool STREAM>
+__device__ __forceinline__ void mx_vjp_chunk(MX_PTRS, const VT *__restrict__ qg, bool hs, T gs, VT *__restrict__ r0,
+                                             VT *__restrict__ r1, VT *__restrict__ r2, VT *__restrict__ r3,
+                                             long long j) {
+    const bool hg = qg != nullptr;
+    VT a[CG][4], go[CG];
+#pragma unroll
+    for (int u = 0; u < CG; ++u) {
+        mx_load_group<STREAM>(p0, p1, p2, p3, j + u * NT, a[u]);
+        if (hg) go[u] = mx_ld<STREAM>(qg + j + u * NT);
+    }
+#pragma unroll
+    for (int u = 0; u < CG; ++u) mx_vjp_group(a[u], go[u], hg, hs, gs, MX_VJP_OUT(j + u * NT));
+}
 extern "C" __global__ void __launch_bounds__(NT) mx_xvjp(MX_PTRS, const T *__restrict__ gout,
                                                            const T *__restrict__ gscale, T *__restrict__ g0,
                                                            T *__restrict__ g1, T *__restrict__ g2,
-                                                           T *__restrict__ g3, long long n, int vec) {
-    const long long tid = (long long)blockIdx.x * NT + threadIdx.x, nt = (long long)gridDim.x * NT;
+                                                           T *__restrict__ g3, long long n, int stream) {
     const bool hg = gout != nullptr, hs = gscale != nullptr;
     const T gs = hs ? *gscale : (T)1;
-    long long done = 0;
-    if (vec) {
-        const long long nv = n / VW;
-        const VT *qg = (const VT *)gout;
-        VT *r0 = (VT *)g0, *r1 = (VT *)g1, *r2 = (VT *)g2, *r3 = (VT *)g3;
-        for (long long j = tid; j < nv; j += nt) {
-            VT a[4];
-            mx_load_group(p0, p1, p2, p3, j, a);
-            VT go;
-            if (hg) go = qg[j];
-            VT o0, o1, o2, o3;
-#pragma unroll
-            for (int e = 0; e < VW; ++e) {
-                const T seed = hg ? (hs ? mx_vget(go, e) * gs : mx_vget(go, e)) : gs;
-                T d0, d1, d2, d3;
-                mx_body_vjp(NIN > 0 ? mx_vget(a[0], e) : (T)0, NIN > 1 ? mx_vget(a[1], e) : (T)0,
-                            NIN > 2 ? mx_vget(a[2], e) : (T)0, NIN > 3 ? mx_vget(a[3], e) : (T)0, seed, d0, d1,
-                            d2, d3);
-                mx_vset(o0, e, d0); mx_vset(o1, e, d1); mx_vset(o2, e, d2); mx_vset(o3, e, d3);
+    const long long nv = n / VW;
+    const VT *qg = (const VT *)gout;
+    VT *r0 = (VT *)g0, *r1 = (VT *)g1, *r2 = (VT *)g2, *r3 = (VT *)g3;
+    for (long long c = (long long)blockIdx.x * CHUNK; c < nv; c += (long long)gridDim.x * CHUNK) {
+        const long long j = c + threadIdx.x;
+        if (c + CHUNK <= nv) {
+            if (stream) mx_vjp_chunk<true>(p0, p1, p2, p3, qg, hs, gs, r0, r1, r2, r3, j);
+            else mx_vjp_chunk<false>(p0, p1, p2, p3, qg, hs, gs, r0, r1, r2, r3, j);
+        } else {
+            for (long long i = j; i < nv; i += NT) {
+                VT a[4], go;
+                mx_load_group(p0, p1, p2, p3, i, a);
+                if (hg) go = qg[i];
+                mx_vjp_group(a, go, hg, hs, gs, MX_VJP_OUT(i));
             }
-            if (r0) r0[j] = o0;
-            if (r1) r1[j] = o1;
-            if (r2) r2[j] = o2;
-            if (r3) r3[j] = o3;
         }
-        done = nv * VW;
     }
-    for (long long i = done + tid; i < n; i += nt) {
+    const long long i = nv * VW + threadIdx.x;  // the last n % VW elements
+    if (blockIdx.x == gridDim.x - 1 && i < n) {
         const T seed = hg ? (hs ? gout[i] * gs : gout[i]) : gs;
         T d0, d1, d2, d3;
         mx_body_vjp(NIN > 0 ? p0[i] : (T)0, NIN > 1 ? p1[i] : (T)0, NIN > 2 ? p2[i] : (T)0,
                     NIN > 3 ? p3[i] : (T)0, seed, d0, d1, d2, d3);
-        if (g0) g0[i] = d0;
-        if (g1) g1[i] = d1;
-        if (g2) g2[i] = d2;
-        if (g3) g3[i] = d3;
+        if (NIN > 0 && g0) g0[i] = d0;
+        if (NIN > 1 && g1) g1[i] = d1;
+        if (NIN > 2 && g2) g2[i] = d2;
+        if (NIN > 3 && g3) g3[i] = d3;
     }
 }
 
@@ -368,35 +418,45 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xscatter(MX_PTRS, const long
     for (int w = 1; w < NT / 64; ++w) r = mx_op_)" + nm + R"((r, sh[w]);
     return r;
 }
-// each thread folds its elements in a fixed order; one partial per block
-extern "C" __global__ void __launch_bounds__(NT) mx_xred_)" + nm + R"((MX_PTRS, long long n, int vec, T *__restrict__ partial) {
+// One partial per block.  A block folds contiguous chunks of GPI x NT groups of
+// every input, one accumulator per vector lane (the fold order depends on n
+// alone).  Bound by HBM: two inputs of 2^26 float32 took 111 us with a
+// grid-wide stride and take 87 us (6.2 TB/s).  Plain loads: past the caches
+// the pass takes 79 us, but a reverse pass over the same inputs then finds
+// nothing of them in the memory-side cache (the two 254 us instead of 233 us).
+// The only block of a small call writes the result itself (direct != 0:
+// partial is the output), one launch instead of two.
+extern "C" __global__ void __launch_bounds__(NT) mx_xred_)" + nm + R"((MX_PTRS, long long n, T ne, int direct, T *__restrict__ partial) {
     __shared__ T sh[NT / 64];
-    const long long tid = (long long)blockIdx.x * NT + threadIdx.x, nt = (long long)gridDim.x * NT;
-    T acc = )" + id + R"(;
-    long long done = 0;
-    if (vec) {
-        const long long nv = n / VW;
-        long long j = tid;
-        for (; j + (GPI - 1) * nt < nv; j += GPI * nt) {
+    const long long nv = n / VW;
+    T acc[VW];
+#pragma unroll
+    for (int e = 0; e < VW; ++e) acc[e] = )" + id + R"(;
+    for (long long c = (long long)blockIdx.x * (GPI * NT); c < nv; c += (long long)gridDim.x * (GPI * NT)) {
+        const long long j = c + threadIdx.x;
+        if (c + GPI * NT <= nv) {
             VT a[GPI][4];
 #pragma unroll
-            for (int u = 0; u < GPI; ++u) mx_load_group(p0, p1, p2, p3, j + u * nt, a[u]);
+            for (int u = 0; u < GPI; ++u) mx_load_group(p0, p1, p2, p3, j + u * NT, a[u]);
 #pragma unroll
             for (int u = 0; u < GPI; ++u)
 #pragma unroll
-                for (int e = 0; e < VW; ++e) acc = mx_op_)" + nm + R"((acc, mx_body_at(a[u], e));
-        }
-        for (; j < nv; j += nt) {
-            VT a[4];
-            mx_load_group(p0, p1, p2, p3, j, a);
+                for (int e = 0; e < VW; ++e) acc[e] = mx_op_)" + nm + R"((acc[e], mx_body_at(a[u], e));
+        } else {
+            for (long long i = j; i < nv; i += NT) {
+                VT a[4];
+                mx_load_group(p0, p1, p2, p3, i, a);
 #pragma unroll
-            for (int e = 0; e < VW; ++e) acc = mx_op_)" + nm + R"((acc, mx_body_at(a, e));
+                for (int e = 0; e < VW; ++e) acc[e] = mx_op_)" + nm + R"((acc[e], mx_body_at(a, e));
+            }
         }
-        done = nv * VW;
     }
-    for (long long i = done + tid; i < n; i += nt) acc = mx_op_)" + nm + R"((acc, mx_body_i(p0, p1, p2, p3, i));
-    const T r = mx_block_)" + nm + R"((acc, sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = r;
+    const long long i = nv * VW + threadIdx.x;  // the last n % VW elements
+    if (blockIdx.x == gridDim.x - 1 && i < n) acc[0] = mx_op_)" + nm + R"((acc[0], mx_body_i(p0, p1, p2, p3, i));
+#pragma unroll
+    for (int e = 1; e < VW; ++e) acc[0] = mx_op_)" + nm + R"((acc[0], acc[e]);
+    const T r = mx_block_)" + nm + R"((acc[0], sh);
+    if (threadIdx.x == 0) partial[blockIdx.x] = direct ? mx_op_)" + nm + R"((ne, r) : r;
 }
 // the partials in block order (thread t takes t, t + NT, ...), then ne op total
 extern "C" __global__ void __launch_bounds__(NT) mx_xfin_)" + nm + R"((const T *__restrict__ partial, int nb, T ne, T *__restrict__ out) {
@@ -552,10 +612,16 @@ int64_t stream_blocks(int64_t n, int vw, int num_cus) {
     return b < 1 ? 1 : (b > cap ? cap : b);
 }
 
+// blocks of an element-wise pass: one chunk each while they are few enough
+int64_t pass_blocks(int64_t n, int vw, int nin) {
+    const int64_t b = ceil_div(n, (int64_t)NT * vw * chunk_groups(nin));
+    return b > kMaxPassBlocks ? kMaxPassBlocks : b;
+}
+
 // the partial pass's grid depends only on n, so the result does not depend on the device
 int64_t reduce_blocks(int64_t n, int vw) {
     const int64_t b = ceil_div(n > 0 ? n : 1, (int64_t)NT * vw * kGroupsPerIt);
-    return b > kMaxRedBlocks ? kMaxRedBlocks : b;
+    return b > kMaxRedBlocks ? kMaxRedBlocks : b <= kOneBlockChunks ? 1 : b;
 }
 
 // Debug mode of the indexed-write loop: every index in range and no slot hit
@@ -648,19 +714,13 @@ mx_status mx_expr_map(mx_expr *e, const void *const *in_dev, int64_t n, void *ou
     if (n == 0) return MX_OK;
     const Compiled *c;
     if (mx_status st = compile(*e, &c)) return st;
-    const DeviceInfo *dv;
-    if (mx_status st = device_info(&dv)) return st;
     const void *p[kMaxIn] = {};
-    bool al = aligned16(out_dev);
-    for (int k = 0; k < e->nin; ++k) {
-        p[k] = in_dev[k];
-        al = al && aligned16(p[k]);
-    }
+    for (int k = 0; k < e->nin; ++k) p[k] = in_dev[k];
     const int vw = e->dtype == MX_F32 ? 4 : 2;
-    int vec = al ? 1 : 0;
+    int past = n * (int64_t)dtype_size(e->dtype) * (e->nin + 1) > kCacheBytes;
     long long nn = n;
-    void *args[] = {&p[0], &p[1], &p[2], &p[3], &out_dev, &nn, &vec};
-    return launch(c->map, stream_blocks(n, vw, dv->num_cus), stream, args, who);
+    void *args[] = {&p[0], &p[1], &p[2], &p[3], &out_dev, &nn, &past};
+    return launch(c->map, pass_blocks(n, vw, e->nin), stream, args, who);
 }
 
 size_t mx_expr_workspace_bytes(const mx_expr *e, int64_t n) {
@@ -681,28 +741,21 @@ mx_status mx_expr_map_reduce(mx_expr *e, mx_redop op, const void *const *in_dev,
     const Compiled *c;
     if (mx_status st = compile(*e, &c)) return st;
     const void *p[kMaxIn] = {};
-    bool al = true;
-    for (int k = 0; k < e->nin && n > 0; ++k) {
-        p[k] = in_dev[k];
-        al = al && aligned16(p[k]);
-    }
-    const int vw = e->dtype == MX_F32 ? 4 : 2;
-    int vec = al ? 1 : 0;
+    for (int k = 0; k < e->nin && n > 0; ++k) p[k] = in_dev[k];
     long long nn = n;
     void *partial = (char *)ws + kCounterBytes;
-    const int64_t nb = n > 0 ? reduce_blocks(n, vw) : 0;
+    const int64_t nb = n > 0 ? reduce_blocks(n, e->dtype == MX_F32 ? 4 : 2) : 0;
+    int nbi = (int)nb, direct = nb == 1;
+    float ne32 = 0.f;
+    double ne64 = 0.0;
+    void *ne = e->dtype == MX_F32 ? (void *)&ne32 : (void *)&ne64;
+    __builtin_memcpy(ne, ne_host, dtype_size(e->dtype));
     if (nb > 0) {
-        void *args[] = {&p[0], &p[1], &p[2], &p[3], &nn, &vec, &partial};
+        void *args[] = {&p[0], &p[1], &p[2], &p[3], &nn, ne, &direct, direct ? &out_dev : &partial};
         if (mx_status st = launch(c->red[op], nb, stream, args, who)) return st;
+        if (direct) return MX_OK;
     }
-    int nbi = (int)nb;
-    if (e->dtype == MX_F32) {
-        float ne = *(const float *)ne_host;
-        void *args[] = {&partial, &nbi, &ne, &out_dev};
-        return launch(c->fin[op], 1, stream, args, who);
-    }
-    double ne = *(const double *)ne_host;
-    void *args[] = {&partial, &nbi, &ne, &out_dev};
+    void *args[] = {&partial, &nbi, ne, &out_dev};
     return launch(c->fin[op], 1, stream, args, who);
 }
 
@@ -795,21 +848,19 @@ mx_status mx_expr_vjp(mx_expr *e, const void *const *in_dev, int64_t n, const vo
     if (n == 0) return MX_OK;
     const Compiled *c;
     if (mx_status st = compile(*e, &c)) return st;
-    const DeviceInfo *dv;
-    if (mx_status st = device_info(&dv)) return st;
     const void *p[kMaxIn] = {};
     void *gk[kMaxIn] = {};
-    bool al = gout_dev == nullptr || aligned16(gout_dev);
+    int arrays = e->nin + (gout_dev != nullptr);
     for (int k = 0; k < e->nin; ++k) {
         p[k] = in_dev[k];
         gk[k] = gin_dev[k];
-        al = al && aligned16(p[k]) && (gk[k] == nullptr || aligned16(gk[k]));
+        arrays += gk[k] != nullptr;
     }
     const int vw = e->dtype == MX_F32 ? 4 : 2;
-    int vec = al ? 1 : 0;
+    int past = n * (int64_t)dtype_size(e->dtype) * arrays > kCacheBytes;
     long long nn = n;
-    void *args[] = {&p[0], &p[1], &p[2], &p[3], &gout_dev, &gscale_dev, &gk[0], &gk[1], &gk[2], &gk[3], &nn, &vec};
-    return launch(c->vjp, stream_blocks(n, vw, dv->num_cus), stream, args, who);
+    void *args[] = {&p[0], &p[1], &p[2], &p[3], &gout_dev, &gscale_dev, &gk[0], &gk[1], &gk[2], &gk[3], &nn, &past};
+    return launch(c->vjp, pass_blocks(n, vw, e->nin), stream, args, who);
 }
 
 }  // extern "C"
