@@ -578,10 +578,12 @@ mx_status mx_kmeans_sse_grad_f32(const float *X_dev, int64_t n, int d, const flo
  *           gB[b_off + c] = sum_r A[a_off + r*cols + c] * g[r].
  * A plan cuts tasks into tiles of equal bytes, longest first: dots into
  * ranges of tile_elems elements, matvecs into whole-row ranges of about
- * 2 * tile_elems elements (one streamed operand instead of two);
- * forward and backward each run as one persistent launch (blocks_per_cu blocks
- * per compute unit pulling tiles with an atomic ticket) plus one combine
- * launch that adds multi-tile partials in tile order.  Results are
+ * 2 * tile_elems elements (one streamed operand instead of two), backward
+ * into at most what a block takes at once;
+ * forward and backward each run as one launch (a block per tile, at most
+ * blocks_per_cu of them resident on a compute unit)
+ * plus, if a task has several tiles, one combine launch that adds their
+ * partials in tile order.  Results are
  * deterministic for a given configuration. */
 typedef struct mx_batch_config {
     int32_t tile_elems;     /* >= 4096; default 16384 */

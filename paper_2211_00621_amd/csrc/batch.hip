@@ -1,4 +1,4 @@
-// Many uneven accelerated expressions in one persistent launch.
+// Many uneven accelerated expressions in one launch.
 //
 // The paper notes that expression acceleration pays off when work is
 // concentrated in few `accelerate` uses and that small problems leave the GPU
@@ -8,11 +8,11 @@
 //
 // Plan (host, once): every task is cut into tiles of equal bytes -- element
 // ranges of `tile_elems` for a dot (two streamed operands), whole-row ranges
-// of about 2 * `tile_elems` elements for a matvec (one) -- and the tiles are
-// ordered longest first.  Forward: a persistent grid pulls tiles
-// with an atomic ticket; a single-tile task writes its result, a multi-tile dot
+// of about 2 * `tile_elems` elements for a matvec (one); backward a tile is at
+// most what a block takes at once -- and the tiles are ordered longest first.  Forward: a block per tile;
+// a single-tile task writes its result, a multi-tile dot
 // writes one partial per tile.  A combine launch adds each task's partials in
-// tile order (deterministic for a given plan) and resets the ticket.  Backward
+// tile order (deterministic for a given plan).  Backward
 // (dot: ga = g b, gb = g a; matvec y = A x: gA = g x^T, gx = A^T g) has the same
 // structure, with per-tile partial column sums for gx.  No float atomics, no
 // cross-block fences.  The autotuner times candidate (tile_elems,
@@ -36,8 +36,11 @@ constexpr int NT = 256;
 constexpr int kDot = 0, kMatvec = 1;
 constexpr int kMinTile = 4096;
 constexpr int kXLds = 2048;  // matvec x staged in LDS up to this many columns
-
-inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+constexpr int NB = 512;      // threads of a backward block
+constexpr int kBwdVec = 2;   // 16-byte vectors per operand and thread of a dot's backward tile
+constexpr int64_t kDotChunk = 4 * kBwdVec * NB;  // elements of a dot's backward tile
+constexpr int kAdjRows = 8;  // rows of a matvec's backward that a thread has in flight
+constexpr int64_t kLongRow = 1 << 22;  // matvec rows past this length are walked one at a time backward
 
 struct TaskDev {
     int32_t kind, pad;
@@ -45,12 +48,11 @@ struct TaskDev {
     int64_t fwd_part, fwd_ntiles, bwd_part, bwd_ntiles;
 };
 
-// One tile, carrying the task fields its kernels need so that taking a tile
-// costs one descriptor load.
+// One tile, carrying the task fields its kernels need, the offsets those of its
+// first element or row, so that taking a tile costs one descriptor load.
 struct TileDev {
-    int32_t task, kind;
-    int64_t begin, end;  // dot: elements; matvec: rows
-    int64_t part;        // partial slot (float offset) or -1 to write the result directly
+    uint32_t kind, count;  // dot: elements; matvec: rows
+    int64_t part;          // partial slot (float offset) or -1 to write the result directly
     int64_t cols, a_off, b_off, out_off;
 };
 
@@ -64,292 +66,306 @@ __device__ __forceinline__ float row16_sum(float v) {
     return v;
 }
 
-// Tile loop of the persistent kernels: thread 0 takes a ticket, the block
-// reads it after a barrier and loads the tile descriptor.  (Taking the next
-// ticket while the current tile streams was measured slower: a busy block
-// then holds a tile an idle block could already be working on.)
-#define MX_TILE_LOOP_BEGIN                                                         \
-    __shared__ int64_t slot;                                                     \
-    for (;;) {                                                                   \
-        __syncthreads();                                                         \
-        if (threadIdx.x == 0) slot = (int64_t)atomicAdd(ticket, 1u);             \
-        __syncthreads();                                                         \
-        const int64_t t = slot;                                                  \
-        if (t >= ntiles) break;                                                  \
-        const TileDev tl = tiles[t];                                             \
-        const TileDev &tk = tl;
+// Four floats at any float address: element alignment is all a 16-byte access
+// needs, so tasks and rows of every offset and length take the same path.  The
+// address is a base that is the same in all lanes plus a 32-bit element offset
+// of the lane, which costs one register where a pointer per access costs two.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+template <bool PAST> __device__ __forceinline__ f4u ld4(const float *base, unsigned off) {
+    const f4u *q = reinterpret_cast<const f4u *>(reinterpret_cast<const char *>(base) + 4u * off);
+    if constexpr (PAST) return __builtin_nontemporal_load(q);
+    else return *q;
+}
+__device__ __forceinline__ void st4(f4u v, float *base, unsigned off) {
+    __builtin_nontemporal_store(v, reinterpret_cast<f4u *>(reinterpret_cast<char *>(base) + 4u * off));
+}
+// The same through a buffer descriptor (raw, range and offsets in bytes): a
+// vector outside the range reads as zeros and is not written, which is how rows
+// past a tile's end and vectors past a row's end are left out without a branch.
+// Vectors lie wholly inside or outside.
+typedef __amdgpu_buffer_rsrc_t buf;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+constexpr unsigned kOutside = 0x7fffff00u;  // an offset past every range
+constexpr int kPastCaches = 2;              // the non-temporal bit of a buffer access
+__device__ __forceinline__ buf make_buf(const float *p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, (int)bytes, 0x00027000);
+}
+template <bool PAST> __device__ __forceinline__ f4u bld4(buf b, unsigned off) {
+    return __builtin_bit_cast(f4u, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, PAST ? kPastCaches : 0));
+}
+__device__ __forceinline__ float bld1(buf b, unsigned off) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
+}
+__device__ __forceinline__ void bst4(f4u v, buf b, unsigned off) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), b, (int)off, 0, kPastCaches);
+}
+__device__ __forceinline__ float dot4(f4u a, f4u b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
 
-#define MX_TILE_LOOP_END }
-
-__global__ void __launch_bounds__(NT) k_batch_fwd(const TaskDev *__restrict__ tasks, const TileDev *__restrict__ tiles,
-                                                  int64_t ntiles, const float *__restrict__ A,
-                                                  const float *__restrict__ B, float *__restrict__ out,
-                                                  float *__restrict__ part, unsigned *ticket, int vec) {
-    __shared__ float red[NT / kWave];
-    __shared__ float xs[kXLds];
-    using R = Red<MX_ADD, float>;
-    MX_TILE_LOOP_BEGIN
-        if (tk.kind == kDot) {
-            const float *a = A + tk.a_off, *b = B + tk.b_off;
-            float ac[4] = {0.f, 0.f, 0.f, 0.f};
-            if (vec && ((tk.a_off | tk.b_off | tl.begin) & 3) == 0) {
-                // 16-byte vectors, four per operand in flight, scalar tail
-                const float4 *a4 = reinterpret_cast<const float4 *>(a), *b4 = reinterpret_cast<const float4 *>(b);
-                const int64_t ve = tl.end >> 2;
-                int64_t i = (tl.begin >> 2) + threadIdx.x;
-                for (; i + 3 * NT < ve; i += 4 * NT) {
-                    float4 x[4], y[4];
+// This thread's part of the dot product of n elements: contiguous chunks of
+// 4 NT vectors per operand, all in flight, the last chunk predicated.
+__device__ __forceinline__ float block_dot(const float *__restrict__ a, const float *__restrict__ b, int64_t n) {
+    const int64_t nv = n >> 2;
+    float ac[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t c = 0; c < nv; c += 4 * NT) {
+        const float *ac4 = a + 4 * c, *bc4 = b + 4 * c;
+        f4u x[4], y[4];
+        if (c + 4 * NT <= nv) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        x[u] = a4[i + u * NT];
-                        y[u] = b4[i + u * NT];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) ac[u] += x[u].x * y[u].x + x[u].y * y[u].y + x[u].z * y[u].z + x[u].w * y[u].w;
-                }
-                for (; i < ve; i += NT) {
-                    const float4 x = a4[i], y = b4[i];
-                    ac[0] += x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
-                }
-                for (int64_t e = 4 * ve + threadIdx.x; e < tl.end; e += NT) ac[1] += a[e] * b[e];
-            } else {
-                int64_t e = tl.begin + threadIdx.x;
-                for (; e + 3 * NT < tl.end; e += 4 * NT) {
-                    float av[4], bv[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        av[u] = a[e + u * NT];
-                        bv[u] = b[e + u * NT];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) ac[u] += av[u] * bv[u];
-                }
-                for (; e < tl.end; e += NT) ac[0] += a[e] * b[e];
-            }
-            float acc = block_reduce<R, NT>((ac[0] + ac[1]) + (ac[2] + ac[3]), red);
-            if (threadIdx.x == 0) {
-                if (tl.part >= 0) part[tl.part] = acc;
-                else out[tk.out_off] = acc;
+            for (int u = 0; u < 4; ++u) {
+                x[u] = ld4<false>(ac4, 4 * (threadIdx.x + u * NT));
+                y[u] = ld4<false>(bc4, 4 * (threadIdx.x + u * NT));
             }
         } else {
-            // 16 lanes per row, 16 rows at a time.  x is staged in LDS once
-            // per tile (when it fits), so every row can be read with 16-byte
-            // loads whatever its alignment: a scalar head up to the next
-            // 16-byte boundary of A, the vector body (eight loads per lane in
-            // flight), a scalar tail; x values come from LDS.
-            const int grp = threadIdx.x >> 4, l = threadIdx.x & 15;
-            const int64_t c = tk.cols;
-            const float *x = B + tk.b_off;
-            const bool stage = vec && c <= kXLds;
-            if (stage) {
-                for (int64_t q = threadIdx.x; q < c; q += NT) xs[q] = x[q];
-                __syncthreads();
-            }
-            for (int64_t r0 = tl.begin; r0 < tl.end; r0 += NT / 16) {
-                const int64_t r = r0 + grp;
-                float ac[4] = {0.f, 0.f, 0.f, 0.f};
-                if (r < tl.end) {
-                    const int64_t e0 = tk.a_off + r * c;  // row start in A
-                    const float *row = A + e0;
-                    if (stage) {
-                        const int64_t head = ((4 - (e0 & 3)) & 3) < c ? ((4 - (e0 & 3)) & 3) : c;
-                        const int64_t nb4 = (c - head) >> 2;
-                        const float4 *row4 = reinterpret_cast<const float4 *>(row + head);
-                        if (l < head) ac[1] += row[l] * xs[l];
-                        // eight loads per lane in flight, the last round
-                        // predicated (a row's remainder is not a latency chain)
-                        for (int64_t v = l; v < nb4; v += 128) {
-                            float4 av[8];
 #pragma unroll
-                            for (int u = 0; u < 8; ++u)
-                                av[u] = v + 16 * u < nb4 ? row4[v + 16 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) {
-                                if (v + 16 * u < nb4) {
-                                    const float *xq = xs + head + 4 * (v + 16 * u);
-                                    ac[u & 3] += av[u].x * xq[0] + av[u].y * xq[1] + av[u].z * xq[2] + av[u].w * xq[3];
-                                }
-                            }
-                        }
-                        const int64_t t0 = head + 4 * nb4;
-                        if (t0 + l < c) ac[2] += row[t0 + l] * xs[t0 + l];
-                    } else {
-                        int64_t j = l;
-                        for (; j + 48 < c; j += 64) {
-                            float av[4], xv[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                av[u] = row[j + 16 * u];
-                                xv[u] = x[j + 16 * u];
-                            }
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) ac[u] += av[u] * xv[u];
-                        }
-                        for (; j < c; j += 16) ac[0] += row[j] * x[j];
-                    }
+            for (int u = 0; u < 4; ++u) {
+                x[u] = y[u] = f4u{0.f, 0.f, 0.f, 0.f};
+                if (threadIdx.x + u * NT < (unsigned)(nv - c)) {
+                    x[u] = ld4<false>(ac4, 4 * (threadIdx.x + u * NT));
+                    y[u] = ld4<false>(bc4, 4 * (threadIdx.x + u * NT));
                 }
-                const float acc = row16_sum((ac[0] + ac[1]) + (ac[2] + ac[3]));
-                if (l == 0 && r < tl.end) out[tk.out_off + r] = acc;
             }
         }
-    MX_TILE_LOOP_END
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ac[u] += dot4(x[u], y[u]);
+    }
+    if (threadIdx.x < (unsigned)(n & 3)) {
+        ac[1] += a[4 * nv + threadIdx.x] * b[4 * nv + threadIdx.x];
+    }
+    return (ac[0] + ac[1]) + (ac[2] + ac[3]);
 }
 
-// Column group j of a matvec tile's adjoint, V = float4 (4 columns, rows
-// 16-byte aligned) or float (1 column): gA rows r = r0, r0 + step, ... below
-// r1 get g[r] x, and the function returns the sum over those rows of
-// g[r] A[r][cols of j] in row order, U rows per round in flight.
-template <class V> struct Lanes;
-template <> struct Lanes<float> {
-    static __device__ __forceinline__ float scale(float v, float s) { return v * s; }
-    static __device__ __forceinline__ void fma(float &acc, float a, float s) { acc += a * s; }
-};
-template <> struct Lanes<float4> {
-    static __device__ __forceinline__ float4 scale(float4 v, float s) { return make_float4(v.x * s, v.y * s, v.z * s, v.w * s); }
-    static __device__ __forceinline__ void fma(float4 &acc, float4 a, float s) {
-        acc.x += a.x * s;
-        acc.y += a.y * s;
-        acc.z += a.z * s;
-        acc.w += a.w * s;
+// The rows of a matvec tile of c <= kXLds columns: 16 lanes per row, R rows
+// per group of lanes and 8 / R vectors per row and lane in flight (R: as many
+// rows as eight vectors per lane cover).  x in LDS, with zeros past its end.
+template <int R>
+__device__ __forceinline__ void matvec_rows(const float *__restrict__ A, const float *x, float *__restrict__ out,
+                                            unsigned c, int64_t n) {
+    constexpr int K = 8 / R, G = NT / 16;
+    const unsigned grp = threadIdx.x >> 4, l = threadIdx.x & 15, nv = c >> 2;
+    const unsigned row = 4u * grp * c;  // byte offset of this group's first row
+    for (int64_t r0 = 0; r0 < n; r0 += G * R) {
+        const unsigned rows = (unsigned)(n - r0 < G * R ? n - r0 : G * R);
+        const buf a = make_buf(A + r0 * c, 4u * rows * c);
+        float ac[R][2];
+#pragma unroll
+        for (int q = 0; q < R; ++q) ac[q][0] = ac[q][1] = 0.f;
+        for (unsigned v = l; v < nv; v += 16 * K) {
+            f4u av[R][K];
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                const unsigned at = v + 16 * u < nv ? row + 16 * (v + 16 * u) : kOutside;
+#pragma unroll
+                for (int q = 0; q < R; ++q) av[q][u] = bld4<false>(a, at + 4u * q * G * c);
+            }
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                const float4 xv = *reinterpret_cast<const float4 *>(x + 4 * (v + 16 * u));
+#pragma unroll
+                for (int q = 0; q < R; ++q) ac[q][u & 1] += dot4(av[q][u], f4u{xv.x, xv.y, xv.z, xv.w});
+            }
+        }
+        if (4 * nv + l < c) {
+            const float xv = x[4 * nv + l];
+#pragma unroll
+            for (int q = 0; q < R; ++q) ac[q][1] += bld1(a, row + 4 * (4 * nv + l) + 4u * q * G * c) * xv;
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const float acc = row16_sum(ac[q][0] + ac[q][1]);
+            if (l == 0 && grp + q * G < rows) out[r0 + grp + q * G] = acc;
+        }
     }
-};
+}
 
-template <class V, int U>
-__device__ __forceinline__ V matvec_adj_cols(const V *__restrict__ a, const V *__restrict__ x,
-                                             const float *__restrict__ g, V *__restrict__ ga, int64_t cv,
-                                             int64_t j, int64_t r0, int64_t r1, int step) {
-    using Ln = Lanes<V>;
-    const V xj = x[j];
-    V acc;
-    __builtin_memset(&acc, 0, sizeof acc);
-    int64_t r = r0;
-    for (; r + (U - 1) * step < r1; r += U * step) {
-        V av[U];
+// A block per tile, dispatched by the hardware in tile order.  Bound by HBM: of
+// 2048 uneven expressions (1.29 GB) 222 us, 5.8 TB/s.  Persistent blocks that
+// took tiles by ticket waited for a round trip to memory before each tile's
+// first load, 260 us; 512 expressions of 49 MB 31 us, now 14.6 us.
+__global__ void __launch_bounds__(NT, 8) k_batch_fwd(const TileDev *__restrict__ tiles, int64_t ntiles,
+                                                  const float *__restrict__ A, const float *__restrict__ B,
+                                                  float *__restrict__ out, float *__restrict__ part) {
+    __shared__ float red[NT / kWave];
+    __shared__ __attribute__((aligned(16))) float xs[kXLds + 512];
+    using R = Red<MX_ADD, float>;
+    const int64_t t = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (t >= ntiles) return;
+    const TileDev tk = tiles[t];
+    const float *a = A + tk.a_off, *b = B + tk.b_off;
+    float *o = out + tk.out_off;
+    if (tk.kind == kDot) {
+        const float acc = block_reduce<R, NT>(block_dot(a, b, tk.count), red);
+        if (threadIdx.x == 0) *(tk.part >= 0 ? part + tk.part : o) = acc;
+    } else if (tk.cols <= kXLds) {
+        const unsigned c = (unsigned)tk.cols;
+        for (unsigned q = threadIdx.x; q < c + 512; q += NT) xs[q] = q < c ? b[q] : 0.f;
+        __syncthreads();
+        if (c > 256) matvec_rows<1>(a, xs, o, c, tk.count);
+        else if (c > 128) matvec_rows<2>(a, xs, o, c, tk.count);
+        else if (c > 64) matvec_rows<4>(a, xs, o, c, tk.count);
+        else matvec_rows<8>(a, xs, o, c, tk.count);
+    } else {
+        for (int64_t r = 0; r < tk.count; ++r) {  // a long row is a dot product
+            const float acc = block_reduce<R, NT>(block_dot(a + r * tk.cols, b, tk.cols), red);
+            if (threadIdx.x == 0) o[r] = acc;
+            __syncthreads();
+        }
+    }
+}
+
+// One matvec tile's backward: gA rows get g[r] x, and dst (the tile's partial
+// column sums, or gB) the sums over its rows of g[r] A[r].  A thread takes four
+// columns and, when there are fewer groups of four than threads, one of P
+// phases of the rows (rows ph, ph + P, ...), whose partials are added in phase
+// order through LDS.  The tile has no more rows than the block takes at once
+// (adj_round), U to a thread.  The last group of a length that is not a
+// multiple of four overlaps the one before it and leaves its first `skip`
+// columns to that, so rows of any length take 16-byte accesses.
+//
+// Bound by HBM: 447 MB of matrices in 198 us (4.5 TB/s of matrix and gradient,
+// 4.8 with the partial sums), 190 us if all rows are multiples of four; with
+// blocks of 256 threads that walked four rounds of rows 214 us, in interleaved
+// rounds 226 us, four rows per thread in flight 199 us.
+template <bool PAST>
+__device__ __forceinline__ void matvec_adj_tile(const float *__restrict__ a, const float *__restrict__ x,
+                                                const float *__restrict__ g, float *__restrict__ ga, int64_t c,
+                                                unsigned rows, float *__restrict__ dst, float4 *red) {
+    constexpr int U = kAdjRows;
+    if (c < 4) {  // one thread per row, element by element
+        f4u s = {0.f, 0.f, 0.f, 0.f};
+        for (int64_t r = threadIdx.x; r < rows; r += NB) {
+            const float gr = g[r];
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (e < c) {
+                    s[e] += a[r * c + e] * gr;
+                    ga[r * c + e] = x[e] * gr;
+                }
+        }
+        red[threadIdx.x] = make_float4(s.x, s.y, s.z, 0.f);
+        __syncthreads();
+        if (threadIdx.x < c) {
+            float t = 0.f;
+            const float *q = reinterpret_cast<const float *>(red) + threadIdx.x;
+#pragma unroll 8
+            for (int ph = 0; ph < NB; ++ph) t += q[4 * ph];
+            dst[threadIdx.x] = t;
+        }
+        return;
+    }
+    const int64_t cv = (c + 3) >> 2;
+    const unsigned cv1 = (unsigned)(cv < NB ? cv : NB);  // groups of a pass over the columns
+    const unsigned P = __builtin_amdgcn_readfirstlane(NB / cv1), j = threadIdx.x % cv1, ph = threadIdx.x / cv1;
+    // the byte stride from a thread's row to its next; rows too long for a
+    // 32-bit offset to reach it come one to a tile
+    const unsigned step = c <= kLongRow ? 4u * P * (unsigned)c : 0x10000000u;
+    for (int64_t j0 = 0; j0 < cv; j0 += NB) {  // one pass unless P == 1
+        const int64_t col0 = 4 * j0 < c - 4 ? 4 * j0 : c - 4;
+        const int64_t want = 4 * (j0 + j);
+        const bool mine = ph < P && want < c;
+        const unsigned dc = (unsigned)((want + 4 <= c ? want : c - 4) - col0);  // this group's first column - col0
+        const int skip = (int)(want - (col0 + dc));
+        const int64_t bytes = c <= kLongRow ? 4 * (rows * c - col0) : 16 * NB;
+        const buf ab = make_buf(a + col0, bytes), ob = make_buf(ga + col0, bytes), gb = make_buf(g, 4u * rows);
+        const unsigned off = (P > 1 ? 4u * ph * (unsigned)c : 0u) + 4u * dc;
+        unsigned ld_at = mine ? off : kOutside, st_at = mine && skip == 0 ? off : kOutside, g_at = 4u * ph;
+        f4u av[U], s = {0.f, 0.f, 0.f, 0.f}, xj = s;
         float gv[U];
+        if (mine) xj = ld4<false>(x + col0, dc);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            av[u] = a[(r + u * step) * cv + j];
-            gv[u] = g[r + u * step];
+        for (int u = 0; u < U; ++u, ld_at += step, g_at += 4 * P) {
+            av[u] = bld4<PAST>(ab, ld_at);
+            gv[u] = bld1(gb, g_at);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            Ln::fma(acc, av[u], gv[u]);
-            ga[(r + u * step) * cv + j] = Ln::scale(xj, gv[u]);
+        for (int u = 0; u < U; ++u, st_at += step) {
+            s += av[u] * gv[u];
+            bst4(xj * gv[u], ob, st_at);
         }
+        if (mine && skip != 0)  // the last one to three columns of gA
+            for (unsigned r = ph; r < rows; r += P) {
+                const float gr = g[r];
+                float *o = ga + r * c + col0 + dc;
+                o[3] = xj[3] * gr;
+                if (skip < 3) o[2] = xj[2] * gr;
+                if (skip < 2) o[1] = xj[1] * gr;
+            }
+        if (P > 1) {
+            red[threadIdx.x] = make_float4(s.x, s.y, s.z, s.w);
+            __syncthreads();
+            if (ph == 0)
+#pragma unroll 8
+                for (unsigned q = 1; q < P; ++q) {
+                    const float4 v = red[q * cv1 + j];
+                    s += f4u{v.x, v.y, v.z, v.w};
+                }
+        }
+        if (mine && ph == 0)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e >= skip) dst[col0 + dc + e] = s[e];
     }
-    for (; r < r1; r += step) {
-        const float gr = g[r];
-        Ln::fma(acc, a[r * cv + j], gr);
-        ga[r * cv + j] = Ln::scale(xj, gr);
-    }
-    return acc;
 }
 
-// One matvec tile's backward with column groups of V: one thread per column
-// group; when there are fewer groups than threads the threads split the rows
-// into P phases (rows ph, ph + P, ...) and the phase partials are added in
-// phase order through LDS.  dst: the tile's partial column sums or gB.
-template <class V, int U>
-__device__ __forceinline__ void matvec_adj_tile(const V *__restrict__ a, const V *__restrict__ x,
-                                                const float *__restrict__ g, V *__restrict__ ga, int64_t cv,
-                                                int64_t rb, int64_t re, float *__restrict__ dst, V *red) {
-    constexpr int W = sizeof(V) / sizeof(float);
-    const int P = cv >= NT ? 1 : (int)(NT / cv);
-    if (P == 1) {
-        for (int64_t j = threadIdx.x; j < cv; j += NT) {
-            const V s = matvec_adj_cols<V, U>(a, x, g, ga, cv, j, rb, re, 1);
-            __builtin_memcpy(dst + W * j, &s, sizeof s);
+// Bound by HBM.  A dot's tile is one round of the block's accesses, so that the
+// blocks which run together walk the four arrays as one front: 843 MB of
+// operands and as much of gradients took 345 us with tiles of 64 KB walked in
+// four rounds (their starts a power of two apart), now 310 us.  Loads past the
+// caches in passes larger than the memory-side cache leave what the forward
+// pass put there: forward and backward of 1.29 GB 704 us, 731 us without.
+template <bool PAST>
+__global__ void __launch_bounds__(NB) k_batch_bwd(const TileDev *__restrict__ tiles, int64_t ntiles,
+                                                  const float *__restrict__ A, const float *__restrict__ B,
+                                                  const float *__restrict__ gout, float *__restrict__ gA,
+                                                  float *__restrict__ gB, float *__restrict__ part) {
+    __shared__ float4 red[NB];
+    const int64_t t = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (t >= ntiles) return;
+    const TileDev tk = tiles[t];
+    if (tk.kind == kDot) {
+        const float g = gout[tk.out_off];
+        const float *a = A + tk.a_off, *b = B + tk.b_off;
+        float *ga = gA + tk.a_off, *gb = gB + tk.b_off;
+        const int64_t n = tk.count, nv = n >> 2;
+        for (int64_t c = 0; c < nv; c += kBwdVec * NB) {
+            const int64_t at = 4 * c;
+            f4u x[kBwdVec], y[kBwdVec];
+            if (c + kBwdVec * NB <= nv) {
+#pragma unroll
+                for (int u = 0; u < kBwdVec; ++u) {
+                    x[u] = ld4<PAST>(a + at, 4 * (threadIdx.x + u * NB));
+                    y[u] = ld4<PAST>(b + at, 4 * (threadIdx.x + u * NB));
+                }
+#pragma unroll
+                for (int u = 0; u < kBwdVec; ++u) {
+                    st4(y[u] * g, ga + at, 4 * (threadIdx.x + u * NB));
+                    st4(x[u] * g, gb + at, 4 * (threadIdx.x + u * NB));
+                }
+            } else {
+                const unsigned left = (unsigned)(nv - c);
+#pragma unroll
+                for (int u = 0; u < kBwdVec; ++u)
+                    if (threadIdx.x + u * NB < left) {
+                        x[u] = ld4<PAST>(a + at, 4 * (threadIdx.x + u * NB));
+                        y[u] = ld4<PAST>(b + at, 4 * (threadIdx.x + u * NB));
+                    }
+#pragma unroll
+                for (int u = 0; u < kBwdVec; ++u)
+                    if (threadIdx.x + u * NB < left) {
+                        st4(y[u] * g, ga + at, 4 * (threadIdx.x + u * NB));
+                        st4(x[u] * g, gb + at, 4 * (threadIdx.x + u * NB));
+                    }
+            }
+        }
+        const int64_t e = 4 * nv + threadIdx.x;
+        if (e < n) {
+            ga[e] = g * b[e];
+            gb[e] = g * a[e];
         }
     } else {
-        const int j = (int)(threadIdx.x % cv), ph = (int)(threadIdx.x / cv);
-        V s;
-        __builtin_memset(&s, 0, sizeof s);
-        if (ph < P) s = matvec_adj_cols<V, U>(a, x, g, ga, cv, j, rb + ph, re, P);
-        red[threadIdx.x] = s;
-        __syncthreads();
-        if (threadIdx.x < cv) {
-            float t[W];
-            __builtin_memcpy(t, &red[threadIdx.x], sizeof t);
-            for (int q = 1; q < P; ++q) {
-                float u[W];
-                __builtin_memcpy(u, &red[q * cv + threadIdx.x], sizeof u);
-#pragma unroll
-                for (int e = 0; e < W; ++e) t[e] += u[e];
-            }
-            __builtin_memcpy(dst + W * threadIdx.x, t, sizeof t);
-        }
+        float *dst = tk.part >= 0 ? part + tk.part : gB + tk.b_off;
+        matvec_adj_tile<PAST>(A + tk.a_off, B + tk.b_off, gout + tk.out_off, gA + tk.a_off, tk.cols, tk.count,
+                              dst, red);
     }
-}
-
-__global__ void __launch_bounds__(NT) k_batch_bwd(const TaskDev *__restrict__ tasks, const TileDev *__restrict__ tiles,
-                                                  int64_t ntiles, const float *__restrict__ A,
-                                                  const float *__restrict__ B, const float *__restrict__ gout,
-                                                  float *__restrict__ gA, float *__restrict__ gB,
-                                                  float *__restrict__ part, unsigned *ticket, int vec) {
-    __shared__ float4 red4[NT];
-    __shared__ float red1[NT];
-    MX_TILE_LOOP_BEGIN
-        if (tk.kind == kDot) {
-            const float g = gout[tk.out_off];
-            const float *a = A + tk.a_off, *b = B + tk.b_off;
-            float *ga = gA + tk.a_off, *gb = gB + tk.b_off;
-            int64_t e = tl.begin + threadIdx.x;
-            if (vec && ((tk.a_off | tk.b_off | tl.begin) & 3) == 0) {
-                const float4 *a4 = reinterpret_cast<const float4 *>(a), *b4 = reinterpret_cast<const float4 *>(b);
-                float4 *ga4 = reinterpret_cast<float4 *>(ga), *gb4 = reinterpret_cast<float4 *>(gb);
-                const int64_t ve = tl.end >> 2;
-                int64_t i = (tl.begin >> 2) + threadIdx.x;
-                for (; i + 3 * NT < ve; i += 4 * NT) {
-                    float4 x[4], y[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        x[u] = a4[i + u * NT];
-                        y[u] = b4[i + u * NT];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        ga4[i + u * NT] = make_float4(g * y[u].x, g * y[u].y, g * y[u].z, g * y[u].w);
-                        gb4[i + u * NT] = make_float4(g * x[u].x, g * x[u].y, g * x[u].z, g * x[u].w);
-                    }
-                }
-                for (; i < ve; i += NT) {
-                    const float4 x = a4[i], y = b4[i];
-                    ga4[i] = make_float4(g * y.x, g * y.y, g * y.z, g * y.w);
-                    gb4[i] = make_float4(g * x.x, g * x.y, g * x.z, g * x.w);
-                }
-                e = 4 * ve + threadIdx.x;
-            } else {
-                for (; e + 3 * NT < tl.end; e += 4 * NT) {
-                    float av[4], bv[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        av[u] = a[e + u * NT];
-                        bv[u] = b[e + u * NT];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        ga[e + u * NT] = g * bv[u];
-                        gb[e + u * NT] = g * av[u];
-                    }
-                }
-            }
-            for (; e < tl.end; e += NT) {
-                ga[e] = g * b[e];
-                gb[e] = g * a[e];
-            }
-        } else {
-            const int64_t c = tk.cols;
-            const float *x = B + tk.b_off, *g = gout + tk.out_off;
-            const float *a = A + tk.a_off;
-            float *ga = gA + tk.a_off;
-            float *dst = tl.part >= 0 ? part + tl.part : gB + tk.b_off;
-            if (vec && ((tk.a_off | tk.b_off | c) & 3) == 0)
-                matvec_adj_tile<float4, 8>(reinterpret_cast<const float4 *>(a), reinterpret_cast<const float4 *>(x),
-                                           g, reinterpret_cast<float4 *>(ga), c >> 2, tl.begin, tl.end, dst, red4);
-            else
-                matvec_adj_tile<float, 16>(a, x, g, ga, c, tl.begin, tl.end, dst, red1);
-        }
-    MX_TILE_LOOP_END
 }
 
 // sum of q = 0 .. nq-1 of p[q * stride], in q order, eight loads in flight
@@ -367,12 +383,10 @@ __device__ __forceinline__ float sum_strided(const float *__restrict__ p, int64_
     return s;
 }
 
-// Adds the tile partials of each multi-tile task in tile order; resets the ticket.
+// Adds the tile partials of each multi-tile task in tile order.
 __global__ void __launch_bounds__(NT) k_batch_combine_fwd(const TaskDev *__restrict__ tasks,
                                                           const int32_t *__restrict__ list, int64_t nlist,
-                                                          const float *__restrict__ part, float *__restrict__ out,
-                                                          unsigned *ticket) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0u;
+                                                          const float *__restrict__ part, float *__restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
     if (i >= nlist) return;
     const TaskDev tk = tasks[list[i]];
@@ -383,9 +397,7 @@ __global__ void __launch_bounds__(NT) k_batch_combine_fwd(const TaskDev *__restr
 // of its per-tile partial column sums in tile order
 __global__ void __launch_bounds__(NT) k_batch_combine_bwd(const TaskDev *__restrict__ tasks,
                                                           const int32_t *__restrict__ list, int64_t nlist,
-                                                          const float *__restrict__ part, float *__restrict__ gB,
-                                                          unsigned *ticket) {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *ticket = 0u;
+                                                          const float *__restrict__ part, float *__restrict__ gB) {
     if ((int64_t)blockIdx.x >= nlist) return;
     const TaskDev tk = tasks[list[blockIdx.x]];
     const int64_t c = tk.cols;
@@ -468,6 +480,16 @@ void free_device(mx_batch_plan *p) {
     p->d_fwd_list = p->d_bwd_list = nullptr;
 }
 
+// rows that a block takes at once in a matvec's backward
+int64_t adj_round(int64_t c) {
+    if (c < 4) return INT64_MAX;  // walked by rows
+    if (c > kLongRow) return 1;
+    return kAdjRows * (NB / std::min<int64_t>(ceil_div(c, 4), NB));
+}
+// rows of a matvec's tile backward (at most what a block takes at once) and forward
+int64_t fwd_rows(int64_t cols, int64_t tile) { return std::max<int64_t>(1, 2 * tile / std::max<int64_t>(cols, 1)); }
+int64_t bwd_rows(int64_t cols, int64_t tile) { return std::min(adj_round(cols), fwd_rows(cols, tile)); }
+
 // Partial-storage requirement at the smallest tile size (covers every candidate).
 void partial_floats(const std::vector<int64_t> &tb, int64_t ntasks, int64_t tile, int64_t *fwd, int64_t *bwd) {
     *fwd = 0;
@@ -478,15 +500,34 @@ void partial_floats(const std::vector<int64_t> &tb, int64_t ntasks, int64_t tile
             const int64_t nt = ceil_div(cols > 0 ? cols : 1, tile);
             if (nt > 1) *fwd += nt;
         } else {
-            const int64_t rpt = std::max<int64_t>(1, 2 * tile / std::max<int64_t>(cols, 1));
-            const int64_t nt = ceil_div(rows > 0 ? rows : 1, rpt);
+            const int64_t nt = ceil_div(rows > 0 ? rows : 1, bwd_rows(cols, tile));
             if (nt > 1) *bwd += nt * cols;
         }
     }
 }
 
-TileDev make_tile(int64_t t, const TaskDev &tk, int64_t begin, int64_t end, int64_t part) {
-    return TileDev{(int32_t)t, tk.kind, begin, end, part, tk.cols, tk.a_off, tk.b_off, tk.out_off};
+// elements (dot) or rows (matvec) [begin, end) of a task
+TileDev make_tile(const TaskDev &tk, int64_t begin, int64_t end, int64_t part) {
+    const bool dot = tk.kind == kDot;
+    return TileDev{(uint32_t)tk.kind, (uint32_t)(end - begin), part, tk.cols, tk.a_off + begin * (dot ? 1 : tk.cols),
+                   tk.b_off + (dot ? begin : 0), tk.out_off + (dot ? 0 : begin)};
+}
+
+// Longest first by operand bytes in classes of an eighth of an octave, in task
+// order within a class (so plans are reproducible): one counting pass.
+void order_tiles(std::vector<TileDev> &v) {
+    auto cls = [](const TileDev &t) {
+        const uint64_t c = t.kind == kDot ? 2 * (uint64_t)t.count : t.count * (uint64_t)t.cols;
+        if (c < 8) return 511 - (int)c;
+        const int e = 63 - __builtin_clzll(c);
+        return 511 - (8 * (e - 2) + (int)((c >> (e - 3)) & 7));
+    };
+    std::vector<size_t> at(513, 0);
+    for (const TileDev &t : v) ++at[(size_t)cls(t) + 1];
+    for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+    std::vector<TileDev> o(v.size());
+    for (const TileDev &t : v) o[at[(size_t)cls(t)]++] = t;
+    v.swap(o);
 }
 
 mx_status build_tiles(mx_batch_plan *p) {
@@ -510,44 +551,41 @@ mx_status build_tiles(mx_batch_plan *p) {
             tk.fwd_ntiles = nt;
             tk.fwd_part = nt > 1 ? fpart : -1;
             for (int64_t q = 0; q < nt; ++q)
-                fwd.push_back(make_tile(t, tk, q * T, std::min(n, (q + 1) * T), nt > 1 ? fpart + q : -1));
+                fwd.push_back(make_tile(tk, q * T, std::min(n, (q + 1) * T), nt > 1 ? fpart + q : -1));
             if (nt > 1) {
                 fwd_list.push_back((int32_t)t);
                 fpart += nt;
             }
-            for (int64_t q = 0; q < nt; ++q)
-                bwd.push_back(make_tile(t, tk, q * T, std::min(n, (q + 1) * T), -1));
+            // nothing to add up backward: a chunk of the block's loads each
+            for (int64_t e = 0; e == 0 || e < n; e += kDotChunk)
+                bwd.push_back(make_tile(tk, e, std::min(n, e + kDotChunk), -1));
             tk.bwd_ntiles = nt;
             tk.bwd_part = -1;
         } else {
-            const int64_t c = std::max<int64_t>(tk.cols, 1);
             // a matvec streams one operand (4 bytes per element) where a dot
             // streams two: twice the elements give tiles of equal bytes
-            const int64_t rpt = std::max<int64_t>(1, 2 * T / c);
+            const int64_t rpt = fwd_rows(tk.cols, T);
             const int64_t nt = std::max<int64_t>(1, ceil_div(tk.rows, rpt));
             tk.fwd_ntiles = nt;
             tk.fwd_part = -1;
-            tk.bwd_ntiles = nt;
-            tk.bwd_part = nt > 1 ? bpart : -1;
-            for (int64_t q = 0; q < nt; ++q) {
-                const int64_t b = q * rpt, e = std::min(tk.rows, (q + 1) * rpt);
-                fwd.push_back(make_tile(t, tk, b, e, -1));
-                bwd.push_back(make_tile(t, tk, b, e, nt > 1 ? bpart + q * tk.cols : -1));
-            }
-            if (nt > 1) {
+            for (int64_t q = 0; q < nt; ++q)
+                fwd.push_back(make_tile(tk, q * rpt, std::min(tk.rows, (q + 1) * rpt), -1));
+            // backward a tile is what a block takes at once
+            const int64_t rows = bwd_rows(tk.cols, T);
+            const int64_t nb = std::max<int64_t>(1, ceil_div(tk.rows, rows));
+            tk.bwd_ntiles = nb;
+            tk.bwd_part = nb > 1 ? bpart : -1;
+            for (int64_t q = 0; q < nb; ++q)
+                bwd.push_back(make_tile(tk, q * rows, std::min(tk.rows, (q + 1) * rows), nb > 1 ? bpart + q * tk.cols : -1));
+            if (nb > 1) {
                 bwd_list.push_back((int32_t)t);
-                bpart += nt * tk.cols;
+                bpart += nb * tk.cols;
                 max_cols = std::max(max_cols, tk.cols);
             }
         }
     }
-    // longest first (stable: ties keep task order, so plans are reproducible)
-    auto cost = [&](const TileDev &x) {
-        const TaskDev &tk = tasks[(size_t)x.task];
-        return tk.kind == kDot ? (x.end - x.begin) : (x.end - x.begin) * tk.cols;
-    };
-    std::stable_sort(fwd.begin(), fwd.end(), [&](const TileDev &x, const TileDev &y) { return cost(x) > cost(y); });
-    std::stable_sort(bwd.begin(), bwd.end(), [&](const TileDev &x, const TileDev &y) { return cost(x) > cost(y); });
+    order_tiles(fwd);
+    order_tiles(bwd);
     MX_REQUIRE((int64_t)fwd.size() < (1LL << 31) && (int64_t)bwd.size() < (1LL << 31), MX_ERR_SHAPE,
                "mx_batch_plan: too many tiles");
     free_device(p);
@@ -593,34 +631,46 @@ float *bwd_part_ptr(const mx_batch_plan *p, void *ws) {
     return (float *)((char *)ws + kCounterBytes + align256((size_t)f * 4));
 }
 
-int grid_of(const mx_batch_plan *p, int64_t ntiles) {
-    int64_t g = (int64_t)p->num_cus * p->cfg.blocks_per_cu;
-    if (g > ntiles) g = ntiles;
-    return (int)std::max<int64_t>(g, 1);
+// a block per tile, in rows of at most 2^20 blocks
+dim3 grid_of(int64_t ntiles) {
+    constexpr int64_t kRow = 1 << 20;
+    return ntiles <= kRow ? dim3((unsigned)std::max<int64_t>(ntiles, 1)) : dim3((unsigned)kRow, (unsigned)ceil_div(ntiles, kRow));
+}
+// LDS that a launch asks for so that no more than blocks_per_cu blocks are
+// resident on a CU (160 KB; the kernels' own arrays are `own`).  64 KB is the
+// most a launch can have: one block per CU is not reached, two are.
+unsigned lds_of(const mx_batch_plan *p, unsigned own) {
+    const unsigned b = (unsigned)p->cfg.blocks_per_cu;
+    const unsigned per = b >= 8 ? 0u : std::min(163840u / (b + 1) + 1024u, 65536u);
+    return per > own ? per - own : 0u;
 }
 
 mx_status fwd_impl(const mx_batch_plan *p, const float *A, const float *B, float *out, void *ws, hipStream_t s) {
-    unsigned *ticket = (unsigned *)ws;
     float *part = fwd_part_ptr(p, ws);
-    const int vec = aligned16(A) && aligned16(B);
-    hipLaunchKernelGGL(k_batch_fwd, dim3(grid_of(p, p->n_fwd)), dim3(NT), 0, s, p->d_tasks, p->d_fwd, p->n_fwd, A, B,
-                       out, part, ticket, vec);
-    hipLaunchKernelGGL(k_batch_combine_fwd, dim3((unsigned)std::max<int64_t>(1, ceil_div(p->n_fwd_list, NT))),
-                       dim3(NT), 0, s, p->d_tasks, p->d_fwd_list, p->n_fwd_list, part, out, ticket);
+    hipLaunchKernelGGL(k_batch_fwd, grid_of(p->n_fwd), dim3(NT), lds_of(p, 4 * (kXLds + 512 + 16)), s, p->d_fwd, p->n_fwd, A, B, out, part);
+    if (p->n_fwd_list > 0)
+        hipLaunchKernelGGL(k_batch_combine_fwd, dim3((unsigned)ceil_div(p->n_fwd_list, NT)), dim3(NT), 0, s,
+                           p->d_tasks, p->d_fwd_list, p->n_fwd_list, part, out);
     return last_launch("mx_batch_forward");
 }
 
+// Loads past the caches for a pass larger than the memory-side cache, where
+// they would push out what the forward pass left there; the inputs of a smaller
+// one stay for the next reader.
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+
 mx_status bwd_impl(const mx_batch_plan *p, const float *A, const float *B, const float *gout, float *gA, float *gB,
                    void *ws, hipStream_t s) {
-    unsigned *ticket = (unsigned *)ws + 1;
     float *part = bwd_part_ptr(p, ws);
-    const int vec = aligned16(A) && aligned16(B) && aligned16(gA) && aligned16(gB);
-    hipLaunchKernelGGL(k_batch_bwd, dim3(grid_of(p, p->n_bwd)), dim3(NT), 0, s, p->d_tasks, p->d_bwd, p->n_bwd, A, B,
-                       gout, gA, gB, part, ticket, vec);
-    const dim3 cgrid((unsigned)std::max<int64_t>(1, p->n_bwd_list),
-                     (unsigned)std::min<int64_t>(1024, ceil_div(p->bwd_list_max_cols, NT)));
-    hipLaunchKernelGGL(k_batch_combine_bwd, cgrid, dim3(NT), 0, s,
-                       p->d_tasks, p->d_bwd_list, p->n_bwd_list, part, gB, ticket);
+    const bool past = (p->a_len + p->b_len) * 2 * (int64_t)sizeof(float) > kCacheBytes;
+    hipLaunchKernelGGL(past ? k_batch_bwd<true> : k_batch_bwd<false>, grid_of(p->n_bwd), dim3(NB),
+                       lds_of(p, 16 * NB), s, p->d_bwd, p->n_bwd, A, B, gout, gA, gB, part);
+    if (p->n_bwd_list > 0) {
+        const dim3 cgrid((unsigned)p->n_bwd_list,
+                         (unsigned)std::min<int64_t>(1024, ceil_div(p->bwd_list_max_cols, NT)));
+        hipLaunchKernelGGL(k_batch_combine_bwd, cgrid, dim3(NT), 0, s, p->d_tasks, p->d_bwd_list, p->n_bwd_list, part,
+                           gB);
+    }
     return last_launch("mx_batch_backward");
 }
 
