@@ -654,11 +654,6 @@ mx_status fwd_impl(const mx_batch_plan *p, const float *A, const float *B, float
     return last_launch("mx_batch_forward");
 }
 
-// Loads past the caches for a pass larger than the memory-side cache, where
-// they would push out what the forward pass left there; the inputs of a smaller
-// one stay for the next reader.
-constexpr int64_t kCacheBytes = (int64_t)256 << 20;
-
 mx_status bwd_impl(const mx_batch_plan *p, const float *A, const float *B, const float *gout, float *gA, float *gB,
                    void *ws, hipStream_t s) {
     float *part = bwd_part_ptr(p, ws);

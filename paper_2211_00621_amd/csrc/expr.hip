@@ -87,11 +87,6 @@ constexpr int kGroupsPerIt = 4;  // vector groups per thread and loop iteration
 constexpr int kMaxRedBlocks = 2048;  // eight per CU resident at once: one round, longer-lived threads
 constexpr int kOneBlockChunks = 4;   // chunks folded by a single block, whose call is one launch
 constexpr int kMaxPassBlocks = 65536;
-// The memory-side cache.  A pass over less keeps its inputs there for the next
-// reader (64 MB of inputs, then read again: 32.6 us the two, 36.9 us with loads
-// past it); of a larger one little would be left (1 GB: 542 us and 521 us).
-constexpr int64_t kCacheBytes = (int64_t)256 << 20;
-
 // 16-byte groups per array and thread that an element-wise pass holds in
 // flight: four were the fastest with two inputs, and with four inputs, a seed
 // and their results two are what fits the registers of eight waves per SIMD

@@ -1,12 +1,21 @@
 // reduce op ne s and the fused reduce op ne (map2 f a b) (Appendix A).
 //
-// Two launches.  Partial pass: every thread folds a grid-strided set of 16-byte
-// vectors (U per operand in flight) into one accumulator per vector lane, the
-// block combines its values with the wave64 DPP tree and writes one partial.
-// Finish pass (one block): folds the partials in block order and applies ne.
-// The kernel boundary orders the two passes, so no block pays for a
-// device-wide fence.  The bracketing depends only on n and the grid, so
-// results are bit-identical from run to run.
+// Two launches.  Partial pass: a block folds contiguous chunks of U x 256
+// 16-byte vectors per operand, all of a chunk in flight, into one accumulator
+// per vector lane, combines its values with the wave64 DPP tree and writes one
+// partial.  Finish pass (one block): folds the partials in block order and
+// applies ne.  The kernel boundary orders the two passes, so no block pays for a
+// device-wide fence.  An input of a few chunks is one block's work, and one
+// launch.  The bracketing depends only on n and the device, so results are
+// bit-identical from run to run, whatever the alignment.
+//
+// Bound by HBM; plain loads, which leave the last part of the inputs in the
+// memory-side cache for a reverse pass.  The dot of 2^26 pairs of float32
+// (537 MB) 97.5 us -> 92.8 us with the finish launch (5.8 TB/s), of 2^24
+// 26.7 us -> 23.5 us, against grid-wide strides; the dot and its adjoint at 2^26
+// 338 us -> 242 us.
+#include <algorithm>
+
 #include "mx_internal.h"
 
 namespace mx {
@@ -15,8 +24,10 @@ namespace {
 constexpr int NT = 256;
 constexpr int U = 4;
 constexpr int kMaxBlocks = 4096;
-
-inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+// Chunks that one block folds alone, in one launch: 2^14 pairs 3.0 us against
+// 3.6 us by two launches (whose host side is 3 us more); at 2^15 the two are
+// 3.6 us and one block is behind.
+constexpr int64_t kOneBlockChunks = 4;
 
 // F < 0: plain reduce of a; otherwise element = Bin<F>(a[i], b[i]).
 template <mx_dtype D, int OP, int F> struct Elem {
@@ -28,13 +39,14 @@ template <mx_dtype D, int OP, int F> struct Elem {
     }
 };
 
+// direct != 0: the only block; partials is the output
 template <mx_dtype D, int OP, int F>
 __global__ void __launch_bounds__(NT) k_reduce(const typename DT<D>::In *__restrict__ a,
                                                const typename DT<D>::In *__restrict__ b, int64_t n,
-                                               typename DT<D>::Acc *__restrict__ partials, int vec) {
+                                               typename DT<D>::Acc ne, int direct,
+                                               typename DT<D>::Acc *__restrict__ partials) {
     using In = typename DT<D>::In;
     using Acc = typename DT<D>::Acc;
-    using Vec = typename DT<D>::Vec;
     using R = Red<OP, Acc>;
     using E = Elem<D, OP, F>;
     constexpr int V = DT<D>::kVec;
@@ -44,47 +56,40 @@ __global__ void __launch_bounds__(NT) k_reduce(const typename DT<D>::In *__restr
     Acc acc[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) acc[j] = R::id();
-    const int64_t gtid = (int64_t)blockIdx.x * NT + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * NT;
-    if (vec) {
-        const int64_t nv = n / V;
-        const Vec *av = reinterpret_cast<const Vec *>(a);
-        const Vec *bv = reinterpret_cast<const Vec *>(b);
-        int64_t i = gtid;
-        for (; i + (U - 1) * stride < nv; i += U * stride) {
-            Vec va[U], vb[U];
+    auto fold = [&](const uvec<In> &va, const uvec<In> &vb) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc[j] = R::ap(acc[j], E::at(va[j], TWO ? vb[j] : In(0)));
+    };
+    const int64_t nv = n / V;
+    for (int64_t c = (int64_t)blockIdx.x * (U * NT); c < nv; c += (int64_t)gridDim.x * (U * NT)) {
+        const int64_t i = c + threadIdx.x;
+        if (c + U * NT <= nv) {
+            uvec<In> va[U], vb[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                va[u] = av[i + u * stride];
-                if constexpr (TWO) vb[u] = bv[i + u * stride];
+                va[u] = load16<false>(a + V * (i + u * NT));
+                if constexpr (TWO) vb[u] = load16<false>(b + V * (i + u * NT));
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int j = 0; j < V; ++j)
-                    acc[j] = R::ap(acc[j], E::at(vget<Vec, In>(va[u], j), TWO ? vget<Vec, In>(vb[u], j) : In(0)));
+            for (int u = 0; u < U; ++u) fold(va[u], vb[u]);
+        } else {
+            for (int64_t j = i; j < nv; j += NT) {
+                const uvec<In> va = load16<false>(a + V * j);
+                fold(va, TWO ? load16<false>(b + V * j) : va);
+            }
         }
-        for (; i < nv; i += stride) {
-            Vec va = av[i];
-            Vec vb;
-            if constexpr (TWO) vb = bv[i];
-#pragma unroll
-            for (int j = 0; j < V; ++j)
-                acc[j] = R::ap(acc[j], E::at(vget<Vec, In>(va, j), TWO ? vget<Vec, In>(vb, j) : In(0)));
-        }
-        if (gtid < n - nv * V) acc[0] = R::ap(acc[0], E::at(a[nv * V + gtid], TWO ? b[nv * V + gtid] : In(0)));
-    } else {
-        for (int64_t i = gtid; i < n; i += stride) acc[0] = R::ap(acc[0], E::at(a[i], TWO ? b[i] : In(0)));
     }
+    const int64_t i = nv * V + threadIdx.x;  // the last n % V elements
+    if (blockIdx.x == gridDim.x - 1 && i < n) acc[0] = R::ap(acc[0], E::at(a[i], TWO ? b[i] : In(0)));
     Acc t = acc[0];
 #pragma unroll
     for (int j = 1; j < V; ++j) t = R::ap(t, acc[j]);
     t = block_reduce<R, NT>(t, smem);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+    if (threadIdx.x == 0) partials[blockIdx.x] = direct ? R::ap(ne, t) : t;
 }
 
 // one block: out = ne (op) (partial_0 (op) ... (op) partial_{nb-1}), strided
-// per thread then the DPP tree
+// per thread (eight loads in flight), then the DPP tree
 template <mx_dtype D, int OP>
 __global__ void __launch_bounds__(NT) k_reduce_finish(const typename DT<D>::Acc *__restrict__ partials, int nb,
                                                       typename DT<D>::Acc ne, typename DT<D>::Acc *out) {
@@ -92,7 +97,13 @@ __global__ void __launch_bounds__(NT) k_reduce_finish(const typename DT<D>::Acc 
     using R = Red<OP, Acc>;
     __shared__ Acc smem[NT / kWave];
     Acc v = R::id();
-    for (int i = threadIdx.x; i < nb; i += NT) v = R::ap(v, partials[i]);
+    for (int i = threadIdx.x; i < nb; i += 8 * NT) {
+        Acc p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = i + u * NT < nb ? partials[i + u * NT] : R::id();
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v = R::ap(v, p[u]);
+    }
     v = block_reduce<R, NT>(v, smem);
     if (threadIdx.x == 0) out[0] = R::ap(ne, v);
 }
@@ -104,15 +115,14 @@ mx_status launch(const void *a, const void *b, int64_t n, const void *ne_host, v
     using Acc = typename DT<D>::Acc;
     Acc ne;
     __builtin_memcpy(&ne, ne_host, sizeof(Acc));
-    const int vec = aligned16(a) && (F < 0 || aligned16(b));
-    const int64_t items = vec ? n / DT<D>::kVec : n;
-    int64_t grid = ceil_div(items > 0 ? items : 1, (int64_t)NT * U);
-    int64_t cap = (int64_t)dev->num_cus * 8;
-    if (cap > kMaxBlocks) cap = kMaxBlocks;
-    if (grid > cap) grid = cap;
-    Acc *partials = (Acc *)((char *)ws + kCounterBytes);
+    int64_t grid = ceil_div(n > 0 ? n : 1, (int64_t)NT * U * DT<D>::kVec);
+    const int64_t cap = std::min<int64_t>((int64_t)dev->num_cus * 8, kMaxBlocks);
+    grid = grid <= kOneBlockChunks ? 1 : std::min(grid, cap);
+    const int direct = grid == 1;
+    Acc *partials = direct ? (Acc *)out : (Acc *)((char *)ws + kCounterBytes);
     hipLaunchKernelGGL((k_reduce<D, OP, F>), dim3((unsigned)grid), dim3(NT), 0, s, (const In *)a,
-                       (const In *)b, n, partials, vec);
+                       (const In *)b, n, ne, direct, partials);
+    if (direct) return last_launch("reduce");
     if (mx_status st = last_launch("reduce")) return st;
     hipLaunchKernelGGL((k_reduce_finish<D, OP>), dim3(1), dim3(NT), 0, s, (const Acc *)partials, (int)grid, ne,
                        (Acc *)out);

@@ -1,0 +1,117 @@
+"""map, map2, the dot's adjoint and the reductions at the edges of a block's chunk (one to four vectors per thread, the
+change between them at 2^16 vectors), of what a single block reduces alone, and past the memory-side cache; unaligned
+slices; nothing written outside.  References in numpy: integer and single-operation float results are exact."""
+import numpy as np
+import pytest
+import torch
+
+from parity import say
+
+import paper_2211_00621_amd as mx  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+abi = mx.abi
+TYPES = {"f32": (np.float32, np.float32), "f64": (np.float64, np.float64), "i32": (np.int32, np.int64),
+         "i64": (np.int64, np.int64)}
+
+
+def slice_of(x, shift):
+    t = torch.zeros(len(x) + shift, dtype=torch.from_numpy(x[:0]).dtype, device="cuda")
+    t[shift:] = torch.from_numpy(x)
+    return t[shift:]
+
+
+def guarded(n, dtype, shift):
+    t = torch.full((n + shift + 5,), 7, dtype=torch.from_numpy(np.zeros(0, dtype)).dtype, device="cuda")
+    return t, t[shift:shift + n]
+
+
+def whole(t, n, shift):
+    torch.cuda.synchronize()
+    h = t.cpu().numpy()
+    assert np.all(h[:shift] == 7) and np.all(h[shift + n:] == 7)
+    return h[shift:shift + n]
+
+
+def make(kind, n, seed):
+    rng = np.random.default_rng(seed)
+    t = TYPES[kind][0]
+    return (rng.uniform(-1, 1, n) if kind[0] == "f" else rng.integers(-10 ** 6, 10 ** 6, n)).astype(t)
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 255, 1023, 1025, 4096, 4099, 16384, 16387, 32771, (1 << 17) + 1, (1 << 18) + 3,
+                               (1 << 18) + 4099])
+@pytest.mark.parametrize("kind", list(TYPES))
+def test_chunk_edges(kind, n, shift):
+    say("stream chunk", kind, n, shift)
+    acc = TYPES[kind][1]
+    a, b = make(kind, n, n), make(kind, n, n + 1)
+    da, db = slice_of(a, shift), slice_of(b, shift)
+    wide_a, wide_b = a.astype(acc), b.astype(acc)
+    t, o = guarded(n, acc, shift)
+    abi.mx_map(abi.MX_U_SQ, da, None, o)
+    assert np.array_equal(whole(t, n, shift), wide_a * wide_a)
+    t, o = guarded(n, acc, shift)
+    abi.mx_map2(abi.MX_B_SUB, da, db, o)
+    assert np.array_equal(whole(t, n, shift), wide_a - wide_b)
+
+    ws = torch.zeros(abi.mx_workspace_bytes(abi.MX_WS_REDUCE, n, 0), dtype=torch.uint8, device="cuda")
+    r = torch.zeros(1, dtype=o.dtype, device="cuda")
+    ne = 3 if kind[0] == "i" else 0.25
+    for op, ref in ((abi.MX_MIN, lambda x: min(ne, x.min())), (abi.MX_MAX, lambda x: max(ne, x.max()))):
+        abi.mx_reduce(op, da, ne, r, ws)
+        assert r.cpu().numpy()[0] == acc(ref(wide_a))
+    abi.mx_reduce(abi.MX_ADD, da, ne, r, ws)
+    abi.mx_map2_reduce(abi.MX_B_MUL, abi.MX_ADD, da, db, ne, (d := torch.zeros_like(r)), ws)
+    got_sum, got_dot = r.cpu().numpy()[0], d.cpu().numpy()[0]
+    if kind[0] == "i":
+        assert got_sum == wide_a.sum() + ne and got_dot == (wide_a * wide_b).sum() + ne
+    else:
+        u = 2.0 ** -24 if kind == "f32" else 2.0 ** -53
+        a64, b64 = a.astype(np.longdouble), b.astype(np.longdouble)
+        assert abs(got_sum - (a64.sum() + ne)) <= (n + 1) * u * (np.abs(a64).sum() + ne)
+        assert abs(got_dot - ((a64 * b64).sum() + ne)) <= (n + 2) * u * (np.abs(a64 * b64).sum() + ne)
+
+    if kind == "f32":
+        g = torch.tensor([0.75], device="cuda")
+        for want_a, want_b in ((1, 1), (1, 0), (0, 1)):
+            (ta, ga), (tb, gb) = guarded(n, np.float32, shift), guarded(n, np.float32, shift)
+            abi.mx_dot_adjoint_f32(da, db, g, ga if want_a else None, gb if want_b else None)
+            if want_a:
+                assert np.array_equal(whole(ta, n, shift), np.float32(0.75) * b)
+            if want_b:
+                assert np.array_equal(whole(tb, n, shift), np.float32(0.75) * a)
+
+
+def test_in_place():
+    """map2 over its own operand and map over its input."""
+    n = (1 << 18) + 4099
+    say("stream in place", n)
+    a, b = make("f32", n, 1), make("f32", n, 2)
+    da, db = slice_of(a, 0), slice_of(b, 0)
+    abi.mx_map2(abi.MX_B_ADD, da, db, db)
+    assert np.array_equal(db.cpu().numpy(), a + b)
+    abi.mx_map(abi.MX_U_SQ, da, None, da)
+    assert np.array_equal(da.cpu().numpy(), a * a)
+
+
+@pytest.mark.parametrize("kind", ["f32", "i32"])
+def test_past_the_cache(kind):
+    """More than 256 MiB in a pass."""
+    n = (34 << 20) + 3
+    say("stream past the cache", kind, n)
+    acc = TYPES[kind][1]
+    a, b = make(kind, n, 5), make(kind, n, 6)
+    da, db = slice_of(a, 1), slice_of(b, 1)
+    t, o = guarded(n, acc, 1)
+    abi.mx_map2(abi.MX_B_MUL, da, db, o)
+    assert np.array_equal(whole(t, n, 1), a.astype(acc) * b.astype(acc))
+    t, o = guarded(n, acc, 1)
+    abi.mx_map(abi.MX_U_NEG, da, None, o)
+    assert np.array_equal(whole(t, n, 1), -a.astype(acc))
+    if kind == "f32":
+        g = torch.tensor([-1.5], device="cuda")
+        (ta, ga), (tb, gb) = guarded(n, np.float32, 1), guarded(n, np.float32, 1)
+        abi.mx_dot_adjoint_f32(da, db, g, ga, gb)
+        assert np.array_equal(whole(ta, n, 1), np.float32(-1.5) * b) and np.array_equal(whole(tb, n, 1), np.float32(-1.5) * a)
