@@ -70,7 +70,7 @@ __device__ __forceinline__ float row16_sum(float v) {
 // needs, so tasks and rows of every offset and length take the same path.  The
 // address is a base that is the same in all lanes plus a 32-bit element offset
 // of the lane, which costs one register where a pointer per access costs two.
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+using f4u = uvec<float>;
 template <bool PAST> __device__ __forceinline__ f4u ld4(const float *base, unsigned off) {
     const f4u *q = reinterpret_cast<const f4u *>(reinterpret_cast<const char *>(base) + 4u * off);
     if constexpr (PAST) return __builtin_nontemporal_load(q);
@@ -78,26 +78,6 @@ template <bool PAST> __device__ __forceinline__ f4u ld4(const float *base, unsig
 }
 __device__ __forceinline__ void st4(f4u v, float *base, unsigned off) {
     __builtin_nontemporal_store(v, reinterpret_cast<f4u *>(reinterpret_cast<char *>(base) + 4u * off));
-}
-// The same through a buffer descriptor (raw, range and offsets in bytes): a
-// vector outside the range reads as zeros and is not written, which is how rows
-// past a tile's end and vectors past a row's end are left out without a branch.
-// Vectors lie wholly inside or outside.
-typedef __amdgpu_buffer_rsrc_t buf;
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-constexpr unsigned kOutside = 0x7fffff00u;  // an offset past every range
-constexpr int kPastCaches = 2;              // the non-temporal bit of a buffer access
-__device__ __forceinline__ buf make_buf(const float *p, int64_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, (int)bytes, 0x00027000);
-}
-template <bool PAST> __device__ __forceinline__ f4u bld4(buf b, unsigned off) {
-    return __builtin_bit_cast(f4u, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, PAST ? kPastCaches : 0));
-}
-__device__ __forceinline__ float bld1(buf b, unsigned off) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
-}
-__device__ __forceinline__ void bst4(f4u v, buf b, unsigned off) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), b, (int)off, 0, kPastCaches);
 }
 __device__ __forceinline__ float dot4(f4u a, f4u b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
 

@@ -49,7 +49,8 @@
 // Reduce-by-key from the registers that already hold the chunk: lane
 // (g, l16) holds dimensions 8g..8g+7 of points mi*16 + l16 and adds them to
 // wave-private LDS sums.  Lanes whose points share a label are separated into
-// passes by their rank among equal labels, so no instruction has two lanes on
+// passes by their rank among equal labels (of those that share one of a few
+// copies of the sums, where LDS has room), so no instruction has two lanes on
 // one address; a wave's LDS operations execute in issue order, so the sums
 // are the same on every run.  The block adds its waves in wave order and
 // writes one partial per block; a finish kernel adds the block partials in
@@ -68,6 +69,7 @@ constexpr int NT = 256;       // 4 waves
 constexpr int kWaves = NT / kWave;
 constexpr int kPtsWave = 64;  // points per wave chunk
 constexpr int kMaxBlocks = 768; // persistent grid (three blocks per CU on 256 CUs)
+constexpr int kMaxCopies = 8;
 constexpr int kMaxD = 64, kMaxK = 256, kMaxKD = 4096;
 // finish kernel: a block owns kFinEntries entries (j, t), its kFinGroups thread
 // groups take the block partials in turn
@@ -207,6 +209,7 @@ struct KmArgs {
     const float *X;
     int64_t n;
     int d, k;
+    int copies;         // of a wave's sums, a power of two: point p of a chunk adds to copy p % copies
     const float *C;
     int32_t *labels;
     float *part_sums;   // [ceil(k*d / 8)][nblocks][8]: entry e of block b at (e / 8 * nblocks + b) * 8 + e % 8
@@ -233,11 +236,14 @@ __device__ __forceinline__ void wave_sync() {
 
 // X fragments of chunk c: point c*64 + mi*16 + l16, dims kc*32 + 8g .. +7.
 // Branch-free, so the loads stay in flight while the current chunk is
-// processed: points past n are read from the last point (their labels are
-// never used) and dimensions past d from dimension d - 1 (the centroids are
-// zero there, so only |x|^2 needs them zeroed, which mask_chunk does when the
-// chunk is consumed).  VX: d == DP, X 16-byte aligned and fewer than 2^32
-// 16-byte vectors in X (two 16-byte loads at 32-bit vector offsets).
+// processed.  VX: d == DP, X 16-byte aligned and fewer than 2^32 16-byte vectors
+// in X (two 16-byte loads at 32-bit vector offsets; points past n are read from
+// the last point, their labels are never used).  Otherwise through a buffer
+// over the chunk: groups of four dimensions past d and points past n read as
+// zeros; the group that d ends in is read from d - 4 (fix_chunk moves it into
+// place when the chunk is consumed), of fewer than four dimensions one by one.
+// With a load per dimension at 64-bit addresses, 2^20 points of 16 dimensions
+// (k = 64) took 86 us a step, now 46 us; of 33 154 us, now 125 us.
 template <int DP, bool VX>
 __device__ __forceinline__ void load_chunk(float4 (&xa)[4][DP / 32][2], const KmArgs &a, int64_t c, int l16,
                                            int g) {
@@ -259,60 +265,80 @@ __device__ __forceinline__ void load_chunk(float4 (&xa)[4][DP / 32][2], const Km
         }
         return;
     }
+    const int64_t left = a.n - c * kPtsWave;
+    const buf b = make_buf(a.X + c * kPtsWave * d, 4 * d * (left < kPtsWave ? left : kPtsWave));
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi) {
-        const int64_t p = c * kPtsWave + mi * 16 + l16;
-        const int64_t pc = p < a.n ? p : a.n - 1;
+    for (int kc = 0; kc < DP / 32; ++kc)
 #pragma unroll
-        for (int kc = 0; kc < DP / 32; ++kc) {
-            const int t0 = kc * 32 + 8 * g;
-            {
-                float v[8];
+        for (int h = 0; h < 2; ++h) {
+            const int t = kc * 32 + 8 * g + 4 * h;
+            if (d >= 4) {
+                const unsigned at = t < d ? 4u * (unsigned)(l16 * d + min(t, d - 4)) : kOutside;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = a.X[pc * d + (t0 + e < d ? t0 + e : d - 1)];
-                xa[mi][kc][0] = make_float4(v[0], v[1], v[2], v[3]);
-                xa[mi][kc][1] = make_float4(v[4], v[5], v[6], v[7]);
+                for (int mi = 0; mi < 4; ++mi)
+                    xa[mi][kc][h] = __builtin_bit_cast(float4, bld4<false>(b, at + 64u * (unsigned)(mi * d)));
+            } else {
+                const unsigned at = t == 0 ? 4u * (unsigned)(l16 * d) : kOutside;
+#pragma unroll
+                for (int mi = 0; mi < 4; ++mi) {
+                    const unsigned o = at + 64u * (unsigned)(mi * d);
+                    xa[mi][kc][h] = make_float4(bld1(b, o), bld1(b, d > 1 ? o + 4 : kOutside),
+                                                bld1(b, d > 2 ? o + 8 : kOutside), 0.f);
+                }
             }
         }
-    }
 }
 
-// zeroes the dimensions past d (nothing to do when d == DP)
+// moves the group of four that d ends in to its place and zeroes the dimensions
+// past d (nothing to do when d is a multiple of four)
 template <int DP, bool VX>
-__device__ __forceinline__ void mask_chunk(float4 (&xa)[4][DP / 32][2], int d, int g) {
+__device__ __forceinline__ void fix_chunk(float4 (&xa)[4][DP / 32][2], int d, int g) {
     if constexpr (!VX) {
+        const int r = d & 3;
+        if (r == 0 || d < 4) return;  // wave-uniform
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int kc = 0; kc < DP / 32; ++kc)
 #pragma unroll
-            for (int kc = 0; kc < DP / 32; ++kc)
+            for (int h = 0; h < 2; ++h) {
+                const bool end = kc * 32 + 8 * g + 4 * h == d - r;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int t = kc * 32 + 8 * g + 4 * h;
-                    float4 &u = xa[mi][kc][h];
-                    u.x = t + 0 < d ? u.x : 0.f;
-                    u.y = t + 1 < d ? u.y : 0.f;
-                    u.z = t + 2 < d ? u.z : 0.f;
-                    u.w = t + 3 < d ? u.w : 0.f;
+                for (int mi = 0; mi < 4; ++mi) {
+                    // elements 4 - r .. 3 of the loaded group are dimensions d - r .. d - 1:
+                    // down by 4 - r, one step and two steps at a time
+                    const float4 u = xa[mi][kc][h];
+                    const bool s1 = end && r != 2, s2 = end && r != 3;
+                    const float a0 = s1 ? u.y : u.x, a1 = s1 ? u.z : u.y, a2 = s1 ? u.w : u.z, a3 = s1 ? 0.f : u.w;
+                    xa[mi][kc][h] = make_float4(s2 ? a2 : a0, s2 ? a3 : a1, s2 ? 0.f : a2, s2 ? 0.f : a3);
                 }
+            }
     }
 }
 
-// DP: d padded to a multiple of 32; KP: k padded to a multiple of 64.
-template <int DP, int KP, bool VX>
-__global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1) k_kmeans_fused(KmArgs a) {
+// Blocks of the fused kernel that a CU's registers are kept to: three at d <= 32,
+// k <= 64; two at d = 64, k <= 32 (2^20 points 112 us at one, 97 us; with the
+// general loads spills made it 133 us against 123 us).
+constexpr int blocks_per_cu(int DP, int KP, bool VX) { return DP == 32 ? (KP <= 64 ? 3 : 2) : VX && KP <= 32 ? 2 : 1; }
+
+// DP: d padded to a multiple of 32; KP: k padded to 16, 32 or a multiple of 64.
+// COPIES: a.copies > 1.
+template <int DP, int KP, bool VX, bool COPIES>
+__global__ void __launch_bounds__(NT, blocks_per_cu(DP, KP, VX)) k_kmeans_fused(KmArgs a) {
     constexpr int LDC = DP + 4;
-    constexpr int LBITS = KP <= 64 ? 6 : KP <= 128 ? 7 : 8;  // bits of a label
+    constexpr int LBITS = KP <= 16 ? 4 : KP <= 32 ? 5 : KP <= 64 ? 6 : KP <= 128 ? 7 : 8;  // bits of a label
+    constexpr bool ONE = KP <= 64;             // one centroid chunk, of NCI blocks of 16
+    constexpr int NCI = ONE ? KP / 16 : 4;
     extern __shared__ __attribute__((aligned(16))) float smem[];
     const int d = a.d, k = a.k;
+    const int copies = COPIES ? a.copies : 1, kr = k * copies;  // kr: rows of a wave's sums
     const int ldd = VX ? DP : sums_ld(d);              // VX: d == DP
     float *Cs = smem;                                  // [KP][LDC]
     float *cnorm = Cs + KP * LDC;                      // [KP]
-    float *sums_all = cnorm + KP;                      // [kWaves][k][ldd]
-    int *counts_all = (int *)(sums_all + kWaves * k * ldd);  // [kWaves][k]
-    float *scr = (float *)(counts_all + kWaves * k);   // [kWaves][scr_floats]
+    float *sums_all = cnorm + KP;                      // [kWaves][copies][k][ldd]
+    int *counts_all = (int *)(sums_all + kWaves * kr * ldd);  // [kWaves][copies][k]
+    float *scr = (float *)(counts_all + kWaves * kr);  // [kWaves][scr_floats]
     __shared__ float cmax_s;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
 
     // the first chunk's points are in flight while the centroids are staged
@@ -331,8 +357,9 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
         const int j = e / LDC, t = e - j * LDC;
         Cs[e] = (j < k && t < d) ? -2.0f * a.C[(int64_t)j * d + t] : 0.f;
     }
-    for (int e = tid; e < kWaves * k * ldd; e += NT) sums_all[e] = 0.f;
-    for (int e = tid; e < kWaves * k; e += NT) counts_all[e] = 0;
+    for (int e = tid; e < kWaves * kr * ldd / 4; e += NT)
+        reinterpret_cast<float4 *>(sums_all)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int e = tid; e < kWaves * kr; e += NT) counts_all[e] = 0;
     __syncthreads();
     if (wave == 0) {
         float m = 0.f;
@@ -362,7 +389,7 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
     // padded dimensions and kSlot = (2^bits - 1) / 128 for the index bits in
     // the values (six with one centroid chunk, else four), times four,
     // rounded up
-    constexpr float kSlot = (KP == 64 ? 63.0f : 15.0f) / 128.0f;
+    constexpr float kSlot = (ONE ? 63.0f : 15.0f) / 128.0f;
     constexpr float kXC = 4.0f * (6.03f + 2.032f * (6.0f * DP / 256.0f) + 2.0f * kSlot) + 0.05f;
     constexpr float kCC = 4.0f * (1.001f * (6.0f * DP / 256.0f) + (DP + 1.0f) / 256.0f + kSlot) + 0.05f;
     const bool bound_ok = cmax >= 0x1p-40f;  // products above the subnormal range
@@ -373,22 +400,30 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
         const float *q = Cs + (cc * 64 + ci * 16 + l16) * LDC + kc * 32 + 8 * g;
         split_bf16(*reinterpret_cast<const float4 *>(q), *reinterpret_cast<const float4 *>(q + 4), ah, am);
     };
-    bf16x8 areg_h[KP == 64 ? 4 : 1][DP / 32], areg_m[KP == 64 ? 4 : 1][DP / 32];
-    if constexpr (KP == 64) {
+    bf16x8 areg_h[ONE ? NCI : 1][DP / 32], areg_m[ONE ? NCI : 1][DP / 32];
+    if constexpr (ONE) {
 #pragma unroll
-        for (int ci = 0; ci < 4; ++ci)
+        for (int ci = 0; ci < NCI; ++ci)
 #pragma unroll
             for (int kc = 0; kc < DP / 32; ++kc) a_ops(0, ci, kc, areg_h[ci][kc], areg_m[ci][kc]);
     }
 
-    float *ws = sums_all + wave * k * ldd;
-    int *wc = counts_all + wave * k;
+    float *ws = sums_all + wave * kr * ldd;
+    int *wc = counts_all + wave * kr;
+    // this lane's copy, and the lanes (points) that share it
+    const int crow = COPIES ? (lane & (copies - 1)) * k : 0;
+    uint64_t sharing = ~0ull;
+    if constexpr (COPIES) {
+        sharing = 1;
+        for (int b = copies; b < 64; b <<= 1) sharing |= sharing << b;  // every copies-th bit
+        sharing <<= lane & (copies - 1);
+    }
     constexpr int kScr = scr_floats(DP, KP);
     float4 *pub = reinterpret_cast<float4 *>(scr + wave * kScr);  // scratch, 16-byte aligned
 
     for (; c < nchunks; c += wstride) {
         const int64_t p0 = c * kPtsWave;
-        mask_chunk<DP, VX>(xa, d, g);
+        fix_chunk<DP, VX>(xa, d, g);
 
         // this lane's part of |x|^2 (its eight or sixteen dimensions)
         float xpart[4];
@@ -418,18 +453,18 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
         //      merged in a fixed order (lexicographic minimum).
         float m1, m2, m3 = INFINITY, xx;  // m3: the third smallest (one centroid chunk only)
         int mj, mj2 = -1;
-        if constexpr (KP == 64) {
+        if constexpr (ONE) {
             // one point block at a time, so only its 16 accumulators are live
-            v4f cn[4];  // |c|^2 of rows 4g .. 4g+3 of each centroid block: the first product's source
+            v4f cn[NCI];  // |c|^2 of rows 4g .. 4g+3 of each centroid block: the first product's source
 #pragma unroll
-            for (int ci = 0; ci < 4; ++ci) {
+            for (int ci = 0; ci < NCI; ++ci) {
                 const float4 c4 = *reinterpret_cast<const float4 *>(cnorm + ci * 16 + 4 * g);
                 cn[ci] = v4f{c4.x, c4.y, c4.z, c4.w};
             }
             float r1[4], r2[4], r3[4];
 #pragma unroll
             for (int pi = 0; pi < 4; ++pi) {
-                v4f acc[4];
+                v4f acc[NCI];
 #pragma unroll
                 for (int kc = 0; kc < DP / 32; ++kc) {
                     // lane (g, l16) holds dimensions kc*32 + 8g .. +7 of point
@@ -437,19 +472,19 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
                     bf16x8 bh, bm;
                     split_bf16(xa[pi][kc][0], xa[pi][kc][1], bh, bm);
 #pragma unroll
-                    for (int ci = 0; ci < 4; ++ci)
+                    for (int ci = 0; ci < NCI; ++ci)
                         acc[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(areg_h[ci][kc], bh, kc == 0 ? cn[ci] : acc[ci],
                                                                           0, 0, 0);
 #pragma unroll
-                    for (int ci = 0; ci < 4; ++ci)
+                    for (int ci = 0; ci < NCI; ++ci)
                         acc[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(areg_h[ci][kc], bm, acc[ci], 0, 0, 0);
 #pragma unroll
-                    for (int ci = 0; ci < 4; ++ci)
+                    for (int ci = 0; ci < NCI; ++ci)
                         acc[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(areg_m[ci][kc], bh, acc[ci], 0, 0, 0);
                 }
                 float b1 = INFINITY, b2 = INFINITY, b3 = INFINITY;
 #pragma unroll
-                for (int ci = 0; ci < 4; ++ci)
+                for (int ci = 0; ci < NCI; ++ci)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
                         // bits 0-1 and 4-5 carry r and ci of the index
@@ -583,7 +618,7 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
         __builtin_amdgcn_sched_barrier(0);
         float4 xn[4][DP / 32][2];
         load_chunk<DP, VX>(xn, a, c + wstride < nchunks ? c + wstride : c, l16, g);
-        int lrv;  // this lane's point: rank << 16 | label, or -1
+        int lrv;  // this lane's point: rank << 16 | row of the sums, or -1
         // ---- certify each label (lane = point); uncertified points are
         //      recomputed in binary64 by the whole wave, lanes over centroids
         {
@@ -595,7 +630,7 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
                 certified = m2 - m1 > margin;
                 // every candidate but the best two is at least 2E above the
                 // best: the minimiser is one of those two
-                two = KP == 64 && !certified && m3 - m1 > margin && mj2 >= 0;
+                two = ONE && !certified && m3 - m1 > margin && mj2 >= 0;
                 label = mj;
             }
             // ---- the best two, compared in the FP32 direct form by all
@@ -603,7 +638,7 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
             //      dimensions for each of its points, the point's lane adds
             //      the four parts in lane-group order; within 2 (d + 3) u of
             //      the larger distance the point goes on to the stages below
-            if constexpr (KP == 64) {
+            if constexpr (ONE) {
                 if (__ballot(two)) {
                     // both indices of each point to the four lanes holding
                     // its dimensions
@@ -765,10 +800,11 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
                 if (lane == q) label = bj;
             }
             if (p < a.n) a.labels[p] = label;
-            if (label >= 0) atomicAdd(&wc[label], 1);  // integer: order-free
-            // rank among the chunk's earlier points with the same label: the
-            // lanes with an equal label, found one label bit at a time
-            const uint64_t valid = __ballot(label >= 0);
+            if (label >= 0) atomicAdd(&wc[crow + label], 1);  // integer: order-free
+            // rank among the chunk's earlier points with the same label and
+            // copy: the lanes with an equal label, found one label bit at a time
+            uint64_t valid = __ballot(label >= 0);
+            if constexpr (COPIES) valid &= sharing;
             uint32_t slo = (uint32_t)valid, shi = (uint32_t)(valid >> 32);
 #pragma unroll
             for (int b = 0; b < LBITS; ++b) {
@@ -780,7 +816,7 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
                 shi &= ~((uint32_t)(mb >> 32) ^ m);
             }
             const int rank = (int)__builtin_amdgcn_mbcnt_hi(shi, __builtin_amdgcn_mbcnt_lo(slo, 0u));
-            lrv = label >= 0 ? (rank << 16) | label : -1;
+            lrv = label >= 0 ? (rank << 16) | (crow + label) : -1;
         }
         wave_sync();
         // ---- reduce-by-key from registers.  Pass m adds every point whose
@@ -856,24 +892,25 @@ __global__ void __launch_bounds__(NT, (DP == 32 && KP == 64) ? (VX ? 3 : 2) : 1)
             }
     }
     __syncthreads();
-    // ---- block partial: waves added in wave order
+    // ---- block partial: the copies in order, of each the waves in order
     const int kd = k * d;
     // entry groups of 8 with the blocks side by side, so that the finish
     // kernel's waves read eight blocks' groups as 256 contiguous bytes
     float *ps = a.part_sums + (int64_t)blockIdx.x * kFinEntries;
     for (int e = tid; e < kd; e += NT) {
         const int j = e / d, t = e - j * d;
-        const int at = sums_at(j, t, ldd);
-        float s = sums_all[at];
+        float s = 0.f;
+        for (int q = 0; q < copies; ++q) {
+            const int at = sums_at(q * k + j, t, ldd);
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) s += sums_all[w * k * ldd + at];
+            for (int w = 0; w < kWaves; ++w) s += sums_all[w * kr * ldd + at];
+        }
         ps[(int64_t)(e / kFinEntries) * gridDim.x * kFinEntries + e % kFinEntries] = s;
     }
     int *pc = a.part_counts + blockIdx.x;  // label j at [j * gridDim.x]
     for (int j = tid; j < k; j += NT) {
-        int cn = counts_all[j];
-#pragma unroll
-        for (int w = 1; w < kWaves; ++w) cn += counts_all[w * k + j];
+        int cn = 0;
+        for (int r = j; r < kWaves * kr; r += k) cn += counts_all[r];
         pc[(int64_t)j * gridDim.x] = cn;
     }
 }
@@ -1000,35 +1037,118 @@ __global__ void __launch_bounds__(NT) k_kmeans_divide_plain(const float *__restr
 }
 
 // ---------------------------------------------------------------- SSE and its gradient
-// Partial sums of (x - c_label)^2, one per block.  VEC: d % 4 == 0 and X, C
-// 16-byte aligned (16-byte loads, the vector index split by 32-bit division
-// when n*d/4 < 2^32, which it is for any X below 16 GiB).
-template <bool VEC>
-__global__ void __launch_bounds__(NT) k_sse_partial(const float *__restrict__ X, int64_t n, int d,
-                                                    const float *__restrict__ C,
-                                                    const int32_t *__restrict__ labels, float *__restrict__ part) {
-    __shared__ float red[NT / kWave];
-    float acc = 0.f;
-    if constexpr (VEC) {
-        const uint32_t dv = (uint32_t)d / 4, nv = (uint32_t)(n * d / 4);
-        const float4 *X4 = reinterpret_cast<const float4 *>(X), *C4 = reinterpret_cast<const float4 *>(C);
-        for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < nv; i += gridDim.x * NT) {
-            const uint32_t p = i / dv, q = i - p * dv;
-            const float4 x = X4[i];
-            const float4 c = C4[(uint32_t)labels[p] * dv + q];
-            const float a = x.x - c.x, b = x.y - c.y, e = x.z - c.z, f = x.w - c.w;
-            acc += (a * a + b * b) + (e * e + f * f);
-        }
+// Both walk X as one array of n d floats in contiguous chunks of 4 vectors per
+// thread at any alignment, and need each element's point and dimension: the
+// chunk's first point by a 64-bit reciprocal in scalar registers, the points
+// after it by a 32-bit one (m32; d below 2^15, else a division).  Bound by HBM
+// and the memory-side cache: 2^20 points of 32 dimensions, SSE 28.8 us -> 24.7 us
+// (two alternating inputs; 5.4 TB/s), gradient 48.9 us -> 44.8 us (6.0 TB/s); of 33
+// dimensions 92 us -> 49 us and 95 us -> 58 us.  Blocks of 256 threads with four
+// vectors each took 30 us and 45 us.
+constexpr int SNT = 512;  // 1024 blocks (the partials' room) of it fill every CU
+constexpr int kSseVec = 2;
+constexpr int kSseChunk = 4 * kSseVec * SNT;  // elements; a vector per thread up to 2^20 elements
+int64_t sse_chunk_of(int64_t total) { return total <= 1 << 20 ? 4 * SNT : kSseChunk; }
+
+struct SseArgs {
+    const float *X, *C;
+    const int32_t *labels;
+    int64_t total, chunk;  // n d; elements of a chunk
+    uint32_t d, m32;
+    uint64_t m64;
+};
+
+SseArgs sse_args(const float *X, int64_t n, int d, const float *C, const int32_t *labels) {
+    const uint64_t ud = (uint64_t)d;
+    return SseArgs{X, C, labels, n * d, sse_chunk_of(n * d), (uint32_t)d, d > 1 ? (uint32_t)(0x100000000ull / ud + 1) : 0u, ~0ull / ud};
+}
+
+// Where a chunk lies: its first point (64-bit reciprocal: the estimate is at
+// most one too small) and, from an element's offset in the chunk, the element's
+// point and dimension.
+struct SseAt {
+    const float *x;
+    const int32_t *lab;
+    uint32_t r0, left;  // dimension of the first element; elements of the chunk
+};
+__device__ __forceinline__ SseAt sse_at(const SseArgs &a, int64_t e0) {
+    int64_t p0 = (int64_t)__umul64hi((uint64_t)e0, a.m64);
+    if ((p0 + 1) * (int64_t)a.d <= e0) ++p0;
+    return SseAt{a.X + e0, a.labels + p0, (uint32_t)(e0 - p0 * (int64_t)a.d),
+                 (uint32_t)(a.total - e0 < a.chunk ? a.total - e0 : a.chunk)};
+}
+__device__ __forceinline__ uint32_t sse_point(const SseArgs &a, uint32_t r) {
+    return a.d == 1 ? r : a.d < 32768u ? __umulhi(r, a.m32) : r / a.d;
+}
+__device__ __forceinline__ float sse_c1(const SseArgs &a, const SseAt &at, uint32_t off) {
+    const uint32_t r = at.r0 + off, q = sse_point(a, r);
+    return a.C[(int64_t)at.lab[q] * a.d + (r - q * a.d)];
+}
+// the centroid values of the four elements from off.  V4: d % 4 == 0, so that
+// the four belong to one point
+template <bool V4> __device__ __forceinline__ uvec<float> sse_c4(const SseArgs &a, const SseAt &at, uint32_t off) {
+    if constexpr (V4) {
+        const uint32_t r = at.r0 + off, q = sse_point(a, r);
+        return load16<false>(a.C + (int64_t)at.lab[q] * a.d + (r - q * a.d));
     } else {
-        const int64_t total = n * d;
-        for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < total; e += (int64_t)gridDim.x * NT) {
-            const int64_t p = e / d;
-            const float diff = X[e] - C[(int64_t)labels[p] * d + (e - p * d)];
-            acc += diff * diff;
+        return uvec<float>{sse_c1(a, at, off), sse_c1(a, at, off + 1), sse_c1(a, at, off + 2), sse_c1(a, at, off + 3)};
+    }
+}
+
+// Partial sums of (x - c_label)^2, one per block; of a single block the result.
+// V4: the next chunk's points and labels are in flight while this one's
+// centroid values are fetched and folded.
+template <bool V4>
+__global__ void __launch_bounds__(SNT) k_sse_partial(SseArgs a, float *__restrict__ part) {
+    __shared__ float red[SNT / kWave];
+    uvec<float> acc = {0.f, 0.f, 0.f, 0.f};
+    const int64_t step = (int64_t)gridDim.x * a.chunk;
+    int64_t e0 = (int64_t)blockIdx.x * a.chunk;
+    auto fold = [&](uvec<float> x, uvec<float> c) {
+        const uvec<float> q = x - c;
+        acc += q * q;
+    };
+    if constexpr (V4) {
+        uvec<float> x[kSseVec];
+        int l[kSseVec];
+        uint32_t o[kSseVec];
+        auto load = [&](int64_t e) {
+            const SseAt at = sse_at(a, e);
+#pragma unroll
+            for (int u = 0; u < kSseVec; ++u) {
+                const uint32_t off = 4 * (threadIdx.x + u * SNT), r = at.r0 + off, q = sse_point(a, r);
+                x[u] = load16<false>(at.x + off);
+                l[u] = at.lab[q];
+                o[u] = r - q * a.d;
+            }
+        };
+        if (e0 + kSseChunk <= a.total && a.chunk == kSseChunk) {
+            load(e0);
+            for (; e0 + kSseChunk <= a.total; e0 += step) {
+                uvec<float> c[kSseVec], xc[kSseVec];
+#pragma unroll
+                for (int u = 0; u < kSseVec; ++u) {
+                    c[u] = load16<false>(a.C + (int64_t)l[u] * a.d + o[u]);
+                    xc[u] = x[u];
+                }
+                if (e0 + step + kSseChunk <= a.total) load(e0 + step);
+#pragma unroll
+                for (int u = 0; u < kSseVec; ++u) fold(xc[u], c[u]);
+            }
         }
     }
-    acc = block_reduce<Red<MX_ADD, float>, NT>(acc, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = acc;
+    for (; e0 < a.total; e0 += step) {
+        const SseAt at = sse_at(a, e0);
+        const uint32_t nv = at.left >> 2, t = 4 * nv + threadIdx.x;
+#pragma unroll 2
+        for (uint32_t i = threadIdx.x; i < nv; i += SNT) fold(load16<false>(at.x + 4 * i), sse_c4<V4>(a, at, 4 * i));
+        if (t < at.left) {
+            const float q = at.x[t] - sse_c1(a, at, t);
+            acc[0] += q * q;
+        }
+    }
+    const float s = block_reduce<Red<MX_ADD, float>, SNT>((acc[0] + acc[1]) + (acc[2] + acc[3]), red);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
 __global__ void __launch_bounds__(NT) k_sse_final(const float *__restrict__ part, int nb, float *__restrict__ out) {
@@ -1039,25 +1159,25 @@ __global__ void __launch_bounds__(NT) k_sse_final(const float *__restrict__ part
     if (threadIdx.x == 0) out[0] = (float)acc;
 }
 
-__global__ void __launch_bounds__(NT) k_sse_grad(const float *__restrict__ X, int64_t n, int d,
-                                                 const float *__restrict__ C, const int32_t *__restrict__ labels,
-                                                 const float *__restrict__ gscale, float *__restrict__ G, int vec) {
+template <bool V4, bool PAST>
+__global__ void __launch_bounds__(SNT) k_sse_grad(SseArgs a, const float *__restrict__ gscale, float *__restrict__ G) {
     const float g2 = 2.0f * gscale[0];
-    const int64_t stride = (int64_t)gridDim.x * NT;
-    if (vec) {  // d % 4 == 0, 16-byte aligned
-        const int64_t nv = n * d / 4;
-        const int dv = d / 4;
-        for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < nv; i += stride) {
-            const int64_t p = i / dv;
-            const float4 x = reinterpret_cast<const float4 *>(X)[i];
-            const float4 c = reinterpret_cast<const float4 *>(C)[(int64_t)labels[p] * dv + (i - p * dv)];
-            reinterpret_cast<float4 *>(G)[i] =
-                make_float4(g2 * (x.x - c.x), g2 * (x.y - c.y), g2 * (x.z - c.z), g2 * (x.w - c.w));
-        }
-    } else {
-        for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < n * d; e += stride) {
-            const int64_t p = e / d;
-            G[e] = g2 * (X[e] - C[(int64_t)labels[p] * d + (e - p * d)]);
+    for (int64_t e0 = (int64_t)blockIdx.x * a.chunk; e0 < a.total; e0 += (int64_t)gridDim.x * a.chunk) {
+        const SseAt at = sse_at(a, e0);
+        float *go = G + e0;
+        if (at.left == kSseChunk) {
+            uvec<float> x[kSseVec], c[kSseVec];
+#pragma unroll
+            for (int u = 0; u < kSseVec; ++u) x[u] = load16<PAST>(at.x + 4 * (threadIdx.x + u * SNT));
+#pragma unroll
+            for (int u = 0; u < kSseVec; ++u) c[u] = sse_c4<V4>(a, at, 4 * (threadIdx.x + u * SNT));
+#pragma unroll
+            for (int u = 0; u < kSseVec; ++u) store16(g2 * (x[u] - c[u]), go + 4 * (threadIdx.x + u * SNT));
+        } else {
+            const uint32_t nv = at.left >> 2, t = 4 * nv + threadIdx.x;
+            for (uint32_t i = threadIdx.x; i < nv; i += SNT)
+                store16(g2 * (load16<false>(at.x + 4 * i) - sse_c4<V4>(a, at, 4 * i)), go + 4 * i);
+            if (t < at.left) go[t] = g2 * (at.x[t] - sse_c1(a, at, t));
         }
     }
 }
@@ -1068,9 +1188,24 @@ int64_t fused_blocks(int64_t n) {
     return b < kMaxBlocks ? b : kMaxBlocks;
 }
 
-size_t fused_lds_bytes(int DP, int KP, int k, int d) {
-    return (size_t)KP * (DP + 4) * 4 + (size_t)KP * 4 + (size_t)kWaves * k * sums_ld(d) * 4 + (size_t)kWaves * k * 4 +
+size_t fused_lds_bytes(int DP, int KP, int k, int d, int copies) {
+    return (size_t)KP * (DP + 4) * 4 + (size_t)KP * 4 +
+           (size_t)kWaves * copies * ((size_t)k * sums_ld(d) * 4 + (size_t)k * 4) +
            (size_t)kWaves * scr_floats(DP, KP) * 4;
+}
+
+// Copies of a wave's sums, so that fewer points of a chunk share a row and the
+// reduce-by-key takes fewer passes: doubled up to 128 rows (two for each of the
+// chunk's points: 2^20 points of 16 dimensions, k = 10, take 50, 41, 37 and 34
+// us a step with 1, 2, 4 and 8, 43 us with 16; k = 32 42 us and 38 us with 1
+// and 2 or 4), within the LDS of the blocks that the registers allow (160 KB a
+// CU: none at d = 32, k = 64, where a block less per CU would cost more).
+int sum_copies(int DP, int KP, bool VX, int k, int d, size_t most) {
+    if (KP > 64) return 1;
+    const size_t room = std::min<size_t>(most, (size_t)163840 / blocks_per_cu(DP, KP, VX) - 64);
+    int c = 1;
+    while (c < kMaxCopies && k * c < 128 && fused_lds_bytes(DP, KP, k, d, 2 * c) <= room) c *= 2;
+    return c;
 }
 
 size_t ws_layout(int64_t n, int d, int k, size_t *sums_off, size_t *counts_off, size_t *plain_off) {
@@ -1098,12 +1233,16 @@ mx_status check(const char *who, const float *X, int64_t n, int d, const float *
 std::atomic<long long> g_last_fallbacks{-1};
 unsigned long long *g_fb_counter[64] = {};
 
+bool fused_vx(const KmArgs &a, int DP) { return a.d == DP && (uintptr_t)a.X % 16 == 0 && a.n * DP / 4 < (1LL << 32); }
+
 template <int DP, int KP>
 void launch_fused(const KmArgs &a, int64_t nb, size_t lds, hipStream_t s) {
-    if (a.d == DP && (uintptr_t)a.X % 16 == 0 && a.n * DP / 4 < (1LL << 32))
-        hipLaunchKernelGGL((k_kmeans_fused<DP, KP, true>), dim3((unsigned)nb), dim3(NT), lds, s, a);
-    else
-        hipLaunchKernelGGL((k_kmeans_fused<DP, KP, false>), dim3((unsigned)nb), dim3(NT), lds, s, a);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(NT), lds, s, a); };
+    const bool vx = fused_vx(a, DP);
+    if constexpr (KP <= 64) {
+        if (a.copies > 1) return vx ? go(k_kmeans_fused<DP, KP, true, true>) : go(k_kmeans_fused<DP, KP, false, true>);
+    }
+    vx ? go(k_kmeans_fused<DP, KP, true, false>) : go(k_kmeans_fused<DP, KP, false, false>);
 }
 
 }  // namespace
@@ -1133,13 +1272,16 @@ mx_status mx_kmeans_step_f32(const float *X_dev, int64_t n, int d, const float *
     const int64_t nb = fused_blocks(n);
     MX_REQUIRE(nb < (1LL << 31), MX_ERR_SHAPE, "%s: too many points", who);
     const int DP = d <= 32 ? 32 : 64;
-    const int KP = (int)ceil_div(k, 64) * 64;
-    const size_t lds = fused_lds_bytes(DP, KP, k, d);
+    // products and candidates of whole blocks of 16 centroids: at k = 10 a step of
+    // 2^20 points of 8 dimensions took 103 us padded to 64, 71 us to 16
+    const int KP = k <= 16 ? 16 : k <= 32 ? 32 : (int)ceil_div(k, 64) * 64;
     const DeviceInfo *dv;
     if (mx_status st = device_info(&dv)) return st;
+    KmArgs a{X_dev, n, d, k, 1, C_dev, labels_dev, (float *)((char *)ws + so), (int *)((char *)ws + co), nullptr};
+    a.copies = sum_copies(DP, KP, fused_vx(a, DP), k, d, (size_t)dv->lds_bytes);
+    const size_t lds = fused_lds_bytes(DP, KP, k, d, a.copies);
     MX_REQUIRE(lds <= (size_t)dv->lds_bytes, MX_ERR_UNSUPPORTED,
                "%s: k = %d, d = %d needs %zu bytes of LDS (the device allows %d)", who, k, d, lds, dv->lds_bytes);
-    KmArgs a{X_dev, n, d, k, C_dev, labels_dev, (float *)((char *)ws + so), (int *)((char *)ws + co), nullptr};
     const bool dbg = debug_mode();
     if (dbg) {
         if (!g_fb_counter[dv->device]) MX_TRY_HIP(hipMalloc(&g_fb_counter[dv->device], sizeof(unsigned long long)));
@@ -1149,6 +1291,8 @@ mx_status mx_kmeans_step_f32(const float *X_dev, int64_t n, int d, const float *
     if (n > 0) {
         if (DP == 32) {
             switch (KP) {
+            case 16: launch_fused<32, 16>(a, nb, lds, stream); break;
+            case 32: launch_fused<32, 32>(a, nb, lds, stream); break;
             case 64: launch_fused<32, 64>(a, nb, lds, stream); break;
             case 128: launch_fused<32, 128>(a, nb, lds, stream); break;
             case 192: launch_fused<32, 192>(a, nb, lds, stream); break;
@@ -1156,6 +1300,8 @@ mx_status mx_kmeans_step_f32(const float *X_dev, int64_t n, int d, const float *
             }
         } else {
             switch (KP) {
+            case 16: launch_fused<64, 16>(a, nb, lds, stream); break;
+            case 32: launch_fused<64, 32>(a, nb, lds, stream); break;
             case 64: launch_fused<64, 64>(a, nb, lds, stream); break;
             default: launch_fused<64, 128>(a, nb, lds, stream); break;  // k*d <= 4096 bounds k to 64 at d = 64
             }
@@ -1212,13 +1358,11 @@ mx_status mx_kmeans_sse_f32(const float *X_dev, int64_t n, int d, const float *C
     MX_REQUIRE(ws && ws_bytes >= need && ((uintptr_t)ws & 255) == 0, MX_ERR_WORKSPACE,
                "%s: workspace needs %zu bytes, 256-byte aligned", who, need);
     float *part = (float *)((char *)ws + kCounterBytes);
-    int nb = (int)std::min<int64_t>(1024, ceil_div(n * d > 0 ? n * d : 1, NT * 4));
-    const bool vec = d % 4 == 0 && (uintptr_t)X_dev % 16 == 0 && (uintptr_t)C_dev % 16 == 0 && n * d / 4 < (1LL << 32);
-    if (vec)
-        hipLaunchKernelGGL(k_sse_partial<true>, dim3(nb), dim3(NT), 0, stream, X_dev, n, d, C_dev, labels_dev, part);
-    else
-        hipLaunchKernelGGL(k_sse_partial<false>, dim3(nb), dim3(NT), 0, stream, X_dev, n, d, C_dev, labels_dev, part);
-    hipLaunchKernelGGL(k_sse_final, dim3(1), dim3(NT), 0, stream, part, nb, sse_dev);
+    const int nb = (int)std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(n * d, sse_chunk_of(n * d))));
+    const SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
+    hipLaunchKernelGGL(d % 4 == 0 ? k_sse_partial<true> : k_sse_partial<false>, dim3(nb), dim3(SNT), 0, stream, a,
+                       nb == 1 ? sse_dev : part);
+    if (nb > 1) hipLaunchKernelGGL(k_sse_final, dim3(1), dim3(NT), 0, stream, part, nb, sse_dev);
     return last_launch(who);
 }
 
@@ -1229,15 +1373,12 @@ mx_status mx_kmeans_sse_grad_f32(const float *X_dev, int64_t n, int d, const flo
     MX_REQUIRE(n >= 0 && d >= 1, MX_ERR_SHAPE, "%s: bad sizes", who);
     if (n == 0) return MX_OK;
     MX_REQUIRE(X_dev && C_dev && labels_dev && gscale_dev && G_dev, MX_ERR_INVALID, "%s: null pointer", who);
-    const DeviceInfo *dv;
-    if (mx_status st = device_info(&dv)) return st;
-    const int vec = (d % 4 == 0) && ((uintptr_t)X_dev % 16 == 0) && ((uintptr_t)C_dev % 16 == 0) &&
-                    ((uintptr_t)G_dev % 16 == 0);
-    const int64_t items = vec ? n * d / 4 : n * d;
-    int64_t grid = ceil_div(items, NT);
-    if (grid > (int64_t)dv->num_cus * 16) grid = (int64_t)dv->num_cus * 16;
-    hipLaunchKernelGGL(k_sse_grad, dim3((unsigned)grid), dim3(NT), 0, stream, X_dev, n, d, C_dev, labels_dev,
-                       gscale_dev, G_dev, vec);
+    const SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
+    const bool past = n * d * 2 * (int64_t)sizeof(float) > kCacheBytes;
+    const unsigned grid = (unsigned)std::min<int64_t>(65536, ceil_div(n * d, sse_chunk_of(n * d)));
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(SNT), 0, stream, a, gscale_dev, G_dev); };
+    if (d % 4 == 0) past ? go(k_sse_grad<true, true>) : go(k_sse_grad<true, false>);
+    else past ? go(k_sse_grad<false, true>) : go(k_sse_grad<false, false>);
     return last_launch(who);
 }
 

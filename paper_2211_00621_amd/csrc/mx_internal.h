@@ -97,6 +97,27 @@ template <class T> __device__ __forceinline__ void store16(uvec<T> v, T *p) {
     __builtin_nontemporal_store(v, reinterpret_cast<uvec<T> *>(p));
 }
 
+// 16 bytes of floats through a buffer descriptor (raw, range and offsets in bytes): a
+// vector outside the range reads as zeros and is not written, which is how rows
+// past a tile's end and vectors past a row's end are left out without a branch.
+// Vectors lie wholly inside or outside.
+typedef __amdgpu_buffer_rsrc_t buf;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+constexpr unsigned kOutside = 0x7fffff00u;  // an offset past every range
+constexpr int kPastCaches = 2;              // the non-temporal bit of a buffer access
+__device__ __forceinline__ buf make_buf(const float *p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, (int)bytes, 0x00027000);
+}
+template <bool PAST> __device__ __forceinline__ uvec<float> bld4(buf b, unsigned off) {
+    return __builtin_bit_cast(uvec<float>, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, PAST ? kPastCaches : 0));
+}
+__device__ __forceinline__ float bld1(buf b, unsigned off) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
+}
+__device__ __forceinline__ void bst4(uvec<float> v, buf b, unsigned off) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), b, (int)off, 0, kPastCaches);
+}
+
 // The memory-side cache.  An element-wise pass over less keeps its inputs there
 // for the next reader (64 MB of inputs, then read again: 32.6 us the two, 36.9
 // us with loads past it); of a larger one little would be left (1 GB: 542 us
