@@ -821,8 +821,9 @@ __global__ void __launch_bounds__(NT) k_fill(Acc *__restrict__ out, int64_t n, A
 // `rb` consecutive rows, whose values form one contiguous span
 // [offsets[r0], offsets[r0 + rb]).  The span's 16-byte vectors are cut into
 // four contiguous quarters, one per wave; inside its quarter a wave's lanes
-// interleave (coalesced), four vectors per lane in flight (16 KB per block;
-// eight blocks per CU).  The offsets cost one round trip per rb rows.
+// interleave (coalesced), four vectors per lane in flight (16 KB per block,
+// eight blocks per CU; eight vectors 27.3 us against 24.3 us, two 25.8 us, for
+// 65 536 rows of mean 490).  The offsets cost one round trip per rb rows.
 //
 // Row attribution: the positions a thread visits increase, so the row they
 // fall in never decreases.  A thread keeps one accumulator for its current
@@ -832,7 +833,7 @@ __global__ void __launch_bounds__(NT) k_fill(Acc *__restrict__ out, int64_t n, A
 // its quarter.  Afterwards each row's NT slots are folded in a fixed order
 // (four per lane, then the DPP wave tree), so the result depends only on the
 // offsets, never on timing.
-constexpr int kSpanRows = 8;  // rows per block, at most
+constexpr int kSpanRows = 16;  // rows per block, at most
 
 // LDS: rb + 1 offsets (padded to 16 bytes), then rb x NT accumulator slots
 __host__ __device__ constexpr size_t span_off_bytes(int rb) { return ((size_t)(rb + 1) * 8 + 15) & ~(size_t)15; }
@@ -1455,10 +1456,19 @@ constexpr int64_t kSpanAvgMax = 16384;  // average row length, at most
 bool seg_span_path(int64_t nseg, int64_t nval, const DeviceInfo *d) {
     return nseg >= (int64_t)d->num_cus * 32 && nval <= nseg * kSpanAvgMax;
 }
-// rows per block of the row-span kernels: 32 blocks per CU, at most kSpanRows rows each
-int span_rows(int64_t nseg, const DeviceInfo *d) {
-    const int64_t rb = ceil_div(nseg, (int64_t)d->num_cus * 32);
-    return (int)(rb < 1 ? 1 : rb > kSpanRows ? kSpanRows : rb);
+// Rows per block of the row-span kernels: what leaves eight blocks per CU, at
+// most sixteen rows of an average length up to `avg16`, eight of longer ones (a
+// row is a block's chain of offsets, values and store; more of them share it,
+// until the spans are long enough by themselves).  Reduce, us with at most 8,
+// 16 and 32: 65 536 rows of mean 203 16.2, 13.5, 17.0, of mean 490 23.2, 23.2,
+// 26.7, of mean 1675 71.0, 74.7, 77.1; 20 000 of mean 489 12.5, 10.8, 9.5; 8192 of
+// mean 917 12.0 with one, 9.7 with two, 8.2 with four.  Broadcast: mean 203 13.4,
+// 12.3, 12.5, mean 490 22.4, 22.8, 23.8.  Eight-byte sums take half, whose LDS
+// slots are twice as large.
+constexpr int64_t kSpanAvg16 = 600, kSpanAvg16Bcast = 300;
+int span_rows(int64_t nseg, int64_t nval, int64_t avg16, size_t acc, const DeviceInfo *d) {
+    const int64_t most = acc <= 4 && nval <= avg16 * nseg ? kSpanRows : kSpanRows / 2;
+    return (int)std::min(most, ceil_div(nseg, (int64_t)d->num_cus * 8));
 }
 
 template <mx_dtype D, int OP>
@@ -1508,7 +1518,7 @@ mx_status launch_seg(bool plain, const void *values, int64_t nval, const int64_t
             return last_launch("mx_segmented_reduce");
         }
         if (seg_span_path(nseg, nval, d)) {
-            const int rb = span_rows(nseg, d);
+            const int rb = span_rows(nseg, nval, kSpanAvg16, sizeof(Acc), d);
             const int64_t grid = ceil_div(nseg, rb);
             MX_REQUIRE(grid <= 0x7fffffff, MX_ERR_SHAPE, "mx_segmented_reduce: too many rows");
             hipLaunchKernelGGL((k_seg_span<D, OP>), dim3((unsigned)grid), dim3(NT), span_lds_bytes<D>(rb), s,
@@ -1621,7 +1631,7 @@ mx_status segmented_broadcast(const float *gout, const int64_t *off, int64_t nse
         return last_launch("mx_segmented_sum_adjoint_f32");
     }
     if (seg_span_path(nseg, nval, d)) {
-        const int rb = span_rows(nseg, d);
+        const int rb = span_rows(nseg, nval, kSpanAvg16Bcast, sizeof(float), d);
         const int64_t grid = ceil_div(nseg, rb);
         MX_REQUIRE(grid <= 0x7fffffff, MX_ERR_SHAPE, "mx_segmented_sum_adjoint_f32: too many rows");
         hipLaunchKernelGGL(k_seg_broadcast, dim3((unsigned)grid), dim3(NT), 0, s, gout, off, nseg, rb, gval,
