@@ -57,35 +57,35 @@ TRAFFIC = {
     # Each XCD's L2 fetches the A row panels and B column panels of its own 32 tiles (4 x 8 of them:
     # 12 panels of 1 MiB, the fewest 32 tiles can need), so each A panel is fetched by two XCDs and
     # each B panel by four; the algorithmic minimum is 33.6 MB read + 16.8 MB written (2.34x)
-    "gemm_nn": {"file": "gemm.hip", "bytes": 117556154,
-                "source": "3fa3f9cc142e6e3fc95d3119b28c30c57cd618a098fbb99592d7b86d88652302"},
-    "gemm_nt": {"file": "gemm.hip", "bytes": 117533627,
-                "source": "3fa3f9cc142e6e3fc95d3119b28c30c57cd618a098fbb99592d7b86d88652302"},
-    "gemm_tn": {"file": "gemm.hip", "bytes": 117545915,
-                "source": "3fa3f9cc142e6e3fc95d3119b28c30c57cd618a098fbb99592d7b86d88652302"},
-    # k_seg_span (row-span path, nontemporal loads), 65536 rows / 32.1 M values: 132.97 MB fetched + 0.26 MB
+    "gemm_nn": {"file": "gemm.hip", "bytes": 117518329,
+                "source": "9d864bd422699980a0cb2bb5a66c83d3fa62ace401ef55575768a0cb684a8318"},
+    "gemm_nt": {"file": "gemm.hip", "bytes": 117508090,
+                "source": "9d864bd422699980a0cb2bb5a66c83d3fa62ace401ef55575768a0cb684a8318"},
+    "gemm_tn": {"file": "gemm.hip", "bytes": 117514233,
+                "source": "9d864bd422699980a0cb2bb5a66c83d3fa62ace401ef55575768a0cb684a8318"},
+    # k_seg_span (row-span path, nontemporal loads), 65536 rows / 32.1 M values: 132.46 MB fetched + 0.26 MB
     # written (1.03x algorithmic: 129.19 MB)
-    "seg_span": {"file": "segmented.hip", "bytes": 133236853,
-                 "source": "a8bece18ab4e27185c0dc7f3fd5dd1e17669a291e87375a06719fcbf9360ccc5"},
+    "seg_span": {"file": "segmented.hip", "bytes": 132718721,
+                 "source": "a3c56bd4f33368dfc7fbafe501633bb8c18c298201b3dc913b0477a524f48603"},
     # mx_xvjp (generated from expr.hip) for exp(-(a-b)^2)*0.5 + a*b over 2^26 float32 pairs:
-    # 536.89 MB fetched + 536.83 MB written (1.00x algorithmic)
-    "expr_vjp": {"file": "expr.hip", "bytes": 1073735829,
-                 "source": "61460c2f96be411e8917cad03f7a568e43228502abc50e0cff6db2ebedee319d"},
+    # 536.92 MB fetched + 536.87 MB written (1.00x algorithmic)
+    "expr_vjp": {"file": "expr.hip", "bytes": 1073796731,
+                 "source": "e9c60cbd040d338763634b52a9c29e55deaa99904b421b9e6dce4228f185b618"},
     # mx_xseg_add, same body over the nested step's 65 536 ragged rows (2 x 32.1 M values):
-    # 261.14 MB fetched + 0.26 MB written (1.01x algorithmic)
-    "expr_seg": {"file": "expr.hip", "bytes": 261411148,
-                 "source": "61460c2f96be411e8917cad03f7a568e43228502abc50e0cff6db2ebedee319d"},
+    # 262.30 MB fetched + 0.26 MB written (1.02x algorithmic)
+    "expr_seg": {"file": "expr.hip", "bytes": 262557234,
+                 "source": "e9c60cbd040d338763634b52a9c29e55deaa99904b421b9e6dce4228f185b618"},
     # k_stencil7, 512 x 512 x 64 float32: 73.15 MB fetched (1.09x: a 16-plane slab re-reads the planes
     # below and above it) + 67.10 MB written
-    "stencil": {"file": "parboil.hip", "bytes": 140264894,
-                "source": "43811f5900aa96af3dc0bca90ae62f896a5a0aac06bc3e30816ec5f7f6f67ece"},
-    # k_kmeans_fused<32,64,true>, 2^20 x 32 points, k = 64: 134.68 MB fetched (X, 1.00x) + 12.11 MB written
+    "stencil": {"file": "parboil.hip", "bytes": 140279381,
+                "source": "e36e32c421864034d324bbbbb984f2f6d0576c348c596ce47b74d91d3db139a8"},
+    # k_kmeans_fused<32,64,true,false>, 2^20 x 32 points, k = 64: 134.68 MB fetched (X, 1.00x) + 12.11 MB written
     # (labels, and 768 block partials stored in 32-byte entry groups)
-    "kmeans": {"file": "kmeans.hip", "bytes": 146787426,
-               "source": "95677d42d858d4619795cb5ed38f6f76aab63f86eb15388f06b026b39355abe0"},
+    "kmeans": {"file": "kmeans.hip", "bytes": 146786934,
+               "source": "ec01a774a80e29f06308a52e4004bd887d9e4bb55e86ac331c1d0a6e1e7d5517"},
     # k_seg_broadcast (row-span path): 2.66 MB fetched (offsets, gradients) + 128.71 MB written
-    "seg_broadcast": {"file": "segmented.hip", "bytes": 131368857,
-                      "source": "a8bece18ab4e27185c0dc7f3fd5dd1e17669a291e87375a06719fcbf9360ccc5"},
+    "seg_broadcast": {"file": "segmented.hip", "bytes": 131377964,
+                      "source": "a3c56bd4f33368dfc7fbafe501633bb8c18c298201b3dc913b0477a524f48603"},
 }
 
 
@@ -639,11 +639,12 @@ def bench_dot(args):
 
 
 # ============================================================ N-body loop
-# VALU instructions per pair interaction in the inner loop of the fused forward
-# pair kernel (gfx950 ISA of k_pairs<STEP>): 3 sub, 3 mul/fma for |d|^2 plus
-# eps2, 2 mul for the cube, 1 mul by the mass, 3 fma into the sums = 12, plus
-# the v_rsq_f32 on the transcendental unit.
-NBODY_VALU_PER_PAIR = 12
+# VALU instructions per pair interaction of the fused forward pair kernel (gfx950
+# ISA of k_pairs_sym<STEP>): every unordered pair is evaluated once for both of
+# its sides, 235 instructions per 16 pairs of a lane (subtract, multiply and FMA,
+# 21 of them for the sums over the lanes) beside 16 v_rsq_f32 on the
+# transcendental unit, so 235 / 32 per interaction.
+NBODY_VALU_PER_PAIR = 235 / 32
 # The ALU peak in lane operations per second: the chip's FP32 vector peak,
 # 157.3 TFLOP/s = 256 CUs x 4 SIMDs x 32 FMA lanes per clock x 2 flops x
 # 2.4 GHz, counts 32 lane operations per clock per SIMD.  (Sixteen, the width
@@ -729,7 +730,7 @@ def bench_nbody(args):
     log(f"nbody: plain fwd {pms:.3f} ms")
 
     pairs_fwd = T * n * n
-    pairs_bwd = (T - T // K) * n * n + T * n * n  # recomputed steps + adjoint steps
+    pairs_bwd = (T // K - 1) * (K - 1) * n * n + T * n * n  # recomputed steps (none in the last segment) + adjoint steps
     peak = nbody_peak_pairs_per_s(NBODY_VALU_PER_PAIR)
     ach = n * n / (parts["step"] * 1e-3)
     line = {
@@ -739,12 +740,12 @@ def bench_nbody(args):
         "config": {"workload": "loop around pairwise map(reduce): N-body N=16384, 20 Euler steps, dt=1e-4, "
                                "eps=1e-3, fwd + adjoint of final KE wrt x0 with checkpoints every 5 steps",
                    "n": n, "steps": T, "ckpt_every": K},
-        "roofline": {"bound": "alu", "kernel": "k_pairs<STEP> (+ slice finish)",
+        "roofline": {"bound": "alu", "kernel": "k_pairs_sym<STEP> (+ finish)",
                      "achieved": round(ach / 1e9, 1), "peak": round(peak / 1e9, 1), "unit": "Gpair/s",
                      "frac": round(ach / peak, 4), "traffic": None,
                      "peak_basis": f"FP32 vector peak as lane operations (256 CU x 4 SIMD x 32 lanes x 2.4 GHz) / "
-                                   f"{NBODY_VALU_PER_PAIR} VALU instructions per pair (reciprocal square root on "
-                                   "the transcendental unit)"},
+                                   f"{NBODY_VALU_PER_PAIR:.2f} VALU instructions per pair, half of what an unordered pair "
+                                   "takes (reciprocal square root on the transcendental unit)"},
         "parts": {"fwd_20_steps_ms": round(ms_fwd, 3), "reverse_ms": round(ms - ms_fwd, 3),
                   "step_launch_us": round(parts["step"] * 1e3, 1),
                   "adjoint_step_launch_us": round(parts["adjoint_step"] * 1e3, 1)},
@@ -906,7 +907,7 @@ def bench_batched(args):
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": "batched uneven: 2048 dot/matvec expressions, sizes log-uniform 1e2..1e6, "
-                               "forward + backward, autotuned persistent launches in a HIP graph",
+                               "forward + backward, autotuned launches in a HIP graph",
                    "tasks": 2048, "elements": elems, "tile_elems": chosen[0], "blocks_per_cu": chosen[1]},
         "roofline": {"bound": "hbm", "kernel": "k_batch_bwd (+ combine)", "achieved": round(ach, 1),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None},
@@ -1039,10 +1040,10 @@ def bench_expr(args):
 
 
 # ============================================================ Parboil-shaped kernels
-# VALU instructions per (voxel, sample) pair in the inner loop of k_mriq
-# (gfx950 ISA: 73 per four samples for the thread's two voxels, of which 16
-# are v_sin / v_cos on the transcendental unit).
-MRIQ_VALU_PER_PAIR = 9.125
+# VALU instructions per (voxel, sample) pair in the inner loop of k_mriq<4,4>
+# (gfx950 ISA: 113 per four samples for the thread's four voxels, of which 32
+# are v_sin / v_cos on the transcendental unit, which issue in 8 cycles each).
+MRIQ_VALU_PER_PAIR = 7.0625
 # VALU instructions per pair in the inner loop of k_tpacf<32> (gfx950 ISA:
 # 89 per four pairs: the dot product, a five-level binary search over the
 # edges, two levels from registers and three LDS probes, and the counter

@@ -309,12 +309,13 @@ __global__ void __launch_bounds__(NT) k_pairs_direct(PairArgs p) {
 // Every unordered pair once.  The two bodies of a pair share the distance, its
 // inverse square root and, in the adjoint, the whole term (d and m_k abar_j -
 // m_j abar_k both change sign with the roles, so body j receives exactly the
-// negative of body k's): 20 VALU instructions and one v_rsq_f32 for the two
+// negative of body k's): 15 VALU instructions and one v_rsq_f32 for the two
 // sides of the forward, 35 for the adjoint, against 2 x 12 and 2 x 29.
-// What a pair saves is the dear part: v_rsq_f32 issues in 8 cycles per wave
-// and a square (an FMA reading one register twice) in 4, against 2 for an FMA,
-// multiply or add of distinct VGPRs (measured, two waves per SIMD or more;
-// any scalar operand makes it 4, so bodies i are read into vector registers).
+// What a pair saves is the dear part: v_rsq_f32 issues in 8 cycles per wave,
+// and an FMA whose three source registers are all even or all odd (two banks)
+// in 4, against 2 for other FMAs, multiplies and adds of VGPRs (measured, two
+// waves per SIMD or more; any scalar operand makes it 4, so bodies i are read
+// into vector registers).
 //
 // The bodies are cut into sets of 256.  A wave holds the 256 bodies j of one
 // set, four per lane, with their sums; the bodies i of the sets before it come
