@@ -434,11 +434,15 @@ __global__ void __launch_bounds__(NT, 4) k_pairs_sym(PairArgs p) {
 }
 
 // Adds the partials of 64 bodies: the j sides of their set's blocks in block
-// order, then the i sides of the sets after it in set order; each of the four
-// waves a quarter of them, the quarters in order; then the update.
+// order, then the i sides of the sets after it in set order; each of the
+// block's waves an equal part of them, the parts in order; then the update.
+// Bound by the latency of its partials: with sixteen waves instead of four a
+// step of 5000 bodies takes 16.6 us instead of 17.1 us, of 8192 27.7 us instead
+// of 28.7 us, of 16 384 69.4 us instead of 70.1 us.
+constexpr int kSymFinish = 1024;
 template <int MODE>
-__global__ void __launch_bounds__(NT) k_pairs_sym_finish(PairArgs p) {
-    constexpr int NW = NT / kWave;
+__global__ void __launch_bounds__(kSymFinish) k_pairs_sym_finish(PairArgs p) {
+    constexpr int NW = kSymFinish / kWave;
     __shared__ float red[NW][3][kWave];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int64_t i = (int64_t)blockIdx.x * kWave + lane;
@@ -607,7 +611,7 @@ mx_status launch_pairs(PairArgs p, void *ws, hipStream_t s) {
         p.sets = sym_sets(p.n);
         p.blocks = sym_blocks(p.n);
         hipLaunchKernelGGL((k_pairs_sym<MODE>), dim3((unsigned)p.blocks), dim3(NT), 0, s, p);
-        hipLaunchKernelGGL((k_pairs_sym_finish<MODE>), dim3((unsigned)ceil_div(p.n, kWave)), dim3(NT), 0, s, p);
+        hipLaunchKernelGGL((k_pairs_sym_finish<MODE>), dim3((unsigned)ceil_div(p.n, kWave)), dim3(kSymFinish), 0, s, p);
         return last_launch("nbody pair kernel");
     case SLICED: break;
     }
