@@ -561,7 +561,7 @@ mx_status mx_kmeans_sse_grad_f32(const float *X_dev, int64_t n, int d, const flo
                                  hipStream_t stream);
 
 /* ======================================================================= */
-/* Batches of uneven independent expressions in one persistent launch       */
+/* Batches of uneven independent expressions in one launch                  */
 /* ======================================================================= */
 /* The paper observes that acceleration pays off when work is concentrated in
  * few `accelerate` uses and that small problems leave the GPU idle (Section

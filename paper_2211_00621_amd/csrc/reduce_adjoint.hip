@@ -20,8 +20,6 @@ constexpr int NT = 256;
 constexpr int kMaxArgBlocks = 2048;  // partial pairs fit MX_WS_REDUCE's 32 KiB
 constexpr int64_t kNone = INT64_MAX;
 
-inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
-
 // (v, i) improves on (bv, bi): strictly better value, or the same value at a
 // lower index
 template <int OP>
@@ -68,31 +66,43 @@ template <int OP> __device__ __forceinline__ void block_argreduce(float &bv, int
     __syncthreads();
 }
 
-// Partial pass: every thread scans a grid-strided set of elements (16-byte
-// vectors when x and gx are aligned) for its best pair and writes zeros to
-// gx on the way; one pair per block.
+// Partial pass: a block scans contiguous chunks of C x 256 16-byte vectors of any
+// alignment, all loads of a chunk in flight, for its threads' best pairs and
+// writes zeros to gx on the way; one pair per block.  Bound by HBM: 2^26 elements
+// (537 MB in and out) 99 us with the finish (5.4 TB/s), 111 us with one vector
+// in flight and a grid-wide stride; 2^22 9.5 us, 11.3 us.
+constexpr int C = 4;
 template <int OP>
 __global__ void __launch_bounds__(NT) k_arg_partial(const float *__restrict__ x, int64_t n, float *__restrict__ gx,
-                                                    float *__restrict__ pv, int64_t *__restrict__ pi, int vec) {
-    const int64_t tid = (int64_t)blockIdx.x * NT + threadIdx.x, nt = (int64_t)gridDim.x * NT;
+                                                    float *__restrict__ pv, int64_t *__restrict__ pi) {
     float bv = ident<OP>();
     int64_t bi = kNone;
-    int64_t done = 0;
-    if (vec) {
-        const int64_t nv = n / 4;
-        const float4 *xv = reinterpret_cast<const float4 *>(x);
-        float4 *gv = reinterpret_cast<float4 *>(gx);
-        for (int64_t j = tid; j < nv; j += nt) {
-            const float4 q = xv[j];
-            take<OP>(q.x, 4 * j, bv, bi);
-            take<OP>(q.y, 4 * j + 1, bv, bi);
-            take<OP>(q.z, 4 * j + 2, bv, bi);
-            take<OP>(q.w, 4 * j + 3, bv, bi);
-            gv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    const uvec<float> zero = {0.f, 0.f, 0.f, 0.f};
+    const int64_t nv = n / 4;
+    auto scan = [&](const uvec<float> &q, int64_t j) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) take<OP>(q[e], 4 * j + e, bv, bi);
+    };
+    for (int64_t c = (int64_t)blockIdx.x * (C * NT); c < nv; c += (int64_t)gridDim.x * (C * NT)) {
+        const int64_t j = c + threadIdx.x;
+        if (c + C * NT <= nv) {
+            uvec<float> q[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u) q[u] = load16<false>(x + 4 * (j + u * NT));
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                scan(q[u], j + u * NT);
+                store16(zero, gx + 4 * (j + u * NT));
+            }
+        } else {
+            for (int64_t i = j; i < nv; i += NT) {
+                scan(load16<false>(x + 4 * i), i);
+                store16(zero, gx + 4 * i);
+            }
         }
-        done = nv * 4;
     }
-    for (int64_t i = done + tid; i < n; i += nt) {
+    const int64_t i = 4 * nv + threadIdx.x;  // the last n % 4 elements
+    if (blockIdx.x == gridDim.x - 1 && i < n) {
         take<OP>(x[i], i, bv, bi);
         gx[i] = 0.f;
     }
@@ -218,9 +228,7 @@ mx_status mx_reduce_adjoint_f32(mx_redop op, const float *x_dev, int64_t n, cons
     const size_t need = mx_workspace_bytes(MX_WS_REDUCE, n, 0);
     MX_REQUIRE(ws && ws_bytes >= need && ((uintptr_t)ws & 255) == 0, MX_ERR_WORKSPACE,
                "%s: workspace needs %zu bytes, 256-byte aligned", who, need);
-    const int vec = aligned16(x_dev) && aligned16(gx_dev);
-    const int64_t items = vec ? n / 4 : n;
-    int64_t grid = ceil_div(items > 0 ? items : 1, (int64_t)NT * 4);
+    int64_t grid = ceil_div(n, (int64_t)4 * C * NT);
     int64_t cap = (int64_t)d->num_cus * 8;
     if (cap > kMaxArgBlocks) cap = kMaxArgBlocks;
     if (grid > cap) grid = cap;
@@ -228,10 +236,10 @@ mx_status mx_reduce_adjoint_f32(mx_redop op, const float *x_dev, int64_t n, cons
     int64_t *pi = (int64_t *)((char *)ws + kCounterBytes + kMaxArgBlocks * sizeof(float));
     const float ne = *ne_host;
     if (op == MX_MIN) {
-        hipLaunchKernelGGL(k_arg_partial<MX_MIN>, dim3((unsigned)grid), dim3(NT), 0, stream, x_dev, n, gx_dev, pv, pi, vec);
+        hipLaunchKernelGGL(k_arg_partial<MX_MIN>, dim3((unsigned)grid), dim3(NT), 0, stream, x_dev, n, gx_dev, pv, pi);
         hipLaunchKernelGGL(k_arg_finish<MX_MIN>, dim3(1), dim3(NT), 0, stream, pv, pi, (int)grid, ne, gout_dev, gx_dev);
     } else {
-        hipLaunchKernelGGL(k_arg_partial<MX_MAX>, dim3((unsigned)grid), dim3(NT), 0, stream, x_dev, n, gx_dev, pv, pi, vec);
+        hipLaunchKernelGGL(k_arg_partial<MX_MAX>, dim3((unsigned)grid), dim3(NT), 0, stream, x_dev, n, gx_dev, pv, pi);
         hipLaunchKernelGGL(k_arg_finish<MX_MAX>, dim3(1), dim3(NT), 0, stream, pv, pi, (int)grid, ne, gout_dev, gx_dev);
     }
     return last_launch(who);
