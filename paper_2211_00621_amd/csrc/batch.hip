@@ -210,6 +210,10 @@ __device__ __forceinline__ void matvec_adj_tile(const float *__restrict__ a, con
                                                 const float *__restrict__ g, float *__restrict__ ga, int64_t c,
                                                 unsigned rows, float *__restrict__ dst, float4 *red) {
     constexpr int U = kAdjRows;
+    if (rows == 0) {  // no range to describe: the sums over no rows
+        for (int64_t j = threadIdx.x; j < c; j += NB) dst[j] = 0.f;
+        return;
+    }
     if (c < 4) {  // one thread per row, element by element
         f4u s = {0.f, 0.f, 0.f, 0.f};
         for (int64_t r = threadIdx.x; r < rows; r += NB) {

@@ -75,3 +75,13 @@ def test_past_the_cache():
     """A table whose operands lie further apart than the memory-side cache."""
     say("batch past the cache")
     check([(1, 40, 1001), (1, 100, 64), (0, 1, 100003), (1, 5, 3)], None, 1, a0=34 << 20)
+
+
+@pytest.mark.parametrize("gap", [0, 1])
+def test_no_rows(gap):
+    """A matvec of no rows, of one pass over the columns to many: gx is zero and nothing else is written, whatever lies
+    behind it in the pools."""
+    say("batch no rows", gap)
+    cols = [0, 3, 4, 7, 2047, 2048, 2049, 2052, 4096, 4099, (1 << 22) + 3]
+    tasks = [t for c in cols for t in ((1, 0, c), (1, 9, 2049))] + [(0, 1, 9000)]
+    check(tasks, None, gap)
