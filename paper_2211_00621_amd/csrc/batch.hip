@@ -36,6 +36,7 @@ constexpr int NT = 256;
 constexpr int kDot = 0, kMatvec = 1;
 constexpr int kMinTile = 4096;
 constexpr int kXLds = 2048;  // matvec x staged in LDS up to this many columns
+constexpr int kXTail = 508;  // floats of zeros between x's whole vectors and its last elements there
 constexpr int NB = 512;      // threads of a backward block
 constexpr int kBwdVec = 2;   // 16-byte vectors per operand and thread of a dot's backward tile
 constexpr int64_t kDotChunk = 4 * kBwdVec * NB;  // elements of a dot's backward tile
@@ -116,11 +117,15 @@ __device__ __forceinline__ float block_dot(const float *__restrict__ a, const fl
 
 // The rows of a matvec tile of c <= kXLds columns: 16 lanes per row, R rows
 // per group of lanes and 8 / R vectors per row and lane in flight (R: as many
-// rows as eight vectors per lane cover).  x in LDS, with zeros past its end.
+// rows as eight vectors per lane cover).  x in LDS: its whole vectors, zeros for
+// the lanes past them (up to 16 (K - 1) vectors, whose elements of A read as
+// zeros, so an infinite element of x must not meet them), then the last c % 4
+// elements.
 template <int R>
 __device__ __forceinline__ void matvec_rows(const float *__restrict__ A, const float *x, float *__restrict__ out,
                                             unsigned c, int64_t n) {
     constexpr int K = 8 / R, G = NT / 16;
+    static_assert(4 * 16 * (K - 1) <= kXTail, "zeros for every lane past the row's vectors");
     const unsigned grp = threadIdx.x >> 4, l = threadIdx.x & 15, nv = c >> 2;
     const unsigned row = 4u * grp * c;  // byte offset of this group's first row
     for (int64_t r0 = 0; r0 < n; r0 += G * R) {
@@ -145,7 +150,7 @@ __device__ __forceinline__ void matvec_rows(const float *__restrict__ A, const f
             }
         }
         if (4 * nv + l < c) {
-            const float xv = x[4 * nv + l];
+            const float xv = x[4 * nv + kXTail + l];
 #pragma unroll
             for (int q = 0; q < R; ++q) ac[q][1] += bld1(a, row + 4 * (4 * nv + l) + 4u * q * G * c) * xv;
         }
@@ -165,7 +170,7 @@ __global__ void __launch_bounds__(NT, 8) k_batch_fwd(const TileDev *__restrict__
                                                   const float *__restrict__ A, const float *__restrict__ B,
                                                   float *__restrict__ out, float *__restrict__ part) {
     __shared__ float red[NT / kWave];
-    __shared__ __attribute__((aligned(16))) float xs[kXLds + 512];
+    __shared__ __attribute__((aligned(16))) float xs[kXLds + kXTail + 4];
     using R = Red<MX_ADD, float>;
     const int64_t t = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     if (t >= ntiles) return;
@@ -177,7 +182,9 @@ __global__ void __launch_bounds__(NT, 8) k_batch_fwd(const TileDev *__restrict__
         if (threadIdx.x == 0) *(tk.part >= 0 ? part + tk.part : o) = acc;
     } else if (tk.cols <= kXLds) {
         const unsigned c = (unsigned)tk.cols;
-        for (unsigned q = threadIdx.x; q < c + 512; q += NT) xs[q] = q < c ? b[q] : 0.f;
+        const unsigned c4 = c & ~3u;
+        for (unsigned q = threadIdx.x; q < c + kXTail; q += NT)
+            xs[q] = q < c4 ? b[q] : q < c4 + kXTail ? 0.f : b[q - kXTail];
         __syncthreads();
         if (c > 256) matvec_rows<1>(a, xs, o, c, tk.count);
         else if (c > 128) matvec_rows<2>(a, xs, o, c, tk.count);
@@ -631,7 +638,7 @@ unsigned lds_of(const mx_batch_plan *p, unsigned own) {
 
 mx_status fwd_impl(const mx_batch_plan *p, const float *A, const float *B, float *out, void *ws, hipStream_t s) {
     float *part = fwd_part_ptr(p, ws);
-    hipLaunchKernelGGL(k_batch_fwd, grid_of(p->n_fwd), dim3(NT), lds_of(p, 4 * (kXLds + 512 + 16)), s, p->d_fwd, p->n_fwd, A, B, out, part);
+    hipLaunchKernelGGL(k_batch_fwd, grid_of(p->n_fwd), dim3(NT), lds_of(p, 4 * (kXLds + kXTail + 4 + 16)), s, p->d_fwd, p->n_fwd, A, B, out, part);
     if (p->n_fwd_list > 0)
         hipLaunchKernelGGL(k_batch_combine_fwd, dim3((unsigned)ceil_div(p->n_fwd_list, NT)), dim3(NT), 0, s,
                            p->d_tasks, p->d_fwd_list, p->n_fwd_list, part, out);

@@ -85,3 +85,24 @@ def test_no_rows(gap):
     cols = [0, 3, 4, 7, 2047, 2048, 2049, 2052, 4096, 4099, (1 << 22) + 3]
     tasks = [t for c in cols for t in ((1, 0, c), (1, 9, 2049))] + [(0, 1, 9000)]
     check(tasks, None, gap)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_non_finite_x(value):
+    """A non-finite element of x reaches each row by one product, whichever element it is: the lanes past a row's end
+    add nothing."""
+    say("batch non-finite x", value)
+    cols = [1, 2, 3, 5, 6, 7, 63, 65, 66, 67, 127, 129, 130, 131, 191, 255, 257, 259, 301, 514, 1001, 2045, 2046, 2047,
+            2049, 4099]
+    tasks = [(1, 21, c) for c in cols for _ in range(3)] + [(0, 1, c) for c in cols]
+    tb, na, nb, no = layout(tasks, 0)
+    A, B = (np.random.default_rng(5).uniform(0.5, 1.0, n).astype(np.float32) for n in (na, nb))
+    A *= np.random.default_rng(6).choice([-1, 1], na).astype(np.float32)
+    for i, (_, _, c, _, b, _) in enumerate(tb):
+        B[b + (c - 1, 0, c // 2)[i % 3]] = value
+    out = torch.empty(no, device="cuda")
+    api.Batch(tb).forward(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), out)
+    h = out.cpu().numpy()
+    for _, rows, c, a, b, o in tb:
+        ref = (A[a:a + rows * c].reshape(rows, c).astype(np.float64) * B[b:b + c]).sum(1)
+        assert np.array_equal(h[o:o + rows], ref.astype(np.float32), equal_nan=True), (rows, c)
