@@ -26,6 +26,7 @@
 //    interleaved rows R*rho + c of the wave's tile (rho = 0..15), which the
 //    epilogue maps back; for C's columns this makes each lane's R outputs
 //    contiguous, so they are stored as one vector.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -110,8 +111,12 @@ template <int R> __device__ __forceinline__ void lds_read(float (&v)[R], const f
 // 8), so blocks b, b+8, b+16, ... share an L2.  Give each XCD a contiguous
 // range of logical tiles, and walk logical tiles in groups of kGroupM tile rows
 // so that neighbouring tiles reuse the same A row panels and B column panels.
-__device__ __forceinline__ void tile_of(int b, int tiles_m, int tiles_n, int &tm, int &tn) {
-    const int nt = tiles_m * tiles_n;
+// Blocks come in rows of 2^20 (a grid's threads in x stay below 2^32); false
+// for the surplus ones of the last row.
+constexpr int kGridRowBits = 20;
+__device__ __forceinline__ bool tile_of(int tiles_m, int tiles_n, int &tm, int &tn) {
+    const int nt = tiles_m * tiles_n, b = (int)(blockIdx.y << kGridRowBits | blockIdx.x);
+    if (b >= nt) return false;
     // XCD x takes nt / 8 tiles, one more where x < nt % 8
     const int x = b & 7, rem = nt & 7;
     const int L = x * (nt >> 3) + (x < rem ? x : rem) + (b >> 3);
@@ -122,6 +127,7 @@ __device__ __forceinline__ void tile_of(int b, int tiles_m, int tiles_n, int &tm
     const int in = L - gi * per_group;
     tm = first_m + in % gm;
     tn = in / gm;
+    return true;
 }
 
 // The wave's operand fragments of one K slice held in LDS: fa[s][i] is the
@@ -194,7 +200,7 @@ __global__ void __launch_bounds__(64 * WM * WN) k_gemm_mfma(const float *__restr
     auto Bs = [&](int i) { return i ? Bs1 : Bs0; };
 
     int tm, tn;
-    tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    if (!tile_of(tiles_m, tiles_n, tm, tn)) return;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -389,7 +395,7 @@ __global__ void __launch_bounds__(64 * KS) k_gemm_direct(const float *__restrict
     constexpr bool RA = !TA, RB = TB;
     __shared__ float4 red[KS * MI * NI * 64];
     int tm, tn;
-    tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    if (!tile_of(tiles_m, tiles_n, tm, tn)) return;
     const int lane = threadIdx.x & 63;
     const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, g = lane >> 4;
@@ -578,7 +584,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KG) k_gemm_split(const float *_
     constexpr int LDSF = 2 * KG * BUF > SUM ? 2 * KG * BUF : SUM;
     __shared__ __attribute__((aligned(16))) float lds[LDSF];
     int tm, tn;
-    tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    if (!tile_of(tiles_m, tiles_n, tm, tn)) return;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -720,7 +726,8 @@ struct GemmArgs {
 #define MX_GEMM_LAUNCH(BM, BN, THREADS, KERNEL, ...)                                                              \
     const int64_t tiles_m = ceil_div(a.M, BM), tiles_n = ceil_div(a.N, BN);                                       \
     MX_REQUIRE(tiles_m * tiles_n < (1LL << 31), MX_ERR_SHAPE, "mx_map_map_reduce_f32: too many tiles");           \
-    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(THREADS);                                               \
+    const int64_t tiles = tiles_m * tiles_n, per_row = 1 << kGridRowBits;                                         \
+    const dim3 grid((unsigned)std::min(tiles, per_row), (unsigned)ceil_div(tiles, per_row)), block(THREADS);      \
     auto go = [&](auto kernel) {                                                                                  \
         hipLaunchKernelGGL(kernel, grid, block, 0, a.s, a.A, a.B, a.C, a.M, a.N, a.K, (int)tiles_m, (int)tiles_n __VA_ARGS__); \
     };                                                                                                            \

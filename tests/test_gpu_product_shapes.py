@@ -75,3 +75,31 @@ def test_special_values_stay_in_their_rows_and_columns():
         want = np.zeros((M, N), dtype=bool)
         want[3], want[:, 7] = True, True
         assert np.array_equal(bad, want)
+
+
+def test_more_threads_than_a_grid_row_holds():
+    """A column of 2^27 elements and more: as many tiles of a few rows as that is are still one launch."""
+    n = (1 << 27) + 37
+    say("product long column", n)
+    x = torch.rand(n, 1, device="cuda") * 2 - 1
+    b = torch.tensor([[1.5]], device="cuda")
+    for ta in (0, 1):
+        C = torch.full((n, 1), 7.0, device="cuda")
+        abi.mx_map_map_reduce_f32(ta, 0, x.view(1, n) if ta else x, b, C)
+        assert torch.equal(C, x * 1.5)
+
+
+def test_more_tiles_than_a_grid_row(monkeypatch):
+    """1025 x 1025 tiles of 16 x 16: 2^20 blocks and 2049 in the second row of the grid."""
+    M = N = 16400
+    K = 300
+    say("product two grid rows", M, N, K)
+    monkeypatch.setenv("MX_GEMM_TILE", "16x16")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    A, B = (torch.rand(M, K, device="cuda", generator=g) * 2 - 1 for _ in range(2))
+    C = torch.full((M, N), 7.0, device="cuda")
+    abi.mx_map_map_reduce_f32(0, 1, A, B, C)
+    for r in range(0, M, 4100):
+        a, b = A[r:r + 4100].double(), B.t().contiguous().double()
+        err = (C[r:r + 4100].double() - a @ b).abs()
+        assert bool((err <= (K + 2) * 2.0 ** -24 * (a.abs() @ b.abs())).all())
