@@ -448,7 +448,9 @@ mx_status mx_map_map_reduce_plain_f32(int ta, int tb, int64_t M, int64_t N, int6
  * Forward Euler: x_{t+1} = x_t + dt v_t, v_{t+1} = v_t + dt a(x_t).
  * The pair sums have a bracketing fixed by n alone, so results are
  * deterministic and independent of the device.
- * Pair entry points need a workspace of mx_nbody_pair_workspace_bytes(n). */
+ * Pair entry points need a workspace of mx_nbody_pair_workspace_bytes(n):
+ * about n^2 / 32 bytes up to 65 536 bodies (139 MB there), under 17 MB beyond.
+ * An output may be one of the inputs where a call does not forbid it. */
 size_t mx_nbody_pair_workspace_bytes(int64_t n);
 
 /* acc4[i] = (a_i, 0).  Errors: MX_ERR_INVALID, MX_ERR_SHAPE, MX_ERR_WORKSPACE. */

@@ -590,17 +590,21 @@ size_t pair_ws_bytes(int64_t n) {
     return kCounterBytes + (sl > 1 ? align256((size_t)sl * (size_t)n * 16) : 0);
 }
 
-// output written over an input (the acceleration and its transposed Jacobian
-// allow it): the direct schedule, whose waves still read what others write,
-// leaves such a call to the symmetric one
-bool overlaps(const float4 *out, const float4 *in, int64_t n) { return in && out < in + n && in < out + n; }
+// An output written over the positions or what the pair sums read of the
+// adjoint: the direct schedule, whose waves still read what others write, leaves
+// such a call to the symmetric one, which writes when every sum is done.
+bool overlaps(const float4 *out, const float4 *in, int64_t n) { return out && in && out < in + n && in < out + n; }
+bool in_place(const PairArgs &p) {
+    return overlaps(p.out0, p.pos, p.n) || overlaps(p.out0, p.aux, p.n) || overlaps(p.out1, p.pos, p.n) ||
+           overlaps(p.out1, p.aux, p.n);
+}
 
 template <int MODE>
 mx_status launch_pairs(PairArgs p, void *ws, hipStream_t s) {
     const int64_t tiles = ceil_div(p.n, NT);
     MX_REQUIRE(tiles < (1LL << 31), MX_ERR_SHAPE, "nbody: too many bodies");
     p.partial = (float4 *)((char *)ws + kCounterBytes);
-    switch (pair_path(p.n, overlaps(p.out0, p.pos, p.n) || overlaps(p.out0, p.aux, p.n))) {
+    switch (pair_path(p.n, in_place(p))) {
     case DIRECT:
         if (p.n <= 1024)
             hipLaunchKernelGGL((k_pairs_direct<MODE, 4>), dim3((unsigned)ceil_div(p.n, 4)), dim3(NT), 0, s, p);

@@ -95,3 +95,31 @@ def test_reverse_sweep_twice_from_one_forward(steps, ckpt):
         hx, hv = torch.full_like(p4, 7.0), torch.full_like(p4, 7.0)
         abi.mx_nbody_ke_vjp_f32(p4, v, EPS2, G, DT, steps, ckpt, None, hx, hv, ws)
         assert torch.equal(hx, gx) and torch.equal(hv, gv)
+
+
+@pytest.mark.parametrize("n", [200, 1000, 4096])
+@pytest.mark.parametrize("over", ["pos4", "vel4"])
+def test_gradients_over_the_state(n, over):
+    """A gradient of the loop, or the velocities' adjoint of a step, written over the state that the sweep reads."""
+    say("nbody gradients over the state", n, over)
+    pos, m, vel = W.nbody(n, seed=n)
+    p4, v = torch.from_numpy(to4(pos, m)).to("cuda"), torch.from_numpy(v4(vel)).to("cuda")
+    eps2, steps, ckpt = 0.05 ** 2, 3, 2
+    ke, gx, gv = api.nbody_ke_grad(p4, v, eps2, G, DT, steps, ckpt)
+    ws = torch.zeros(abi.mx_nbody_workspace_bytes(n, steps, ckpt), dtype=torch.uint8, device="cuda")
+    S = float(torch.cat([gx, gv]).abs().max())
+    for which in ("gx4", "gv4"):
+        s = {"pos4": p4.clone(), "vel4": v.clone(), "other": torch.empty_like(p4)}
+        gx2, gv2 = (s[over], s["other"]) if which == "gx4" else (s["other"], s[over])
+        ke2 = torch.empty((), device="cuda")
+        abi.mx_nbody_ke_grad_f32(s["pos4"], s["vel4"], eps2, G, DT, steps, ckpt, ke2, gx2, gv2, ws)
+        # the schedules' sums differ by their rounding alone
+        assert torch.equal(ke2, ke)
+        assert float((gx2 - gx).abs().max()) <= 1e-4 * S and float((gv2 - gv).abs().max()) <= 1e-4 * S, which
+    xb, vb, wp = torch.randn_like(p4), torch.randn_like(p4), torch.zeros(
+        abi.mx_nbody_pair_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    xo, vo, x2, p2 = torch.empty_like(p4), torch.empty_like(p4), torch.empty_like(p4), p4.clone()
+    abi.mx_nbody_adjoint_step_f32(p4, xb, vb, eps2, G, DT, xo, vo, wp)
+    abi.mx_nbody_adjoint_step_f32(p2, xb, vb, eps2, G, DT, x2, p2, wp)
+    assert torch.equal(p2, vo)
+    assert float((x2 - xo).abs().max()) <= 1e-4 * float((xo - xb).abs().max())
