@@ -721,6 +721,7 @@ struct GemmArgs {
     const float *A, *B;
     float *C;
     hipStream_t s;
+    int64_t num_cus;
 };
 
 #define MX_GEMM_LAUNCH(BM, BN, THREADS, KERNEL, ...)                                                              \
@@ -748,7 +749,14 @@ template <int MI, int NI, int WM, int WN, int KG> mx_status launch_split(const G
     MX_GEMM_LAUNCH(16 * MI * WM, 16 * NI * WN, 64 * WM * WN * KG, k_gemm_split);
 #undef SHAPE
 }
+// Past three rounds of blocks no wave without a slice of K: 10^6 x 1 x 32 took
+// 167 us with eight waves a tile, 63 us with one.  Before, the idle waves cost
+// nothing, and their instruction fetches serve the one that works (1000 x 8 x 64
+// 2.6 us with eight, 3.3 us with two).
 template <int MI, int NI, int KS> mx_status launch_direct(const GemmArgs &a) {
+    if constexpr (KS > 1)
+        if (a.K <= KS / 2 * BK && ceil_div(a.M, 16 * MI) * ceil_div(a.N, 16 * NI) > 3 * a.num_cus)
+            return launch_direct<MI, NI, KS / 2>(a);
 #define SHAPE MI, NI, KS
     MX_GEMM_LAUNCH(16 * MI, 16 * NI, 64 * KS, k_gemm_direct);
 #undef SHAPE
@@ -764,17 +772,25 @@ template <int MI, int NI, int KS> mx_status launch_direct(const GemmArgs &a) {
 // 39 us, the 136 of 128 x 64 38 us (and 60 us before, 128 x 64 tiles one slice
 // ahead).  The 16 x 16 tiles share a CU by several, so their rounds need not be
 // whole; the direct 32 x 32 tiles read too much memory past one round.
+//
+// Products of K <= 256, where no wave of a direct tile has two slices: past the
+// first rounds the fixed part becomes `more` a round, since the direct tiles,
+// of as many waves as K has slices, share a CU by up to 32, and the twelve waves
+// of 32 x 64 and 64 x 32 mostly wait (10^6 x 8 by 16 x 16, 32 x 32, 64 x 32 and 64 x 64
+// tiles, us: K = 8 74, 76, 157 and 103; K = 32 84, 79, 184 and 127; K = 256 237,
+// 315, 349 and 366; 1000 x 1000 x 64 9, 7, 8 and 6).
 struct GemmShape {
     const char *name;  // MX_GEMM_TILE in the environment forces a shape, for tuning and tests
     int bm, bn;
     double fixed, per_k;
     mx_status (*launch)(const GemmArgs &);
+    double first = 0., more = 0.;  // rounds at `fixed`, and the fixed part of those after them
 };
 const GemmShape kShapes[] = {
-    {"16x16", 16, 16, 0.95, 2.3, launch_direct<1, 1, 8>},
-    {"32x32", 32, 32, 1.4, 5.5, launch_direct<2, 2, 4>},
-    {"32x64", 32, 64, 1.5, 10.5, launch_split<2, 2, 1, 2, 6>},
-    {"64x32", 64, 32, 1.5, 10.5, launch_split<2, 2, 2, 1, 6>},
+    {"16x16", 16, 16, 0.95, 2.3, launch_direct<1, 1, 8>, 3., .3},
+    {"32x32", 32, 32, 1.4, 5.5, launch_direct<2, 2, 4>, 3., .45},
+    {"32x64", 32, 64, 1.5, 10.5, launch_split<2, 2, 1, 2, 6>, 1., 2.4},
+    {"64x32", 64, 32, 1.5, 10.5, launch_split<2, 2, 2, 1, 6>, 1., 2.4},
     {"64x64", 64, 64, 1.8, 19., launch_split<2, 2, 2, 2, 2>},
     {"80x64", 80, 64, 2.2, 23.5, launch_split<5, 1, 1, 4, 4>},
     {"64x80", 64, 80, 2.2, 24., launch_split<1, 5, 4, 1, 4>},
@@ -788,7 +804,7 @@ const GemmShape kShapes[] = {
 };
 constexpr int kNumShapes = sizeof kShapes / sizeof kShapes[0], kPipelined = kNumShapes - 1;
 
-const GemmShape &gemm_choice(const GemmArgs &a, const DeviceInfo *d) {
+const GemmShape &gemm_choice(const GemmArgs &a) {
     const int64_t lda = a.ta ? a.M : a.K, ldb = a.tb ? a.K : a.N;
     // the pipelined kernel takes whole tiles of aligned rows
     const bool whole = a.M % 128 == 0 && a.N % 128 == 0 && a.K % 64 == 0 && a.K >= 128 && lda % 4 == 0 &&
@@ -806,11 +822,13 @@ const GemmShape &gemm_choice(const GemmArgs &a, const DeviceInfo *d) {
         const GemmShape &s = kShapes[i];
         if (i == kPipelined && !whole) continue;
         const double tiles = (double)ceil_div(a.M, s.bm) * (double)ceil_div(a.N, s.bn);
-        double rounds = tiles / d->num_cus;
+        double rounds = tiles / (double)a.num_cus;
         if (rounds < 1.) rounds = 1.;
         else if (i > 0) rounds = ceil(rounds);
         const double per_k = i == 1 && rounds > 1. ? 9. : s.per_k;
-        const double us = rounds * (s.fixed + per_k * (double)a.K * 1e-3);
+        double fixed = s.fixed * rounds;
+        if (a.K <= 256 && s.more > 0. && rounds > s.first) fixed = s.fixed * s.first + s.more * (rounds - s.first);
+        const double us = fixed + rounds * per_k * (double)a.K * 1e-3;
         if (us < best_us) {
             best_us = us;
             best = i;
@@ -832,8 +850,8 @@ mx_status mx_map_map_reduce_f32(int ta, int tb, int64_t M, int64_t N, int64_t K,
     if (M == 0 || N == 0) return MX_OK;
     const DeviceInfo *d;
     if (mx_status st = device_info(&d)) return st;
-    const GemmArgs a{ta, tb, M, N, K, A_dev, B_dev, C_dev, stream};
-    return gemm_choice(a, d).launch(a);
+    const GemmArgs a{ta, tb, M, N, K, A_dev, B_dev, C_dev, stream, d->num_cus};
+    return gemm_choice(a).launch(a);
 }
 
 mx_status mx_map_map_reduce_plain_f32(int ta, int tb, int64_t M, int64_t N, int64_t K,

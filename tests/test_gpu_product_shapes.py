@@ -103,3 +103,19 @@ def test_more_tiles_than_a_grid_row(monkeypatch):
         a, b = A[r:r + 4100].double(), B.t().contiguous().double()
         err = (C[r:r + 4100].double() - a @ b).abs()
         assert bool((err <= (K + 2) * 2.0 ** -24 * (a.abs() @ b.abs())).all())
+
+
+@pytest.mark.parametrize("K", [0, 1, 31, 32, 33, 64, 65, 96, 128, 129, 160, 256, 257])
+def test_waves_by_slices(K, monkeypatch):
+    """Past three rounds of blocks the direct tiles take as many waves as K has slices, at most eight or four."""
+    M, N = 1300, 611  # 3198 and 820 tiles
+    for name in ("16x16", "32x32"):
+        monkeypatch.setenv("MX_GEMM_TILE", name)
+        for ta, tb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+            if K:
+                check(M, N, K, ta, tb, 1, name)
+            else:
+                C = torch.full((M, N), 7.0, device="cuda")
+                abi.mx_map_map_reduce_f32(ta, tb, torch.empty((0, M) if ta else (M, 0), device="cuda"),
+                                          torch.empty((N, 0) if tb else (0, N), device="cuda"), C)
+                assert not C.any()
