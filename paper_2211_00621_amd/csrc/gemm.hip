@@ -812,10 +812,14 @@ const GemmShape &gemm_choice(const GemmArgs &a) {
     // nothing to read, or rows so few that a vector of them could pass the end
     if (a.K == 0 || (a.ta && a.M < 4) || (!a.tb && a.N < 4)) return kShapes[0];
     // read on every call (a getenv is cheap next to a launch), so one process
-    // can run every shape
-    if (const char *e = getenv("MX_GEMM_TILE"))
-        for (int i = 0; i < kNumShapes; ++i)
-            if (!strcmp(e, kShapes[i].name) && (i != kPipelined || whole)) return kShapes[i];
+    // can run every shape; a number of waves ("128x64w8") that no kernel has for
+    // this product leaves the sides
+    if (const char *e = getenv("MX_GEMM_TILE")) {
+        if (!strcmp(e, kShapes[kPipelined].name) && whole) return kShapes[kPipelined];
+        const std::string sides(e, strcspn(e, "w"));
+        for (int i = 0; i < kPipelined; ++i)
+            if (sides == kShapes[i].name) return kShapes[i];
+    }
     int best = 0;
     double best_us = 1e300;
     for (int i = 0; i < kNumShapes; ++i) {

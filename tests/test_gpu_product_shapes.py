@@ -119,3 +119,22 @@ def test_waves_by_slices(K, monkeypatch):
                 abi.mx_map_map_reduce_f32(ta, tb, torch.empty((0, M) if ta else (M, 0), device="cuda"),
                                           torch.empty((N, 0) if tb else (0, N), device="cuda"), C)
                 assert not C.any()
+
+
+def test_forced_sides_without_their_number_of_waves(monkeypatch):
+    """A forced shape with a number of waves that no kernel has, or not for this product, is the shape of those sides."""
+    M, N, K = 300, 200, 1000
+    say("product forced sides")
+    A, B = (torch.rand(*s, device="cuda") * 2 - 1 for s in ((M, K), (K, N)))
+
+    def product(name):
+        monkeypatch.setenv("MX_GEMM_TILE", name)
+        C = torch.empty((M, N), device="cuda")
+        abi.mx_map_map_reduce_f32(0, 0, A, B, C)
+        return C
+
+    # the shapes add K in different orders
+    assert not torch.equal(product("128x64"), product("16x16")) and not torch.equal(product("128x128"), product("16x16"))
+    assert torch.equal(product("128x64w8"), product("128x64"))
+    for name in ("128x128w8", "128x128w8b", "128x128w16"):
+        assert torch.equal(product(name), product("128x128"))
