@@ -8,6 +8,7 @@ the call returns a non-zero status.  All computation happens in the library.
 from __future__ import annotations
 
 import ctypes
+import os
 
 import numpy as np
 import torch
@@ -50,6 +51,15 @@ def _check(status: int, name: str) -> None:
 
 
 _cuda_ready = False
+
+
+def _forked() -> None:
+    # the child has no runtime: torch says so where it is asked for a stream
+    global _cuda_ready
+    _cuda_ready = False
+
+
+os.register_at_fork(after_in_child=_forked)
 
 
 def _stream(stream) -> int:

@@ -158,3 +158,14 @@ def test_records_layout_on_the_host():
     recs["xs"]["len"][1] = 4                 # a positive length with null data
     with pytest.raises(abi.MxError):
         abi.mx_records_layout(recs, desc)
+
+
+def test_a_forked_child_asks_torch_for_its_stream(monkeypatch):
+    """The raw stream handle is for a process whose runtime is up; a child of it has none, and torch says so."""
+    from paper_2211_00621_amd import abi
+    monkeypatch.setattr(abi, "_cuda_ready", True)
+    pid = os.fork()
+    if pid == 0:
+        os._exit(1 if abi._cuda_ready else 0)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert abi._cuda_ready
