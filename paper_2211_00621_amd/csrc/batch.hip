@@ -628,11 +628,18 @@ dim3 grid_of(int64_t ntiles) {
     return ntiles <= kRow ? dim3((unsigned)std::max<int64_t>(ntiles, 1)) : dim3((unsigned)kRow, (unsigned)ceil_div(ntiles, kRow));
 }
 // LDS that a launch asks for so that no more than blocks_per_cu blocks are
-// resident on a CU (160 KB; the kernels' own arrays are `own`).  64 KB is the
-// most a launch can have: one block per CU is not reached, two are.
+// resident on a CU (the kernels' own arrays are `own`; eight blocks forward and
+// four backward are what its waves allow).
+constexpr unsigned kCuLds = 163840, kWaveBlocks = 8;
+constexpr unsigned lds_for_blocks(unsigned b) { return b >= kWaveBlocks ? 0u : kCuLds / (b + 1) + 1024u; }
+constexpr bool lds_holds_blocks() {
+    for (unsigned b = 1; b < kWaveBlocks; ++b)
+        if (kCuLds / lds_for_blocks(b) != b) return false;
+    return true;
+}
+static_assert(lds_holds_blocks(), "as many blocks as asked for fit a CU, and no more");
 unsigned lds_of(const mx_batch_plan *p, unsigned own) {
-    const unsigned b = (unsigned)p->cfg.blocks_per_cu;
-    const unsigned per = b >= 8 ? 0u : std::min(163840u / (b + 1) + 1024u, 65536u);
+    const unsigned per = lds_for_blocks((unsigned)p->cfg.blocks_per_cu);
     return per > own ? per - own : 0u;
 }
 
