@@ -617,7 +617,7 @@ mx_status mx_batch_forward_plain(const mx_batch_plan *plan, const float *A_dev, 
 mx_status mx_batch_backward_plain(const mx_batch_plan *plan, const float *A_dev, const float *B_dev,
                                   const float *gout_dev, float *gA_dev, float *gB_dev, hipStream_t stream);
 
-/* Picks tile_elems in {4096 .. 65536} and blocks_per_cu in {2, 4, 8, 16} by
+/* Picks tile_elems in {4096 .. 65536} and blocks_per_cu in {2, 4, 8} by
  * timing forward + backward on the given buffers (which it overwrites), and
  * sets it on the plan.  If cache_path (may be NULL) names a JSON-lines file
  * holding an entry for this task shape and device, that entry is used without

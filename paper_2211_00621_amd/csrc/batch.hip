@@ -444,7 +444,6 @@ using namespace mx;
 
 struct mx_batch_plan {
     int device = 0;
-    int num_cus = 256;
     std::vector<int64_t> table;  // [ntasks][6]
     int64_t ntasks = 0;
     int64_t a_len = 0, b_len = 0, out_len = 0;
@@ -726,7 +725,6 @@ mx_status mx_batch_plan_create(const int64_t *table_host, int64_t ntasks, const 
     if (mx_status st = device_info(&d)) return st;
     auto *p = new mx_batch_plan();
     p->device = d->device;
-    p->num_cus = d->num_cus;
     p->ntasks = ntasks;
     p->table.assign(table_host, table_host + 6 * ntasks);
     for (int64_t t = 0; t < ntasks; ++t) {
@@ -847,7 +845,7 @@ mx_status mx_batch_autotune(mx_batch_plan *plan, const float *A_dev, const float
         return MX_OK;
     }
     static const int tiles[] = {4096, 8192, 16384, 32768, 65536};
-    static const int bpcs[] = {2, 4, 8, 16};
+    static const int bpcs[] = {2, 4, 8};  // more than eight are the same launches
     hipEvent_t e0, e1;
     MX_TRY_HIP(hipEventCreate(&e0));
     MX_TRY_HIP(hipEventCreate(&e1));

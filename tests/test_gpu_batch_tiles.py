@@ -106,3 +106,12 @@ def test_non_finite_x(value):
     for _, rows, c, a, b, o in tb:
         ref = (A[a:a + rows * c].reshape(rows, c).astype(np.float64) * B[b:b + c]).sum(1)
         assert np.array_equal(h[o:o + rows], ref.astype(np.float32), equal_nan=True), (rows, c)
+
+
+def test_autotune_times_each_launch_once():
+    """More than eight blocks per CU are the launches of eight: the tuner does not choose between them."""
+    say("batch autotune candidates")
+    tb, na, nb, no = layout([(0, 1, 20000), (1, 100, 300)] * 20, 0)
+    A, B, gout, gA, gB, out = (torch.rand(n, device="cuda") for n in (na, nb, no, na, nb, no))
+    for _ in range(3):
+        assert api.Batch(tb).autotune(A, B, out, gout, gA, gB)[1] in (2, 4, 8)
