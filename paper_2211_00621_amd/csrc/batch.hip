@@ -14,7 +14,7 @@
 // writes one partial per tile.  A combine launch adds each task's partials in
 // tile order (deterministic for a given plan).  Backward
 // (dot: ga = g b, gb = g a; matvec y = A x: gA = g x^T, gx = A^T g) has the same
-// structure, with per-tile partial column sums for gx.  No float atomics, no
+// structure, with per-tile partial column sums for gx and long rows in several tiles.  No float atomics, no
 // cross-block fences.  The autotuner times candidate (tile_elems,
 // blocks_per_cu) pairs on the caller's buffers and caches the choice per task
 // table and device in a JSON file.
@@ -36,11 +36,12 @@ constexpr int NT = 256;
 constexpr int kDot = 0, kMatvec = 1;
 constexpr int kMinTile = 4096;
 constexpr int kXLds = 2048;  // matvec x staged in LDS up to this many columns
-constexpr int kXTail = 508;  // floats of zeros between x's whole vectors and its last elements there
 constexpr int NB = 512;      // threads of a backward block
 constexpr int kBwdVec = 2;   // 16-byte vectors per operand and thread of a dot's backward tile
 constexpr int64_t kDotChunk = 4 * kBwdVec * NB;  // elements of a dot's backward tile
 constexpr int kAdjRows = 8;  // rows of a matvec's backward that a thread has in flight
+constexpr int kWidthShift = 8;
+constexpr unsigned kAdjParts = 16;  // sums that a column's phases are added in
 constexpr int64_t kLongRow = 1 << 22;  // matvec rows past this length are walked one at a time backward
 
 struct TaskDev {
@@ -52,7 +53,8 @@ struct TaskDev {
 // One tile, carrying the task fields its kernels need, the offsets those of its
 // first element or row, so that taking a tile costs one descriptor load.
 struct TileDev {
-    uint32_t kind, count;  // dot: elements; matvec: rows
+    uint32_t kind;         // the kind, and from kWidthShift on the columns of a matvec's tile backward
+    uint32_t count;        // dot: elements; matvec: rows
     int64_t part;          // partial slot (float offset) or -1 to write the result directly
     int64_t cols, a_off, b_off, out_off;
 };
@@ -118,15 +120,19 @@ __device__ __forceinline__ float block_dot(const float *__restrict__ a, const fl
 // The rows of a matvec tile of c <= kXLds columns: 16 lanes per row, R rows
 // per group of lanes and 8 / R vectors per row and lane in flight (R: as many
 // rows as eight vectors per lane cover).  x in LDS: its whole vectors, zeros for
-// the lanes past them (up to 16 (K - 1) vectors, whose elements of A read as
-// zeros, so an infinite element of x must not meet them), then the last c % 4
-// elements.
+// the lanes past them (up to 16 (K - 1) vectors, whose elements of A read as zeros,
+// so an infinite element of x must not meet them), then the last c % 4 elements.
+constexpr int kXPad = 64 * 7;  // at K = 8
 template <int R>
-__device__ __forceinline__ void matvec_rows(const float *__restrict__ A, const float *x, float *__restrict__ out,
-                                            unsigned c, int64_t n) {
+__device__ __forceinline__ void matvec_rows(const float *__restrict__ A, const float *__restrict__ b, float *x,
+                                            float *__restrict__ out, unsigned c, int64_t n) {
     constexpr int K = 8 / R, G = NT / 16;
-    static_assert(4 * 16 * (K - 1) <= kXTail, "zeros for every lane past the row's vectors");
+    constexpr unsigned PAD = 64 * (K - 1);
     const unsigned grp = threadIdx.x >> 4, l = threadIdx.x & 15, nv = c >> 2;
+    for (unsigned v = threadIdx.x; v < nv + PAD / 4; v += NT)
+        *reinterpret_cast<f4u *>(x + 4 * v) = v < nv ? ld4<false>(b, 4 * v) : f4u{0.f, 0.f, 0.f, 0.f};
+    if (threadIdx.x < (c & 3)) x[4 * nv + PAD + threadIdx.x] = b[4 * nv + threadIdx.x];
+    __syncthreads();
     const unsigned row = 4u * grp * c;  // byte offset of this group's first row
     for (int64_t r0 = 0; r0 < n; r0 += G * R) {
         const unsigned rows = (unsigned)(n - r0 < G * R ? n - r0 : G * R);
@@ -150,7 +156,7 @@ __device__ __forceinline__ void matvec_rows(const float *__restrict__ A, const f
             }
         }
         if (4 * nv + l < c) {
-            const float xv = x[4 * nv + kXTail + l];
+            const float xv = x[4 * nv + PAD + l];
 #pragma unroll
             for (int q = 0; q < R; ++q) ac[q][1] += bld1(a, row + 4 * (4 * nv + l) + 4u * q * G * c) * xv;
         }
@@ -170,7 +176,7 @@ __global__ void __launch_bounds__(NT, 8) k_batch_fwd(const TileDev *__restrict__
                                                   const float *__restrict__ A, const float *__restrict__ B,
                                                   float *__restrict__ out, float *__restrict__ part) {
     __shared__ float red[NT / kWave];
-    __shared__ __attribute__((aligned(16))) float xs[kXLds + kXTail + 4];
+    __shared__ __attribute__((aligned(16))) float xs[kXLds + kXPad];
     using R = Red<MX_ADD, float>;
     const int64_t t = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     if (t >= ntiles) return;
@@ -182,14 +188,10 @@ __global__ void __launch_bounds__(NT, 8) k_batch_fwd(const TileDev *__restrict__
         if (threadIdx.x == 0) *(tk.part >= 0 ? part + tk.part : o) = acc;
     } else if (tk.cols <= kXLds) {
         const unsigned c = (unsigned)tk.cols;
-        const unsigned c4 = c & ~3u;
-        for (unsigned q = threadIdx.x; q < c + kXTail; q += NT)
-            xs[q] = q < c4 ? b[q] : q < c4 + kXTail ? 0.f : b[q - kXTail];
-        __syncthreads();
-        if (c > 256) matvec_rows<1>(a, xs, o, c, tk.count);
-        else if (c > 128) matvec_rows<2>(a, xs, o, c, tk.count);
-        else if (c > 64) matvec_rows<4>(a, xs, o, c, tk.count);
-        else matvec_rows<8>(a, xs, o, c, tk.count);
+        if (c > 256) matvec_rows<1>(a, b, xs, o, c, tk.count);
+        else if (c > 128) matvec_rows<2>(a, b, xs, o, c, tk.count);
+        else if (c > 64) matvec_rows<4>(a, b, xs, o, c, tk.count);
+        else matvec_rows<8>(a, b, xs, o, c, tk.count);
     } else {
         for (int64_t r = 0; r < tk.count; ++r) {  // a long row is a dot product
             const float acc = block_reduce<R, NT>(block_dot(a + r * tk.cols, b, tk.cols), red);
@@ -199,13 +201,14 @@ __global__ void __launch_bounds__(NT, 8) k_batch_fwd(const TileDev *__restrict__
     }
 }
 
-// One matvec tile's backward: gA rows get g[r] x, and dst (the tile's partial
-// column sums, or gB) the sums over its rows of g[r] A[r].  A thread takes four
-// columns and, when there are fewer groups of four than threads, one of P
-// phases of the rows (rows ph, ph + P, ...), whose partials are added in phase
-// order through LDS.  The tile has no more rows than the block takes at once
-// (adj_round), U to a thread.  The last group of a length that is not a
-// multiple of four overlaps the one before it and leaves its first `skip`
+// One matvec tile's backward, w columns of rows c apart: gA rows get g[r] x, and dst
+// (the tile's partial column sums, or gB) the sums over its rows of g[r] A[r].  A
+// thread takes four columns and, when there are fewer groups of four than
+// threads, one of P phases of the rows (rows ph, ph + P, ...), whose partials are
+// added in phase order through LDS, of many phases sixteen strided parts first.
+// The tile has no more rows than the block takes at once (adj_round), U to a
+// thread, and no more columns (adj_cols).  The last group of a width that is not
+// a multiple of four overlaps the one before it and leaves its first `skip`
 // columns to that, so rows of any length take 16-byte accesses.
 //
 // Bound by HBM: 447 MB of matrices in 198 us (4.5 TB/s of matrix and gradient,
@@ -215,86 +218,112 @@ __global__ void __launch_bounds__(NT, 8) k_batch_fwd(const TileDev *__restrict__
 template <bool PAST>
 __device__ __forceinline__ void matvec_adj_tile(const float *__restrict__ a, const float *__restrict__ x,
                                                 const float *__restrict__ g, float *__restrict__ ga, int64_t c,
-                                                unsigned rows, float *__restrict__ dst, float4 *red) {
+                                                unsigned w, unsigned rows, float *__restrict__ dst, float4 *red) {
     constexpr int U = kAdjRows;
     if (rows == 0) {  // no range to describe: the sums over no rows
-        for (int64_t j = threadIdx.x; j < c; j += NB) dst[j] = 0.f;
+        for (unsigned j = threadIdx.x; j < w; j += NB) dst[j] = 0.f;
         return;
     }
-    if (c < 4) {  // one thread per row, element by element
-        f4u s = {0.f, 0.f, 0.f, 0.f};
-        for (int64_t r = threadIdx.x; r < rows; r += NB) {
-            const float gr = g[r];
+    if (w < 4) {  // whole rows, one thread each, element by element
+        constexpr int U = 4;
+        float s[3] = {0.f, 0.f, 0.f}, xe[3];
 #pragma unroll
-            for (int e = 0; e < 3; ++e)
-                if (e < c) {
-                    s[e] += a[r * c + e] * gr;
-                    ga[r * c + e] = x[e] * gr;
+        for (unsigned e = 0; e < 3; ++e) xe[e] = e < w ? x[e] : 0.f;
+        for (unsigned r0 = threadIdx.x; r0 < rows; r0 += U * NB) {
+            float gv[U], av[U][3];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned r = r0 + u * NB;
+                gv[u] = r < rows ? g[r] : 0.f;
+#pragma unroll
+                for (unsigned e = 0; e < 3; ++e) av[u][e] = r < rows && e < w ? a[r * w + e] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (unsigned e = 0; e < 3; ++e) {
+                    s[e] += av[u][e] * gv[u];
+                    if (r0 + u * NB < rows && e < w) ga[(r0 + u * NB) * w + e] = xe[e] * gv[u];
                 }
         }
-        red[threadIdx.x] = make_float4(s.x, s.y, s.z, 0.f);
+        float *ws = reinterpret_cast<float *>(red);  // [wave][3]
+#pragma unroll
+        for (unsigned e = 0; e < 3; ++e) {
+            const float v = wave_reduce<Red<MX_ADD, float>>(s[e]);
+            if (threadIdx.x % kWave == 0) ws[threadIdx.x / kWave * 3 + e] = v;
+        }
         __syncthreads();
-        if (threadIdx.x < c) {
-            float t = 0.f;
-            const float *q = reinterpret_cast<const float *>(red) + threadIdx.x;
-#pragma unroll 8
-            for (int ph = 0; ph < NB; ++ph) t += q[4 * ph];
+        if (threadIdx.x < w) {
+            float t = ws[threadIdx.x];
+#pragma unroll
+            for (int k = 1; k < NB / kWave; ++k) t += ws[3 * k + threadIdx.x];
             dst[threadIdx.x] = t;
         }
         return;
     }
-    const int64_t cv = (c + 3) >> 2;
-    const unsigned cv1 = (unsigned)(cv < NB ? cv : NB);  // groups of a pass over the columns
-    const unsigned P = __builtin_amdgcn_readfirstlane(NB / cv1), j = threadIdx.x % cv1, ph = threadIdx.x / cv1;
+    const unsigned cv = (w + 3) >> 2;  // groups of four columns, at most NB
+    const unsigned P = __builtin_amdgcn_readfirstlane(NB / cv < rows ? NB / cv : rows), j = threadIdx.x % cv,
+                   ph = threadIdx.x / cv;
     // the byte stride from a thread's row to its next; rows too long for a
     // 32-bit offset to reach it come one to a tile
     const unsigned step = c <= kLongRow ? 4u * P * (unsigned)c : 0x10000000u;
-    for (int64_t j0 = 0; j0 < cv; j0 += NB) {  // one pass unless P == 1
-        const int64_t col0 = 4 * j0 < c - 4 ? 4 * j0 : c - 4;
-        const int64_t want = 4 * (j0 + j);
-        const bool mine = ph < P && want < c;
-        const unsigned dc = (unsigned)((want + 4 <= c ? want : c - 4) - col0);  // this group's first column - col0
-        const int skip = (int)(want - (col0 + dc));
-        const int64_t bytes = c <= kLongRow ? 4 * (rows * c - col0) : 16 * NB;
-        const buf ab = make_buf(a + col0, bytes), ob = make_buf(ga + col0, bytes), gb = make_buf(g, 4u * rows);
-        const unsigned off = (P > 1 ? 4u * ph * (unsigned)c : 0u) + 4u * dc;
-        unsigned ld_at = mine ? off : kOutside, st_at = mine && skip == 0 ? off : kOutside, g_at = 4u * ph;
-        f4u av[U], s = {0.f, 0.f, 0.f, 0.f}, xj = s;
-        float gv[U];
-        if (mine) xj = ld4<false>(x + col0, dc);
+    const bool mine = ph < P;
+    const unsigned first = 4 * j + 4 <= w ? 4 * j : w - 4;  // this group's first column
+    const int skip = (int)(4 * j - first);
+    const int64_t bytes = 4 * ((rows - 1) * (c <= kLongRow ? c : 0) + w);
+    const buf ab = make_buf(a, bytes), ob = make_buf(ga, bytes), gb = make_buf(g, 4u * rows);
+    const unsigned off = (P > 1 ? 4u * ph * (unsigned)c : 0u) + 4u * first;
+    unsigned ld_at = mine ? off : kOutside, st_at = mine && skip == 0 ? off : kOutside, g_at = 4u * ph;
+    f4u av[U], s = {0.f, 0.f, 0.f, 0.f}, xj = s;
+    float gv[U];
+    if (mine) xj = ld4<false>(x, first);
 #pragma unroll
-        for (int u = 0; u < U; ++u, ld_at += step, g_at += 4 * P) {
-            av[u] = bld4<PAST>(ab, ld_at);
-            gv[u] = bld1(gb, g_at);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u, st_at += step) {
-            s += av[u] * gv[u];
-            bst4(xj * gv[u], ob, st_at);
-        }
-        if (mine && skip != 0)  // the last one to three columns of gA
-            for (unsigned r = ph; r < rows; r += P) {
-                const float gr = g[r];
-                float *o = ga + r * c + col0 + dc;
-                o[3] = xj[3] * gr;
-                if (skip < 3) o[2] = xj[2] * gr;
-                if (skip < 2) o[1] = xj[1] * gr;
-            }
-        if (P > 1) {
-            red[threadIdx.x] = make_float4(s.x, s.y, s.z, s.w);
-            __syncthreads();
-            if (ph == 0)
-#pragma unroll 8
-                for (unsigned q = 1; q < P; ++q) {
-                    const float4 v = red[q * cv1 + j];
-                    s += f4u{v.x, v.y, v.z, v.w};
-                }
-        }
-        if (mine && ph == 0)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (e >= skip) dst[col0 + dc + e] = s[e];
+    for (int u = 0; u < U; ++u, ld_at += step, g_at += 4 * P) {
+        av[u] = bld4<PAST>(ab, ld_at);
+        gv[u] = bld1(gb, g_at);
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u, st_at += step) {
+        s += av[u] * gv[u];
+        bst4(xj * gv[u], ob, st_at);
+    }
+    if (mine && skip != 0)  // the last one to three columns of gA
+        for (unsigned r = ph; r < rows; r += P) {
+            const float gr = g[r];
+            float *o = ga + r * c + first;
+            o[3] = xj[3] * gr;
+            if (skip < 3) o[2] = xj[2] * gr;
+            if (skip < 2) o[1] = xj[1] * gr;
+        }
+    if (P > 1) {
+        red[threadIdx.x] = make_float4(s.x, s.y, s.z, s.w);
+        __syncthreads();
+        unsigned parts = P;
+        if (P > kAdjParts) {  // part k: phases k, k + kAdjParts, ...
+            f4u t = {0.f, 0.f, 0.f, 0.f};
+            if (ph < kAdjParts)
+#pragma unroll 4
+                for (unsigned q = ph; q < P; q += kAdjParts) {
+                    const float4 v = red[q * cv + j];
+                    t += f4u{v.x, v.y, v.z, v.w};
+                }
+            __syncthreads();
+            if (ph < kAdjParts) red[threadIdx.x] = make_float4(t.x, t.y, t.z, t.w);
+            s = t;
+            parts = kAdjParts;
+            __syncthreads();
+        }
+        if (ph == 0)
+#pragma unroll 8
+            for (unsigned q = 1; q < parts; ++q) {
+                const float4 v = red[q * cv + j];
+                s += f4u{v.x, v.y, v.z, v.w};
+            }
+    }
+    if (ph == 0)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e >= skip) dst[first + e] = s[e];
 }
 
 // Bound by HBM.  A dot's tile is one round of the block's accesses, so that the
@@ -354,7 +383,7 @@ __global__ void __launch_bounds__(NB) k_batch_bwd(const TileDev *__restrict__ ti
         }
     } else {
         float *dst = tk.part >= 0 ? part + tk.part : gB + tk.b_off;
-        matvec_adj_tile<PAST>(A + tk.a_off, B + tk.b_off, gout + tk.out_off, gA + tk.a_off, tk.cols, tk.count,
+        matvec_adj_tile<PAST>(A + tk.a_off, B + tk.b_off, gout + tk.out_off, gA + tk.a_off, tk.cols, tk.kind >> kWidthShift, tk.count,
                               dst, red);
     }
 }
@@ -384,16 +413,36 @@ __global__ void __launch_bounds__(NT) k_batch_combine_fwd(const TaskDev *__restr
     out[tk.out_off] = sum_strided(part + tk.fwd_part, tk.fwd_ntiles, 1);
 }
 
-// grid (tasks in the list, column chunks of NT): column j of task gets the sum
-// of its per-tile partial column sums in tile order
+// grid (tasks in the list, column chunks): column j of a task gets the sum of
+// its per-tile partial column sums, PARTS runs of tiles each in tile order, then
+// the runs in order.  One run up to kRunTiles tiles; past them a thread per column
+// would wait for eight loads at a time (2000 x 2000, 250 tiles: backward 18.1 us
+// with one run).
+constexpr int kRunTiles = 16;
+template <int PARTS>
 __global__ void __launch_bounds__(NT) k_batch_combine_bwd(const TaskDev *__restrict__ tasks,
                                                           const int32_t *__restrict__ list, int64_t nlist,
                                                           const float *__restrict__ part, float *__restrict__ gB) {
+    constexpr int COLS = NT / PARTS;
+    __shared__ float red[PARTS][COLS];
     if ((int64_t)blockIdx.x >= nlist) return;
     const TaskDev tk = tasks[list[blockIdx.x]];
-    const int64_t c = tk.cols;
-    for (int64_t j = (int64_t)blockIdx.y * NT + threadIdx.x; j < c; j += (int64_t)gridDim.y * NT)
-        gB[tk.b_off + j] = sum_strided(part + tk.bwd_part + j, tk.bwd_ntiles, c);
+    const int64_t c = tk.cols, per = (tk.bwd_ntiles + PARTS - 1) / PARTS;
+    const int q = threadIdx.x / COLS, l = threadIdx.x % COLS;
+    const int64_t q0 = q * per, n = q0 + per < tk.bwd_ntiles ? per : tk.bwd_ntiles - q0;
+    for (int64_t j0 = (int64_t)blockIdx.y * COLS; j0 < c; j0 += (int64_t)gridDim.y * COLS) {
+        const int64_t j = j0 + l;
+        float s = j < c ? sum_strided(part + tk.bwd_part + q0 * c + j, n, c) : 0.f;
+        if constexpr (PARTS > 1) {
+            red[q][l] = s;
+            __syncthreads();
+            if (q == 0)
+#pragma unroll
+                for (int k = 1; k < PARTS; ++k) s += red[k][l];
+            __syncthreads();
+        }
+        if (q == 0 && j < c) gB[tk.b_off + j] = s;
+    }
 }
 
 // ---------------------------------------------------------------- plain: one launch per task
@@ -452,7 +501,7 @@ struct mx_batch_plan {
     TileDev *d_fwd = nullptr, *d_bwd = nullptr;
     int32_t *d_fwd_list = nullptr, *d_bwd_list = nullptr;
     int64_t n_fwd = 0, n_bwd = 0, n_fwd_list = 0, n_bwd_list = 0;
-    int64_t bwd_list_max_cols = 1;
+    int64_t bwd_list_max_cols = 1, bwd_list_max_tiles = 1;
     int64_t fwd_part_floats = 0, bwd_part_floats = 0;
     size_t ws_need = 0;
 };
@@ -472,9 +521,16 @@ void free_device(mx_batch_plan *p) {
 
 // rows that a block takes at once in a matvec's backward
 int64_t adj_round(int64_t c) {
-    if (c < 4) return INT64_MAX;  // walked by rows
+    if (c < 4) return 2 * kMinTile / std::max<int64_t>(c, 1);  // one to two rounds
     if (c > kLongRow) return 1;
     return kAdjRows * (NB / std::min<int64_t>(ceil_div(c, 4), NB));
+}
+// columns of a matvec's tile backward with `left` more to go: a row's parts share
+// no sum, and 1 x 2^23 takes 6.0 ms by one block that walks it; never one to three
+// columns, which would be no group of four
+int64_t adj_cols(int64_t left) {
+    const int64_t most = 4 * NB;
+    return left <= most ? left : left < most + 4 ? most - 4 : most;
 }
 // rows of a matvec's tile backward (at most what a block takes at once) and forward
 int64_t fwd_rows(int64_t cols, int64_t tile) { return std::max<int64_t>(1, 2 * tile / std::max<int64_t>(cols, 1)); }
@@ -507,7 +563,8 @@ TileDev make_tile(const TaskDev &tk, int64_t begin, int64_t end, int64_t part) {
 // order within a class (so plans are reproducible): one counting pass.
 void order_tiles(std::vector<TileDev> &v) {
     auto cls = [](const TileDev &t) {
-        const uint64_t c = t.kind == kDot ? 2 * (uint64_t)t.count : t.count * (uint64_t)t.cols;
+        const uint64_t w = t.kind >> kWidthShift;
+        const uint64_t c = t.kind == kDot ? 2 * (uint64_t)t.count : t.count * (w ? w : (uint64_t)t.cols);
         if (c < 8) return 511 - (int)c;
         const int e = 63 - __builtin_clzll(c);
         return 511 - (8 * (e - 2) + (int)((c >> (e - 3)) & 7));
@@ -525,7 +582,7 @@ mx_status build_tiles(mx_batch_plan *p) {
     std::vector<TaskDev> tasks((size_t)p->ntasks);
     std::vector<TileDev> fwd, bwd;
     std::vector<int32_t> fwd_list, bwd_list;
-    int64_t fpart = 0, bpart = 0, max_cols = 1;
+    int64_t fpart = 0, bpart = 0, max_cols = 1, max_tiles = 1;
     for (int64_t t = 0; t < p->ntasks; ++t) {
         const int64_t *r = &p->table[(size_t)(6 * t)];
         TaskDev &tk = tasks[(size_t)t];
@@ -566,11 +623,19 @@ mx_status build_tiles(mx_batch_plan *p) {
             tk.bwd_ntiles = nb;
             tk.bwd_part = nb > 1 ? bpart : -1;
             for (int64_t q = 0; q < nb; ++q)
-                bwd.push_back(make_tile(tk, q * rows, std::min(tk.rows, (q + 1) * rows), nb > 1 ? bpart + q * tk.cols : -1));
+                for (int64_t c0 = 0, w; c0 == 0 || c0 < tk.cols; c0 += std::max<int64_t>(w, 1)) {
+                    w = adj_cols(tk.cols - c0);
+                    TileDev t = make_tile(tk, q * rows, std::min(tk.rows, (q + 1) * rows), nb > 1 ? bpart + q * tk.cols + c0 : -1);
+                    t.kind |= (uint32_t)w << kWidthShift;
+                    t.a_off += c0;
+                    t.b_off += c0;
+                    bwd.push_back(t);
+                }
             if (nb > 1) {
                 bwd_list.push_back((int32_t)t);
                 bpart += nb * tk.cols;
                 max_cols = std::max(max_cols, tk.cols);
+                max_tiles = std::max(max_tiles, nb);
             }
         }
     }
@@ -596,6 +661,7 @@ mx_status build_tiles(mx_batch_plan *p) {
     p->n_fwd_list = (int64_t)fwd_list.size();
     p->n_bwd_list = (int64_t)bwd_list.size();
     p->bwd_list_max_cols = max_cols;
+    p->bwd_list_max_tiles = max_tiles;
     p->fwd_part_floats = fpart;
     p->bwd_part_floats = bpart;
     return MX_OK;
@@ -628,7 +694,12 @@ dim3 grid_of(int64_t ntiles) {
 }
 // LDS that a launch asks for so that no more than blocks_per_cu blocks are
 // resident on a CU (the kernels' own arrays are `own`; eight blocks forward and
-// four backward are what its waves allow).
+// four backward are what its waves allow).  A backward pass past the caches
+// keeps to two: more rows open at once cost more than they hide (forward and
+// backward of 889 MB of matrices 767 us with four, 744 us with three, 716 us with
+// two), where a small one is all latency (20 000 dots of 0 .. 50 elements 37 us
+// with two, 23 us with four).
+constexpr unsigned kPastBlocks = 2;
 constexpr unsigned kCuLds = 163840, kWaveBlocks = 8;
 constexpr unsigned lds_for_blocks(unsigned b) { return b >= kWaveBlocks ? 0u : kCuLds / (b + 1) + 1024u; }
 constexpr bool lds_holds_blocks() {
@@ -637,14 +708,14 @@ constexpr bool lds_holds_blocks() {
     return true;
 }
 static_assert(lds_holds_blocks(), "as many blocks as asked for fit a CU, and no more");
-unsigned lds_of(const mx_batch_plan *p, unsigned own) {
-    const unsigned per = lds_for_blocks((unsigned)p->cfg.blocks_per_cu);
+unsigned lds_of(const mx_batch_plan *p, unsigned own, unsigned most = kWaveBlocks) {
+    const unsigned per = lds_for_blocks(std::min((unsigned)p->cfg.blocks_per_cu, most));
     return per > own ? per - own : 0u;
 }
 
 mx_status fwd_impl(const mx_batch_plan *p, const float *A, const float *B, float *out, void *ws, hipStream_t s) {
     float *part = fwd_part_ptr(p, ws);
-    hipLaunchKernelGGL(k_batch_fwd, grid_of(p->n_fwd), dim3(NT), lds_of(p, 4 * (kXLds + kXTail + 4 + 16)), s, p->d_fwd, p->n_fwd, A, B, out, part);
+    hipLaunchKernelGGL(k_batch_fwd, grid_of(p->n_fwd), dim3(NT), lds_of(p, 4 * (kXLds + kXPad + 16)), s, p->d_fwd, p->n_fwd, A, B, out, part);
     if (p->n_fwd_list > 0)
         hipLaunchKernelGGL(k_batch_combine_fwd, dim3((unsigned)ceil_div(p->n_fwd_list, NT)), dim3(NT), 0, s,
                            p->d_tasks, p->d_fwd_list, p->n_fwd_list, part, out);
@@ -656,12 +727,14 @@ mx_status bwd_impl(const mx_batch_plan *p, const float *A, const float *B, const
     float *part = bwd_part_ptr(p, ws);
     const bool past = (p->a_len + p->b_len) * 2 * (int64_t)sizeof(float) > kCacheBytes;
     hipLaunchKernelGGL(past ? k_batch_bwd<true> : k_batch_bwd<false>, grid_of(p->n_bwd), dim3(NB),
-                       lds_of(p, 16 * NB), s, p->d_bwd, p->n_bwd, A, B, gout, gA, gB, part);
+                       lds_of(p, 16 * NB, past ? kPastBlocks : kWaveBlocks), s, p->d_bwd, p->n_bwd, A, B, gout, gA, gB, part);
     if (p->n_bwd_list > 0) {
+        constexpr int PARTS = 8;
+        const bool runs = p->bwd_list_max_tiles > kRunTiles;
         const dim3 cgrid((unsigned)p->n_bwd_list,
-                         (unsigned)std::min<int64_t>(1024, ceil_div(p->bwd_list_max_cols, NT)));
-        hipLaunchKernelGGL(k_batch_combine_bwd, cgrid, dim3(NT), 0, s, p->d_tasks, p->d_bwd_list, p->n_bwd_list, part,
-                           gB);
+                         (unsigned)std::min<int64_t>(1024, ceil_div(p->bwd_list_max_cols, runs ? NT / PARTS : NT)));
+        hipLaunchKernelGGL(runs ? k_batch_combine_bwd<PARTS> : k_batch_combine_bwd<1>, cgrid, dim3(NT), 0, s, p->d_tasks,
+                           p->d_bwd_list, p->n_bwd_list, part, gB);
     }
     return last_launch("mx_batch_backward");
 }

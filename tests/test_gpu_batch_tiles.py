@@ -115,3 +115,15 @@ def test_autotune_times_each_launch_once():
     A, B, gout, gA, gB, out = (torch.rand(n, device="cuda") for n in (na, nb, no, na, nb, no))
     for _ in range(3):
         assert api.Batch(tb).autotune(A, B, out, gout, gA, gB)[1] in (2, 4, 8)
+
+
+@pytest.mark.parametrize("gap", [0, 1])
+@pytest.mark.parametrize("cfg", [None, (65536, 8), (4096, 2)])
+def test_wide_and_tall_backward(cfg, gap):
+    """Long rows in several tiles of columns (remainders of one to four past 2048), short ones whose many phases are added
+    in parts, rows of one to three elements in several rounds, and tasks of many tiles whose sums are added in runs."""
+    say("batch wide and tall", cfg, gap)
+    tasks = [(1, r, c) for c in (2051, 2052, 4095, 4096, 4097, 4098, 4100, 6145, 20003) for r in (1, 2, 9, 20)]
+    tasks += [(1, r, c) for c in (1, 2, 3, 4, 5, 17, 33) for r in (1, 2, 15, 17, 511, 2049, 4097, 8193)]
+    tasks += [(1, 40000, 1), (1, 30000, 4), (1, 3000, 1001), (1, 700, 2100)]
+    check(tasks, cfg, gap)
