@@ -131,20 +131,77 @@ __global__ void __launch_bounds__(NT) k_arg_finish(const float *__restrict__ pv,
     }
 }
 
-// One wave per ragged row (rows grid-strided over the waves): the row's best
-// pair, then the row written as g at the arg and 0 elsewhere.  Reads and writes
-// go in 16-byte vectors at 4-byte alignment, four per lane in flight; the best
-// value by the DPP tree, then the lowest index among the lanes that hold it.
-// HBM bound at 65 536 rows of mean length 490 (32 M values, 256 MB in and out):
-// 40 us (6.4 TB/s, the last-level cache serving part); 89 us with one element
-// per lane and pass and 64-bit pairs shuffled.
+// A group of G lanes per ragged row, a wave, or a 16-lane DPP row where rows are
+// short (rows grid-strided over the waves): the row's best pair, then the row
+// written as g at the arg and 0 elsewhere.  Reads and writes go in 16-byte vectors
+// at 4-byte alignment, four per lane in flight; the best value by the DPP tree,
+// then the lowest index among the lanes that hold it.  HBM bound at 65 536 rows of
+// mean length 490 (32 M values, 256 MB in and out): 40 us (6.4 TB/s, the last-level
+// cache serving part); 89 us with one element per lane and pass and 64-bit pairs
+// shuffled.
+//
+// A row past kRounds rounds of 16 lanes' loads is taken by its whole wave (in a
+// vector per lane, since registers for more would cost the others a wave per SIMD): 262 144
+// rows of mean length 45, twenty of them of 524 288, took 2.7 ms with a wave and one
+// element per lane for every row, 7.4 ms with 16 lanes.
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int OP, int G>  // G lanes per row: a wave, or a 16-lane DPP row where rows are short
+// v at index i improves on bv.  A thread's indices rise, so of equal values the
+// lowest index stays; an element equal to the identity never improves on ne, so
+// it needs no index.
+template <int OP> __device__ __forceinline__ void scan(float v, int64_t i, float &bv, int64_t &bi) {
+    if (OP == MX_MIN ? v < bv : v > bv) {
+        bv = v;
+        bi = i;
+    }
+}
+
+// row x[0 .. n) with its gradient y, by lane `lane` of L, U vectors in flight (all
+// lanes of the wave active)
+template <int OP, int L, int U>
+__device__ __forceinline__ void arg_row(const float *__restrict__ x, float *__restrict__ y, int64_t n, int lane, float ne,
+                                        float g) {
+    const int64_t nv = n / 4;
+    float bv = ident<OP>();
+    int64_t bi = kNone;
+    for (int64_t i = lane; i < nv; i += U * L) {
+        f4u q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * L < nv) q[u] = *reinterpret_cast<const f4u *>(x + 4 * (i + u * L));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i + u * L < nv) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) scan<OP>(q[u][c], 4 * (i + u * L) + c, bv, bi);
+            }
+    }
+    if (4 * nv + lane < n) scan<OP>(x[4 * nv + lane], 4 * nv + lane, bv, bi);
+    using B = Red<OP, float>;
+    using I = Red<MX_MIN, int64_t>;
+    const float best = group_reduce<B, L>(bv);
+    int64_t at = group_reduce<I, L>(bv == best ? bi : kNone);
+    // ne stands at index -1; a NaN ne is never improved on by the fold
+    if (!better<OP>(best, 0, ne, -1)) at = kNone;
+    for (int64_t i = lane; i < nv; i += L) {
+        f4u z = f4u{0.f, 0.f, 0.f, 0.f};
+        const int64_t c = at - 4 * i;
+        if (c >= 0 && c < 4) {
+            z.x = c == 0 ? g : 0.f;
+            z.y = c == 1 ? g : 0.f;
+            z.z = c == 2 ? g : 0.f;
+            z.w = c == 3 ? g : 0.f;
+        }
+        *reinterpret_cast<f4u *>(y + 4 * i) = z;
+    }
+    if (4 * nv + lane < n) y[4 * nv + lane] = 4 * nv + lane == at ? g : 0.f;
+}
+
+template <int OP, int G>
 __global__ void __launch_bounds__(NT) k_seg_arg(const float *__restrict__ values, const int64_t *__restrict__ offsets,
                                                 int64_t nseg, float ne, const float *__restrict__ gout,
                                                 float *__restrict__ gvalues) {
-    constexpr int U = 4;
+    constexpr int kRounds = 4;
     const int lane = threadIdx.x % G;
     const int64_t ng = (int64_t)gridDim.x * (NT / G);
     // the groups of a wave stay together (their rows may differ): all lanes
@@ -154,42 +211,14 @@ __global__ void __launch_bounds__(NT) k_seg_arg(const float *__restrict__ values
         const bool has = r < nseg;
         const int64_t s = has ? offsets[r] : 0, e = has ? offsets[r + 1] : 0;
         const float g = has ? gout[r] : 0.f;
-        const int64_t n = e - s, nv = n / 4;
-        const float *x = values + s;
-        float bv = ident<OP>();
-        int64_t bi = kNone;
-        for (int64_t i = lane; i < nv; i += U * G) {
-            f4u q[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (i + u * G < nv) q[u] = *reinterpret_cast<const f4u *>(x + 4 * (i + u * G));
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (i + u * G < nv) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) take<OP>(q[u][c], 4 * (i + u * G) + c, bv, bi);
-                }
-        }
-        if (4 * nv + lane < n) take<OP>(x[4 * nv + lane], 4 * nv + lane, bv, bi);
-        using B = Red<OP, float>;
-        using I = Red<MX_MIN, int64_t>;
-        const float best = group_reduce<B, G>(bv);
-        int64_t at = group_reduce<I, G>(bv == best ? bi : kNone);
-        // ne stands at index -1; a NaN ne is never improved on by the fold
-        if (!better<OP>(best, 0, ne, -1)) at = kNone;
-        float *y = gvalues + s;
-        for (int64_t i = lane; i < nv; i += G) {
-            f4u z = f4u{0.f, 0.f, 0.f, 0.f};
-            const int64_t c = at - 4 * i;
-            if (c >= 0 && c < 4) {
-                z.x = c == 0 ? g : 0.f;
-                z.y = c == 1 ? g : 0.f;
-                z.z = c == 2 ? g : 0.f;
-                z.w = c == 3 ? g : 0.f;
+        const bool far = G < kWave && e - s > (int64_t)kRounds * 16 * G;
+        arg_row<OP, G, 4>(values + s, gvalues + s, far ? 0 : e - s, lane, ne, g);
+        if constexpr (G < kWave)
+            for (uint64_t m = __ballot(far && lane == 0); m; m &= m - 1) {
+                const int o = __builtin_ctzll(m);
+                const int64_t fs = read_lane(s, o), fe = read_lane(e, o);
+                arg_row<OP, kWave, 1>(values + fs, gvalues + fs, fe - fs, threadIdx.x % kWave, ne, read_lane(g, o));
             }
-            *reinterpret_cast<f4u *>(y + 4 * i) = z;
-        }
-        if (4 * nv + lane < n) y[4 * nv + lane] = 4 * nv + lane == at ? g : 0.f;
     }
 }
 
@@ -264,8 +293,8 @@ mx_status mx_segmented_reduce_adjoint_f32(mx_redop op, const float *values_dev, 
     if (mx_status st = device_info(&d)) return st;
     // lanes per row by mean length; with few rows a wave each costs nothing (4000
     // rows of mean 143: 3.9 us against 5.7 us with 16 lanes; 65 536 of mean 79:
-    // 20.4 us against 10)
-    const int group = nvalues <= 64 * nseg || (nvalues <= 160 * nseg && nseg >= 16384) ? 16 : kWave;
+    // 20.4 us against 10; 300 of mean 7 2.3 against 2.6, 3000 2.8 against 2.2)
+    const int group = (nvalues <= 64 * nseg && nseg >= 1024) || (nvalues <= 160 * nseg && nseg >= 16384) ? 16 : kWave;
     int64_t grid = ceil_div(nseg, NT / group);
     if (grid > (int64_t)d->num_cus * 16) grid = (int64_t)d->num_cus * 16;
     const float ne = *ne_host;
