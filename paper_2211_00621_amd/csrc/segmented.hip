@@ -1140,9 +1140,9 @@ k_bcast_blocks(const float *__restrict__ gout, const int64_t *__restrict__ offse
 // chunked kernels are all latency, and many rows of short to ordinary length,
 // where a block of the row-span kernel has little to stream between its round
 // trips (offsets, values, store).  A group of G lanes takes one row, every load
-// of a row of up to U G vectors in flight at once; longer rows are then taken by
-// the whole block, U vectors per thread in flight, so that a single long row
-// streams as in the kernels this one replaces.
+// of a row of up to U G vectors in flight at once; longer rows are then taken by a
+// wave each, and past kWaveCap by the whole block, U vectors per thread in
+// flight, so that a single long row streams as in the kernels this one replaces.
 //
 // us before and now (sum, launches replayed from a graph): 300 rows, 23 001
 // values 10.1, 2.5; 1000 rows, 12 357 values 18.8, 2.5; 65 536 rows of mean
@@ -1174,17 +1174,23 @@ __global__ void __launch_bounds__(NTB) k_seg_groups(const typename DT<D>::In *__
     using Acc = typename DT<D>::Acc;
     using Vec = typename DT<D>::Vec;
     using R = Red<OP, Acc>;
-    constexpr int V = DT<D>::kVec, ROWS = NTB / G;
+    constexpr int V = DT<D>::kVec, ROWS = NTB / G, NW = NTB / kWave;
     __shared__ int64_t soff[ROWS + 1];
-    __shared__ Acc part[NTB / kWave];
+    __shared__ Acc part[NW];
+    __shared__ unsigned long long longer;  // rows past what a group takes
     const int t = threadIdx.x;
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const int nrows = (int)(nseg - r0 < ROWS ? nseg - r0 : ROWS);
     if (t <= nrows) soff[t] = offsets[r0 + t];
+    if (t == 0) longer = 0;
     __syncthreads();
-    // lane l of L folds the vectors l, l + L, ... of [s, e), then the remainder
-    auto fold = [&](int64_t s, int64_t e, int l, int L) {
-        Acc a = R::id();
+    // lane l of L folds the vectors l, l + L, ... of [s, e) into A sums, then the
+    // remainder
+    auto fold = [&](auto sums, int64_t s, int64_t e, int l, int L) {
+        constexpr int A = decltype(sums)::value;
+        Acc a[A];
+#pragma unroll
+        for (int j = 0; j < A; ++j) a[j] = R::id();
         const int64_t nv = (e - s) / V;
         const In *p = values + s;
         for (int64_t i = l; i < nv; i += (int64_t)U * L) {
@@ -1196,28 +1202,47 @@ __global__ void __launch_bounds__(NTB) k_seg_groups(const typename DT<D>::In *__
             for (int u = 0; u < U; ++u)
                 if (i + (int64_t)u * L < nv) {
 #pragma unroll
-                    for (int j = 0; j < V; ++j) a = R::ap(a, Acc(vget<Vec, In>(x[u], j)));
+                    for (int j = 0; j < V; ++j) a[j % A] = R::ap(a[j % A], Acc(vget<Vec, In>(x[u], j)));
                 }
         }
-        if (s + nv * V + l < e) a = R::ap(a, Acc(p[nv * V + l]));
-        return a;
+        if (s + nv * V + l < e) a[0] = R::ap(a[0], Acc(p[nv * V + l]));
+#pragma unroll
+        for (int h = A / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int j = 0; j < h; ++j) a[j] = R::ap(a[j], a[j + h]);
+        return a[0];
     };
-    constexpr int64_t kCap = (int64_t)G * U * V;  // longest row a group takes
+    // as many sums as keep sixteen additions in a row (one sum for each element of
+    // a vector would cost short rows 3 %); a long row's are its vectors' own
+    using Sums = std::integral_constant<int, (U * V / 16 < 1 ? 1 : U * V / 16)>;
+    using AllSums = std::integral_constant<int, V>;
+    constexpr int64_t kCap = (int64_t)G * U * V;              // longest row a group takes
+    constexpr int64_t kWaveCap = (int64_t)kWave * U * V * 4;  // and a wave
     const int k = t / G, l = t % G;
     const int64_t s = k < nrows ? soff[k] : 0, e = k < nrows ? soff[k + 1] : 0;
     const bool mine = e - s <= kCap;
-    const Acc v = group_reduce<R, G>(mine ? fold(s, e, l, G) : R::id());
+    const Acc v = group_reduce<R, G>(mine ? fold(Sums{}, s, e, l, G) : R::id());
     if (l == 0 && k < nrows && mine) out[r0 + k] = s < e ? R::ap(ne, v) : ne;
+    if (l == 0 && !mine) atomicOr(&longer, 1ull << k);
     if (!__syncthreads_or(!mine)) return;
-    for (int q = 0; q < nrows; ++q) {
+    const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+    const bool few = __popcll(longer) <= 2;  // too few to give every wave one
+    int turn = 0;
+    for (uint64_t m = longer; m; m &= m - 1) {  // alike in every thread
+        const int q = __builtin_ctzll(m);
         const int64_t qs = soff[q], qe = soff[q + 1];
-        if (qe - qs <= kCap) continue;  // alike in every thread
-        const Acc a = wave_reduce<R>(fold(qs, qe, t, NTB));
-        if ((t & (kWave - 1)) == 0) part[t / kWave] = a;
+        const bool whole = few || qe - qs > kWaveCap;
+        if (!whole && turn++ % NW != w) continue;
+        const Acc a = wave_reduce<R>(fold(AllSums{}, qs, qe, whole ? t : t % kWave, whole ? NTB : kWave));
+        if (!whole) {
+            if (t % kWave == 0) out[r0 + q] = R::ap(ne, a);
+            continue;
+        }
+        if (t % kWave == 0) part[w] = a;
         __syncthreads();
         if (t == 0) {
             Acc z = part[0];
-            for (int o = 1; o < NTB / kWave; ++o) z = R::ap(z, part[o]);
+            for (int o = 1; o < NW; ++o) z = R::ap(z, part[o]);
             out[r0 + q] = R::ap(ne, z);
         }
         __syncthreads();

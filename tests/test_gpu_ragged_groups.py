@@ -111,3 +111,22 @@ def test_group_reverses(case):
                 ref = O.segmented_reduce_adjoint(op, ne, v, off, g)
             assert np.array_equal(got[shift:nv + shift], ref.astype(np.float32)), (op, ne, shift)
             assert (got[:shift] == 5.0).all() and (got[nv + shift:] == 5.0).all()
+
+
+LONG = {
+    # many long rows to a block, for its waves in turn, and some past what a wave takes; sixteen lanes a row
+    "lanes": np.array(([3] * 20 + [257, 300, 1025, 4096, 4097] + [0]) * 25 + [9] * 400 + [7000]),
+    # a wave a row, and one or two long rows in a block, which takes them whole
+    "wave": np.array([60] * 15 + [1025] + [70] * 14 + [1026, 16385] + [0, 50, 4097, 4099, 1500, 2000, 3000, 16384, 16385]),
+    # as many rows as take sixteen lanes in the reverse of a maximum, twenty of them for their whole wave
+    "reverse": np.array(([5] * 60 + [1024, 1025, 1029, 9001]) * 20),
+}
+
+
+@pytest.mark.parametrize("case", list(LONG))
+@pytest.mark.parametrize("dt", [np.float32, np.float64, np.int32])
+def test_long_rows_by_waves_and_blocks(case, dt, monkeypatch):
+    monkeypatch.setitem(globals(), "lengths", LONG.__getitem__)
+    test_group_reduce(case, dt)
+    if dt == np.float32:
+        test_group_reverses(case)
