@@ -1481,19 +1481,21 @@ constexpr int64_t kSpanAvgMax = 16384;  // average row length, at most
 bool seg_span_path(int64_t nseg, int64_t nval, const DeviceInfo *d) {
     return nseg >= (int64_t)d->num_cus * 32 && nval <= nseg * kSpanAvgMax;
 }
-// Rows per block of the row-span kernels: what leaves eight blocks per CU, at
-// most sixteen rows of an average length up to `avg16`, eight of longer ones (a
+// Rows per block of the row-span kernels: what leaves eight blocks per CU (32 of
+// rows of an average length past kSpanLong, so that uneven rows even out), at most
+// sixteen rows of an average length up to `avg16`, eight of longer ones (a
 // row is a block's chain of offsets, values and store; more of them share it,
 // until the spans are long enough by themselves).  Reduce, us with at most 8,
 // 16 and 32: 65 536 rows of mean 203 16.2, 13.5, 17.0, of mean 490 23.2, 23.2,
 // 26.7, of mean 1675 71.0, 74.7, 77.1; 20 000 of mean 489 12.5, 10.8, 9.5; 8192 of
-// mean 917 12.0 with one, 9.7 with two, 8.2 with four.  Broadcast: mean 203 13.4,
-// 12.3, 12.5, mean 490 22.4, 22.8, 23.8.  Eight-byte sums take half, whose LDS
-// slots are twice as large.
-constexpr int64_t kSpanAvg16 = 600, kSpanAvg16Bcast = 300;
+// mean 917 12.0 with one, 9.7 with two, 8.2 with four; 9000 of mean 2379 19.1 with
+// two, 20.8 with three, 23.1 with five.  Broadcast: mean 203 13.4, 12.3, 12.5, mean
+// 490 22.4, 22.8, 23.8.  Eight-byte sums take half, whose LDS slots are twice as
+// large.
+constexpr int64_t kSpanAvg16 = 600, kSpanAvg16Bcast = 300, kSpanLong = 2048;
 int span_rows(int64_t nseg, int64_t nval, int64_t avg16, size_t acc, const DeviceInfo *d) {
     const int64_t most = acc <= 4 && nval <= avg16 * nseg ? kSpanRows : kSpanRows / 2;
-    return (int)std::min(most, ceil_div(nseg, (int64_t)d->num_cus * 8));
+    return (int)std::min(most, ceil_div(nseg, (int64_t)d->num_cus * (nval > kSpanLong * nseg ? 32 : 8)));
 }
 
 template <mx_dtype D, int OP>
