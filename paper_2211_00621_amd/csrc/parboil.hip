@@ -351,9 +351,9 @@ __global__ void __launch_bounds__(NT) k_stencil7(const float *__restrict__ in, f
 // Bound by issue: two transcendental instructions of 8 cycles and five others
 // per pair of sample and voxel.
 //
-// Work split: a block covers 64 V voxels, V per lane; its WS waves take the
-// samples of a tile by fours in turn and their sums are added in wave order
-// through LDS (which V and WS: mx_mriq_f32).
+// Work split: VW groups of WS waves cover 64 V voxels each, V per lane; a group's
+// waves take the samples of a tile by fours in turn and their sums are added in
+// wave order through LDS (which V, WS and VW: mx_mriq_f32).
 constexpr int kMriTile = 1024;
 constexpr float kMriRaw = 250.f;
 
@@ -372,20 +372,22 @@ template <int K> __device__ __forceinline__ void sincos_group(const float (&u)[K
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int V, int WS>
-__global__ void __launch_bounds__(WS *kWave) k_mriq(const float *__restrict__ kx, const float *__restrict__ ky,
+template <int V, int WS, int VW>
+__global__ void __launch_bounds__(WS *VW *kWave) k_mriq(const float *__restrict__ kx, const float *__restrict__ ky,
                                                     const float *__restrict__ kz, const float *__restrict__ phi,
                                                     int64_t nk, const float *__restrict__ x,
                                                     const float *__restrict__ y, const float *__restrict__ z,
                                                     int64_t nv, float *__restrict__ qr, float *__restrict__ qi) {
-    constexpr int BT = WS * kWave;
+    static_assert(WS == 1 || VW == 1, "the sums of one group of waves");
+    constexpr int BT = WS * VW * kWave;
     constexpr int U = 4;  // samples at a time
     __shared__ float4 ks[kMriTile];
-    __shared__ float red[BT * V * 2];
+    __shared__ float red[WS > 1 ? BT * V * 2 : 1];
     __shared__ float kmax[BT / kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t v0 = (int64_t)blockIdx.x * (kWave * V) + lane;
+    const int ws = WS > 1 ? w : 0;  // this wave's place among those that share its voxels
+    const int64_t v0 = ((int64_t)blockIdx.x * VW + (WS > 1 ? 0 : w)) * (kWave * V) + lane;
     float xv[V], yv[V], zv[V], r[V], i[V];
 #pragma unroll
     for (int q = 0; q < V; ++q) {
@@ -416,7 +418,7 @@ __global__ void __launch_bounds__(WS *kWave) k_mriq(const float *__restrict__ kx
 #pragma unroll
         for (int q = 0; q < V; ++q) raw = raw && mx * (fabsf(xv[q]) + fabsf(yv[q]) + fabsf(zv[q])) <= kMriRaw;
         auto tile = [&](auto reduce) {
-            for (int j = w * U; j < pad; j += WS * U) {
+            for (int j = ws * U; j < pad; j += WS * U) {
                 float u[U * V], sn[U * V], cs[U * V], m[U];
 #pragma unroll
                 for (int e = 0; e < U; ++e) {
@@ -441,20 +443,21 @@ __global__ void __launch_bounds__(WS *kWave) k_mriq(const float *__restrict__ kx
         if (__all(raw)) tile(std::false_type{});
         else tile(std::true_type{});
     }
-    // red[wave][2 V][lane]; the first wave adds the waves in order
+    if constexpr (WS > 1) {  // red[wave][2 V][lane]; the first wave adds the waves in order
 #pragma unroll
-    for (int q = 0; q < V; ++q) {
-        red[(w * 2 * V + 2 * q) * kWave + lane] = r[q];
-        red[(w * 2 * V + 2 * q + 1) * kWave + lane] = i[q];
-    }
-    __syncthreads();
-    if (w != 0) return;
-#pragma unroll
-    for (int q = 0; q < V; ++q)
-        for (int o = 1; o < WS; ++o) {
-            r[q] += red[(o * 2 * V + 2 * q) * kWave + lane];
-            i[q] += red[(o * 2 * V + 2 * q + 1) * kWave + lane];
+        for (int q = 0; q < V; ++q) {
+            red[(w * 2 * V + 2 * q) * kWave + lane] = r[q];
+            red[(w * 2 * V + 2 * q + 1) * kWave + lane] = i[q];
         }
+        __syncthreads();
+        if (w != 0) return;
+#pragma unroll
+        for (int q = 0; q < V; ++q)
+            for (int o = 1; o < WS; ++o) {
+                r[q] += red[(o * 2 * V + 2 * q) * kWave + lane];
+                i[q] += red[(o * 2 * V + 2 * q + 1) * kWave + lane];
+            }
+    }
 #pragma unroll
     for (int q = 0; q < V; ++q) {
         const int64_t v = v0 + q * kWave;
@@ -720,13 +723,16 @@ mx_status mx_mriq_f32(const float *kx_dev, const float *ky_dev, const float *kz_
     // the samples dealt to 16 waves, whose sums cost more than they save where
     // the chip is full.  us at 2048 samples, (voxels per lane, waves): 2^18
     // voxels (4,4) 106, (2,4) 116, (1,16) 124, and 160 for two voxels per lane,
-    // one wave and no raised priority; 2^16: 46, 32, 34; 2^14: 44, 27, 12.
-#define MX_MRIQ(V, WS)                                                                                             \
-    hipLaunchKernelGGL((k_mriq<V, WS>), dim3((unsigned)ceil_div(nv, (int64_t)kWave * V)), dim3(WS > 4 ? WS * kWave : NT), \
+    // one wave and no raised priority; 2^16: 46, 32, 34; 2^14: 44, 27, 12.  Few samples
+    // have none for the waves to share: two voxels per lane and a wave each (one
+    // sample, 2^20 voxels: 8.6 us by (4,4); 24 samples 12.4 us, 48 16.8 us against 16.6).
+#define MX_MRIQ(V, WS, VW)                                                                                         \
+    hipLaunchKernelGGL((k_mriq<V, WS, VW>), dim3((unsigned)ceil_div(nv, (int64_t)kWave * V * VW)), dim3(WS * VW * kWave), \
                        0, stream, kx_dev, ky_dev, kz_dev, phi_dev, nk, x_dev, y_dev, z_dev, nv, qr_dev, qi_dev)
-    if (nv >= 3 << 16) MX_MRIQ(4, 4);
-    else if (nv > 1 << 15) MX_MRIQ(2, 4);
-    else MX_MRIQ(1, 16);
+    if (nk <= 16 || (nk <= 40 && nv >= 1 << 19)) MX_MRIQ(2, 1, 4);
+    else if (nv >= 3 << 16) MX_MRIQ(4, 4, 1);
+    else if (nv > 1 << 15) MX_MRIQ(2, 4, 1);
+    else MX_MRIQ(1, 16, 1);
 #undef MX_MRIQ
     return last_launch(who);
 }

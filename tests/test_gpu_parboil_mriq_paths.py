@@ -55,3 +55,11 @@ def test_mriq_large_angle_in_one_tile():
     rr, ri = O.mriq(*k, phi, *[xc[idx] for xc in x])
     b = mriq_bound(k, phi, x, idx)
     assert np.all(np.abs(qr[idx] - rr) <= b) and np.all(np.abs(qi[idx] - ri) <= b)
+
+
+@pytest.mark.parametrize("nv", [1, 511, 513, (1 << 19) - 1, 1 << 19])
+@pytest.mark.parametrize("nk", [1, 4, 16, 17, 40, 41])
+def test_mriq_few_samples(nv, nk):
+    """Too few samples for the waves of a block to share: a wave for each two voxels of its lanes."""
+    test_mriq_splits(nv, nk, 1.0)
+    test_mriq_splits(nv, nk, 40.0)
