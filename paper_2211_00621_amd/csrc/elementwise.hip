@@ -2,11 +2,11 @@
 // Streaming kernels, bound by HBM.  A block takes a contiguous chunk of C x 256
 // 16-byte vectors of every array, all its loads in flight together, and up to
 // 65536 blocks a chunk is all it does, so that the blocks which run together
-// walk each array as one front.  The stores go past the caches, and so do the
-// loads of a pass larger than the memory-side cache.  A slice of any element
-// alignment takes the same path.  2^26 pairs of float32: map2 (805 MB) 160 us ->
-// 126 us (6.4 TB/s), the dot's adjoint (1.07 GB) 211 us -> 174 us (6.2 TB/s),
-// against a vector per thread in a grid-wide stride; 2^20 3.3 us -> 3.0 us.
+// walk each array as one front.  A slice of any element alignment takes the same
+// path.  2^26 pairs of float32: map2 (805 MB) 160 us -> 126 us (6.4 TB/s), the
+// dot's adjoint (1.07 GB) 211 us -> 174 us (6.2 TB/s), against a vector per thread
+// in a grid-wide stride; 2^20 3.3 us -> 3.0 us.  Which caches the accesses pass:
+// pass_mode below.
 #include "mx_internal.h"
 
 namespace mx {
@@ -30,10 +30,30 @@ template <mx_dtype D, bool PAST> __device__ __forceinline__ typename InVec<D>::t
     else return *q;
 }
 
-// Vectors of a block's chunk.  Up to 2^16 vectors one per thread, which spreads
-// a small call over more CUs (2^18 elements of the dot's adjoint 2.4 us with
-// four, 2.3 us with one).
-__host__ __device__ constexpr int64_t chunk_of(int64_t nv) { return nv <= 1 << 16 ? NT : C * NT; }
+// Vectors of a block's chunk (2^18 elements of the dot's adjoint 2.4 us with four
+// per thread, 2.3 us with one).
+__host__ __device__ constexpr int64_t chunk_of(int64_t nv) { return nv <= kSmallPass ? NT : C * NT; }
+
+// How a pass goes by the caches.  us, plain stores, through, past the caches, of the
+// map2 alone and of map, map, map2 on one another's results (float32):
+//   2^20  2.6, 2.3, 2.5;  7.0, 7.1, 6.8       2^21  4.5, 3.4, 4.0;  12.0, 10.9, 12.4
+//   2^22  8.4, 8.5, 8.5;  18.7, 17.8, 20.2    2^24  36, 35, 29;  71.5, 69.6, 77.1
+// and of the dot's adjoint alone: 2^20 3.6, 3.3, 3.1; 2^21 7.2, 4.9, 5.4; 2^23 20.5,
+// 20.5, 20.1; 2^24 49, 48, 39.5.  So the stores of small passes go past the caches,
+// those of larger ones into the memory-side cache alone, where the next call finds
+// them; past its size, and for gradients, whose reader is seldom the next call,
+// past half of it, past all caches; and so do the loads of a pass larger than it.
+enum Mode { STORES_PAST, STORES_THROUGH, ALL_PAST };
+constexpr int64_t kThroughMin = 16 << 20;
+Mode pass_mode(int64_t bytes, bool gradient) {
+    if (bytes > kCacheBytes) return ALL_PAST;
+    return bytes > kThroughMin && bytes < (gradient ? kCacheBytes / 2 : kCacheBytes) ? STORES_THROUGH : STORES_PAST;
+}
+template <Mode M> constexpr bool kPast = M == ALL_PAST;
+template <Mode M, class T> __device__ __forceinline__ void put(uvec<T> v, T *p) {
+    if constexpr (M == STORES_THROUGH) store16_through(v, p);
+    else store16(v, p);
+}
 
 int grid_for(int64_t n, int64_t elems) {
     const int64_t nv = n / elems, g = ceil_div(nv, chunk_of(nv));
@@ -56,7 +76,7 @@ __device__ __forceinline__ void walk_chunks(int64_t n, Full full, Part part, Res
 }
 
 // ---------------------------------------------------------------- map
-template <mx_dtype D, int F, bool PAST>
+template <mx_dtype D, int F, Mode M>
 __global__ void __launch_bounds__(NT) k_map(const typename DT<D>::In *__restrict__ x,
                                             typename DT<D>::Acc *__restrict__ out, int64_t n,
                                             typename DT<D>::Acc p0, typename DT<D>::Acc p1) {
@@ -67,14 +87,14 @@ __global__ void __launch_bounds__(NT) k_map(const typename DT<D>::In *__restrict
         uvec<Acc> r;
 #pragma unroll
         for (int e = 0; e < V; ++e) r[e] = Un<F, Acc>::ap(Acc(v[e]), p0, p1);
-        store16(r, out + V * j);
+        put<M>(r, out + V * j);
     };
     walk_chunks<V>(
         n,
         [&](int64_t j) {
             Vec v[C];
 #pragma unroll
-            for (int u = 0; u < C; ++u) v[u] = load_in<D, PAST>(x + V * (j + u * NT));
+            for (int u = 0; u < C; ++u) v[u] = load_in<D, kPast<M>>(x + V * (j + u * NT));
 #pragma unroll
             for (int u = 0; u < C; ++u) one(v[u], j + u * NT);
         },
@@ -83,7 +103,7 @@ __global__ void __launch_bounds__(NT) k_map(const typename DT<D>::In *__restrict
 }
 
 // ---------------------------------------------------------------- map2
-template <mx_dtype D, int F, bool PAST>
+template <mx_dtype D, int F, Mode M>
 __global__ void __launch_bounds__(NT) k_map2(const typename DT<D>::In *__restrict__ a,
                                              const typename DT<D>::In *__restrict__ b,
                                              typename DT<D>::Acc *out, int64_t n) {
@@ -94,7 +114,7 @@ __global__ void __launch_bounds__(NT) k_map2(const typename DT<D>::In *__restric
         uvec<Acc> r;
 #pragma unroll
         for (int e = 0; e < V; ++e) r[e] = Bin<F, Acc>::ap(Acc(va[e]), Acc(vb[e]));
-        store16(r, out + V * j);
+        put<M>(r, out + V * j);
     };
     walk_chunks<V>(
         n,
@@ -102,8 +122,8 @@ __global__ void __launch_bounds__(NT) k_map2(const typename DT<D>::In *__restric
             Vec va[C], vb[C];
 #pragma unroll
             for (int u = 0; u < C; ++u) {
-                va[u] = load_in<D, PAST>(a + V * (j + u * NT));
-                vb[u] = load_in<D, PAST>(b + V * (j + u * NT));
+                va[u] = load_in<D, kPast<M>>(a + V * (j + u * NT));
+                vb[u] = load_in<D, kPast<M>>(b + V * (j + u * NT));
             }
 #pragma unroll
             for (int u = 0; u < C; ++u) one(va[u], vb[u], j + u * NT);
@@ -113,7 +133,7 @@ __global__ void __launch_bounds__(NT) k_map2(const typename DT<D>::In *__restric
 }
 
 // ---------------------------------------------------------------- dot adjoint
-template <bool PAST>
+template <Mode M>
 __global__ void __launch_bounds__(NT) k_dot_adjoint(const float *__restrict__ a,
                                                     const float *__restrict__ b, int64_t n,
                                                     const float *__restrict__ gout,
@@ -126,18 +146,18 @@ __global__ void __launch_bounds__(NT) k_dot_adjoint(const float *__restrict__ a,
             uvec<float> va[C], vb[C];
 #pragma unroll
             for (int u = 0; u < C; ++u) {
-                if (ga) vb[u] = load16<PAST>(b + 4 * (j + u * NT));
-                if (gb) va[u] = load16<PAST>(a + 4 * (j + u * NT));
+                if (ga) vb[u] = load16<kPast<M>>(b + 4 * (j + u * NT));
+                if (gb) va[u] = load16<kPast<M>>(a + 4 * (j + u * NT));
             }
 #pragma unroll
             for (int u = 0; u < C; ++u) {
-                if (ga) store16(vb[u] * g, ga + 4 * (j + u * NT));
-                if (gb) store16(va[u] * g, gb + 4 * (j + u * NT));
+                if (ga) put<M>(vb[u] * g, ga + 4 * (j + u * NT));
+                if (gb) put<M>(va[u] * g, gb + 4 * (j + u * NT));
             }
         },
         [&](int64_t j) {
-            if (ga) store16(load16<false>(b + 4 * j) * g, ga + 4 * j);
-            if (gb) store16(load16<false>(a + 4 * j) * g, gb + 4 * j);
+            if (ga) put<M>(load16<false>(b + 4 * j) * g, ga + 4 * j);
+            if (gb) put<M>(load16<false>(a + 4 * j) * g, gb + 4 * j);
         },
         [&](int64_t i) {
             if (ga) ga[i] = g * b[i];
@@ -146,6 +166,14 @@ __global__ void __launch_bounds__(NT) k_dot_adjoint(const float *__restrict__ a,
 }
 
 // ---------------------------------------------------------------- dispatch
+template <class Go> void by_mode(Mode m, Go go) {
+    switch (m) {
+    case STORES_PAST: return go(std::integral_constant<Mode, STORES_PAST>{});
+    case STORES_THROUGH: return go(std::integral_constant<Mode, STORES_THROUGH>{});
+    case ALL_PAST: return go(std::integral_constant<Mode, ALL_PAST>{});
+    }
+}
+
 template <mx_dtype D>
 mx_status launch_map(int f, const void *x, int64_t n, const void *params, void *out, hipStream_t s) {
     using In = typename DT<D>::In;
@@ -155,13 +183,15 @@ mx_status launch_map(int f, const void *x, int64_t n, const void *params, void *
         __builtin_memcpy(&p0, params, sizeof(Acc));
         __builtin_memcpy(&p1, (const char *)params + sizeof(Acc), sizeof(Acc));
     }
-    const bool past = n * (int64_t)(sizeof(In) + sizeof(Acc)) > kCacheBytes;
+    const Mode mode = pass_mode(n * (int64_t)(sizeof(In) + sizeof(Acc)), false);
     const int grid = grid_for(n, kElems<D>);
     const In *xi = (const In *)x;
     Acc *o = (Acc *)out;
 #define MX_MAPCASE(F)                                                                       \
     case F:                                                                                 \
-        hipLaunchKernelGGL((past ? k_map<D, F, true> : k_map<D, F, false>), dim3(grid), dim3(NT), 0, s, xi, o, n, p0, p1); \
+        by_mode(mode, [&](auto m) {                                                         \
+            hipLaunchKernelGGL((k_map<D, F, decltype(m)::value>), dim3(grid), dim3(NT), 0, s, xi, o, n, p0, p1); \
+        });                                                                                 \
         break;
     switch (f) {
         MX_MAPCASE(MX_U_ID)
@@ -191,13 +221,18 @@ template <mx_dtype D>
 mx_status launch_map2(int f, const void *a, const void *b, int64_t n, void *out, hipStream_t s) {
     using In = typename DT<D>::In;
     using Acc = typename DT<D>::Acc;
-    const bool past = n * (int64_t)(2 * sizeof(In) + sizeof(Acc)) > kCacheBytes;
+    const Mode mode = pass_mode(n * (int64_t)(2 * sizeof(In) + sizeof(Acc)), false);
     const int grid = grid_for(n, kElems<D>);
     const In *ai = (const In *)a, *bi = (const In *)b;
     Acc *o = (Acc *)out;
-#define MX_MAP2CASE(F)                                                                   \
-    case F:                                                                              \
-        hipLaunchKernelGGL((past ? k_map2<D, F, true> : k_map2<D, F, false>), dim3(grid), dim3(NT), 0, s, ai, bi, o, n); \
+    auto go = [&](auto body) {
+        by_mode(mode, [&](auto m) {
+            hipLaunchKernelGGL((k_map2<D, decltype(body)::value, decltype(m)::value>), dim3(grid), dim3(NT), 0, s, ai, bi, o, n);
+        });
+    };
+#define MX_MAP2CASE(F)                             \
+    case F:                                        \
+        go(std::integral_constant<int, F>{});      \
         break;
     switch (f) {
         MX_MAP2CASE(MX_B_ADD)
@@ -207,8 +242,7 @@ mx_status launch_map2(int f, const void *a, const void *b, int64_t n, void *out,
         MX_MAP2CASE(MX_B_MAX)
     case MX_B_DIV:
         if constexpr (D == MX_F32 || D == MX_F64) {
-            hipLaunchKernelGGL((past ? k_map2<D, MX_B_DIV, true> : k_map2<D, MX_B_DIV, false>), dim3(grid), dim3(NT), 0,
-                               s, ai, bi, o, n);
+            go(std::integral_constant<int, MX_B_DIV>{});
             break;
         } else {
             return set_error(MX_ERR_DTYPE, "mx_map2: division needs a floating-point type");
@@ -273,9 +307,10 @@ mx_status mx_dot_adjoint_f32(const float *a_dev, const float *b_dev, int64_t n,
     MX_REQUIRE(!ga_dev || b_dev, MX_ERR_INVALID, "mx_dot_adjoint_f32: ga needs b");
     MX_REQUIRE(!gb_dev || a_dev, MX_ERR_INVALID, "mx_dot_adjoint_f32: gb needs a");
     if (!ga_dev && !gb_dev) return MX_OK;
-    const bool past = n * (int64_t)sizeof(float) * 2 * ((ga_dev != nullptr) + (gb_dev != nullptr)) > kCacheBytes;
-    hipLaunchKernelGGL(past ? k_dot_adjoint<true> : k_dot_adjoint<false>, dim3(grid_for(n, 4)), dim3(NT), 0, stream,
-                       a_dev, b_dev, n, gout_dev, ga_dev, gb_dev);
+    by_mode(pass_mode(n * (int64_t)sizeof(float) * 2 * ((ga_dev != nullptr) + (gb_dev != nullptr)), true), [&](auto m) {
+        hipLaunchKernelGGL(k_dot_adjoint<decltype(m)::value>, dim3(grid_for(n, 4)), dim3(NT), 0, stream, a_dev, b_dev, n,
+                           gout_dev, ga_dev, gb_dev);
+    });
     return last_launch("mx_dot_adjoint_f32");
 }
 

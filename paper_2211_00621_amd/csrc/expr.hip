@@ -91,6 +91,8 @@ constexpr int kMaxPassBlocks = 65536;
 // flight: four were the fastest with two inputs, and with four inputs, a seed
 // and their results two are what fits the registers of eight waves per SIMD
 int chunk_groups(int nin) { return nin >= 3 ? 2 : 4; }
+// of a small pass one (kSmallPass)
+int chunk_groups(int nin, int64_t groups) { return groups <= kSmallPass ? 1 : chunk_groups(nin); }
 
 bool reads_a(int op) { return op >= MX_X_ADD; }
 bool reads_b(int op) { return op >= MX_X_ADD && op <= MX_X_MAX; }
@@ -236,6 +238,7 @@ std::string gen_source(const mx_expr &e) {
     s += "#define NT " + std::to_string(NT) + "\n#define GPI " + std::to_string(kGroupsPerIt) + "\n";
     s += "#define NIN " + std::to_string(e.nin) + "\n";
     s += "#define CG " + std::to_string(chunk_groups(e.nin)) + "\n";
+    s += "#define MX_CHUNK(nv) ((nv) <= " + std::to_string(kSmallPass) + " ? NT : CG * NT)\n";
     s += "#define SU (NIN >= 4 ? 2 : NIN >= 2 ? 4 : 8)\n";  // 16-byte groups per input in flight per lane
     s += "__device__ __forceinline__ T mx_body(" + in_params + ") {\n#pragma clang fp contract(off)\n" + fwd +
          "    return v" + std::to_string(os) + ";\n}\n";
@@ -276,7 +279,6 @@ __device__ __forceinline__ T mx_body_i(MX_PTRS, long long i) {
 // 2^26 elements (1.07 GB) went from 194 us to 172 us (6.2 TB/s; four groups
 // with plain loads and stores 189 us, one group 181 us, two 178 us); at 2^20
 // from 4.1 us to 3.0 us.
-#define CHUNK (CG * NT)
 template <bool STREAM> __device__ __forceinline__ void mx_map_chunk(MX_PTRS, VT *__restrict__ qo, long long j) {
     VT a[CG][4];
 #pragma unroll
@@ -292,15 +294,15 @@ template <bool STREAM> __device__ __forceinline__ void mx_map_chunk(MX_PTRS, VT 
 
 // out[i] = body(x_i)
 extern "C" __global__ void __launch_bounds__(NT) mx_xmap(MX_PTRS, T *__restrict__ out, long long n, int stream) {
-    const long long nv = n / VW;
+    const long long nv = n / VW, chunk = MX_CHUNK(nv);
     VT *qo = (VT *)out;
-    for (long long c = (long long)blockIdx.x * CHUNK; c < nv; c += (long long)gridDim.x * CHUNK) {
-        const long long j = c + threadIdx.x;
-        if (c + CHUNK <= nv) {
+    for (long long c = (long long)blockIdx.x * chunk; c < nv; c += (long long)gridDim.x * chunk) {
+        const long long j = c + threadIdx.x, end = c + chunk < nv ? c + chunk : nv;
+        if (end - c == CG * NT) {
             if (stream) mx_map_chunk<true>(p0, p1, p2, p3, qo, j);
             else mx_map_chunk<false>(p0, p1, p2, p3, qo, j);
         } else {
-            for (long long i = j; i < nv; i += NT) {
+            for (long long i = j; i < end; i += NT) {
                 VT a[4], r;
                 mx_load_group(p0, p1, p2, p3, i, a);
 #pragma unroll
@@ -351,16 +353,16 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xvjp(MX_PTRS, const T *__res
                                                            T *__restrict__ g3, long long n, int stream) {
     const bool hg = gout != nullptr, hs = gscale != nullptr;
     const T gs = hs ? *gscale : (T)1;
-    const long long nv = n / VW;
+    const long long nv = n / VW, chunk = MX_CHUNK(nv);
     const VT *qg = (const VT *)gout;
     VT *r0 = (VT *)g0, *r1 = (VT *)g1, *r2 = (VT *)g2, *r3 = (VT *)g3;
-    for (long long c = (long long)blockIdx.x * CHUNK; c < nv; c += (long long)gridDim.x * CHUNK) {
-        const long long j = c + threadIdx.x;
-        if (c + CHUNK <= nv) {
+    for (long long c = (long long)blockIdx.x * chunk; c < nv; c += (long long)gridDim.x * chunk) {
+        const long long j = c + threadIdx.x, end = c + chunk < nv ? c + chunk : nv;
+        if (end - c == CG * NT) {
             if (stream) mx_vjp_chunk<true>(p0, p1, p2, p3, qg, hs, gs, r0, r1, r2, r3, j);
             else mx_vjp_chunk<false>(p0, p1, p2, p3, qg, hs, gs, r0, r1, r2, r3, j);
         } else {
-            for (long long i = j; i < nv; i += NT) {
+            for (long long i = j; i < end; i += NT) {
                 VT a[4], go;
                 mx_load_group(p0, p1, p2, p3, i, a);
                 if (hg) go = qg[i];
@@ -609,7 +611,7 @@ int64_t stream_blocks(int64_t n, int vw, int num_cus) {
 
 // blocks of an element-wise pass: one chunk each while they are few enough
 int64_t pass_blocks(int64_t n, int vw, int nin) {
-    const int64_t b = ceil_div(n, (int64_t)NT * vw * chunk_groups(nin));
+    const int64_t b = ceil_div(n, (int64_t)NT * vw * chunk_groups(nin, n / vw));
     return b > kMaxPassBlocks ? kMaxPassBlocks : b;
 }
 

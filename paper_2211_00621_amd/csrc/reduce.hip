@@ -1,13 +1,14 @@
 // reduce op ne s and the fused reduce op ne (map2 f a b) (Appendix A).
 //
-// Two launches.  Partial pass: a block folds contiguous chunks of U x 256
-// 16-byte vectors per operand, all of a chunk in flight, into one accumulator
-// per vector lane, combines its values with the wave64 DPP tree and writes one
-// partial.  Finish pass (one block): folds the partials in block order and
-// applies ne.  The kernel boundary orders the two passes, so no block pays for a
-// device-wide fence.  An input of a few chunks is one block's work, and one
-// launch.  The bracketing depends only on n and the device, so results are
-// bit-identical from run to run, whatever the alignment.
+// Two launches.  Partial pass: a block folds contiguous chunks of U x 256 16-byte
+// vectors per operand (of 256 where the input is small), all of a chunk in flight,
+// into one accumulator per vector lane, and each chunk's into one of all its
+// chunks; it combines them with the wave64 DPP tree and writes one partial.  Finish
+// pass (one block): folds the partials in block order and applies ne.  The kernel
+// boundary orders the two passes, so no block pays for a device-wide fence.  An
+// input of a few chunks is one block's work, and one launch.  The bracketing
+// depends only on n and the device, so results are bit-identical from run to run,
+// whatever the alignment.
 //
 // Bound by HBM; plain loads, which leave the last part of the inputs in the
 // memory-side cache for a reverse pass.  The dot of 2^26 pairs of float32
@@ -28,6 +29,7 @@ constexpr int kMaxBlocks = 4096;
 // 3.6 us by two launches (whose host side is 3 us more); at 2^15 the two are
 // 3.6 us and one block is behind.
 constexpr int64_t kOneBlockChunks = 4;
+__host__ __device__ constexpr int64_t chunk_of(int64_t nv) { return nv <= kSmallPass ? NT : U * NT; }
 
 // F < 0: plain reduce of a; otherwise element = Bin<F>(a[i], b[i]).
 template <mx_dtype D, int OP, int F> struct Elem {
@@ -53,17 +55,19 @@ __global__ void __launch_bounds__(NT) k_reduce(const typename DT<D>::In *__restr
     constexpr bool TWO = F >= 0;
     __shared__ Acc smem[NT / kWave];
 
-    Acc acc[V];
+    Acc acc[V], sum[V];
 #pragma unroll
-    for (int j = 0; j < V; ++j) acc[j] = R::id();
+    for (int j = 0; j < V; ++j) sum[j] = R::id();
     auto fold = [&](const uvec<In> &va, const uvec<In> &vb) {
 #pragma unroll
         for (int j = 0; j < V; ++j) acc[j] = R::ap(acc[j], E::at(va[j], TWO ? vb[j] : In(0)));
     };
-    const int64_t nv = n / V;
-    for (int64_t c = (int64_t)blockIdx.x * (U * NT); c < nv; c += (int64_t)gridDim.x * (U * NT)) {
-        const int64_t i = c + threadIdx.x;
-        if (c + U * NT <= nv) {
+    const int64_t nv = n / V, chunk = direct ? U * NT : chunk_of(nv);
+    for (int64_t c = (int64_t)blockIdx.x * chunk; c < nv; c += (int64_t)gridDim.x * chunk) {
+        const int64_t i = c + threadIdx.x, end = c + chunk < nv ? c + chunk : nv;
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc[j] = R::id();
+        if (end - c == U * NT) {
             uvec<In> va[U], vb[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -73,17 +77,19 @@ __global__ void __launch_bounds__(NT) k_reduce(const typename DT<D>::In *__restr
 #pragma unroll
             for (int u = 0; u < U; ++u) fold(va[u], vb[u]);
         } else {
-            for (int64_t j = i; j < nv; j += NT) {
+            for (int64_t j = i; j < end; j += NT) {
                 const uvec<In> va = load16<false>(a + V * j);
                 fold(va, TWO ? load16<false>(b + V * j) : va);
             }
         }
+#pragma unroll
+        for (int j = 0; j < V; ++j) sum[j] = R::ap(sum[j], acc[j]);
     }
     const int64_t i = nv * V + threadIdx.x;  // the last n % V elements
-    if (blockIdx.x == gridDim.x - 1 && i < n) acc[0] = R::ap(acc[0], E::at(a[i], TWO ? b[i] : In(0)));
-    Acc t = acc[0];
+    if (blockIdx.x == gridDim.x - 1 && i < n) sum[0] = R::ap(sum[0], E::at(a[i], TWO ? b[i] : In(0)));
+    Acc t = sum[0];
 #pragma unroll
-    for (int j = 1; j < V; ++j) t = R::ap(t, acc[j]);
+    for (int j = 1; j < V; ++j) t = R::ap(t, sum[j]);
     t = block_reduce<R, NT>(t, smem);
     if (threadIdx.x == 0) partials[blockIdx.x] = direct ? R::ap(ne, t) : t;
 }
@@ -115,9 +121,8 @@ mx_status launch(const void *a, const void *b, int64_t n, const void *ne_host, v
     using Acc = typename DT<D>::Acc;
     Acc ne;
     __builtin_memcpy(&ne, ne_host, sizeof(Acc));
-    int64_t grid = ceil_div(n > 0 ? n : 1, (int64_t)NT * U * DT<D>::kVec);
-    const int64_t cap = std::min<int64_t>((int64_t)dev->num_cus * 8, kMaxBlocks);
-    grid = grid <= kOneBlockChunks ? 1 : std::min(grid, cap);
+    const int64_t nv = n / DT<D>::kVec, cap = std::min<int64_t>((int64_t)dev->num_cus * 8, kMaxBlocks);
+    const int64_t grid = nv <= kOneBlockChunks * U * NT ? 1 : std::min(ceil_div(nv, chunk_of(nv)), cap);
     const int direct = grid == 1;
     Acc *partials = direct ? (Acc *)out : (Acc *)((char *)ws + kCounterBytes);
     hipLaunchKernelGGL((k_reduce<D, OP, F>), dim3((unsigned)grid), dim3(NT), 0, s, (const In *)a,

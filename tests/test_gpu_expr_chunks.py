@@ -108,3 +108,12 @@ def test_past_the_cache():
     abi.mx_expr_map_reduce(e, abi.MX_ADD, ds, n, 0.0, r, ws)
     v = (a * b + c) * d
     check_scalar(float(host(r)), float(v.sum()), float(np.abs(v).sum()), n, what="past the cache")
+
+
+@pytest.mark.parametrize("vectors,more", [(511, 3), (512, 0), (513, 1), (1 << 17, 0), ((1 << 17) + 1, 1), ((1 << 17) + 1500, 3)])
+@pytest.mark.parametrize("dtype", [abi.MX_F32, abi.MX_F64])
+@pytest.mark.parametrize("name", ["two", "four"])
+def test_small_pass_edges(name, dtype, vectors, more):
+    """Passes of one vector per thread, up to 2^17 vectors, and the first past them."""
+    width = 4 if dtype == abi.MX_F32 else 2
+    test_chunk_edges(name, dtype, vectors * width + more % width, 1)

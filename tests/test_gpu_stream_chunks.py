@@ -115,3 +115,41 @@ def test_past_the_cache(kind):
         (ta, ga), (tb, gb) = guarded(n, np.float32, 1), guarded(n, np.float32, 1)
         abi.mx_dot_adjoint_f32(da, db, g, ga, gb)
         assert np.array_equal(whole(ta, n, 1), np.float32(-1.5) * b) and np.array_equal(whole(tb, n, 1), np.float32(-1.5) * a)
+
+
+@pytest.mark.parametrize("n", [(1 << 19) - 1, (1 << 19) + 3, (1 << 19) + 4099, (1 << 21) - 1, (1 << 21) + 5, (1 << 23) - 3,
+                               (1 << 23) + 3, (1 << 25) - 1])
+@pytest.mark.parametrize("kind", ["f32", "i32", "f64"])
+def test_read_back(kind, n):
+    """On both sides of the passes' one vector per thread (2^17 vectors) and of each way of storing (16 MB, half the
+    memory-side cache and all of it): a pass reduced by the next, in place, and the dot's adjoint; nothing outside."""
+    say("stream read back", kind, n)
+    acc = TYPES[kind][1]
+    a, b = make("i32", n, 8) % 1000, make("i32", n, 9) % 1000  # whole numbers: every result and sum below 2^53 is exact
+    a, b = a.astype(TYPES[kind][0]), b.astype(TYPES[kind][0])
+    da, db = slice_of(a, 1), slice_of(b, 1)
+    t, o = guarded(n, acc, 1)
+    ws = torch.zeros(abi.mx_workspace_bytes(abi.MX_WS_REDUCE, n, 0), dtype=torch.uint8, device="cuda")
+    r = torch.zeros(2, dtype=o.dtype, device="cuda")
+    abi.mx_map2(abi.MX_B_SUB, da, db, o)
+    abi.mx_reduce(abi.MX_MAX, o, -5000, r[:1], ws)
+    if kind == "f32":
+        abi.mx_map(abi.MX_U_SQ, o, None, o)
+    else:
+        abi.mx_map2(abi.MX_B_MUL, o, o, o)
+    abi.mx_reduce(abi.MX_ADD, o, 0, r[1:], ws)
+    want = a.astype(acc) - b.astype(acc)
+    got = r.cpu().numpy()
+    assert got[0] == want.max()
+    want = want * want
+    assert np.array_equal(whole(t, n, 1), want)
+    total = want.astype(np.float64).sum() if kind[0] == "f" else want.sum()
+    if kind == "f32":  # a chain of at most n additions
+        assert abs(got[1] - total) <= n * 2.0 ** -24 * total
+    else:
+        assert got[1] == total
+    if kind == "f32":
+        g = torch.tensor([0.5], device="cuda")
+        (ta, ga), (tb, gb) = guarded(n, np.float32, 1), guarded(n, np.float32, 1)
+        abi.mx_dot_adjoint_f32(da, db, g, ga, gb)
+        assert np.array_equal(whole(ta, n, 1), np.float32(0.5) * b) and np.array_equal(whole(tb, n, 1), np.float32(0.5) * a)
