@@ -1047,8 +1047,17 @@ __global__ void __launch_bounds__(NT) k_kmeans_divide_plain(const float *__restr
 // vectors each took 30 us and 45 us.
 constexpr int SNT = 512;  // 1024 blocks (the partials' room) of it fill every CU
 constexpr int kSseVec = 2;
-constexpr int kSseChunk = 4 * kSseVec * SNT;  // elements; a vector per thread up to 2^20 elements
-int64_t sse_chunk_of(int64_t total) { return total <= 1 << 20 ? 4 * SNT : kSseChunk; }
+constexpr int kSseChunk = 4 * kSseVec * SNT;  // elements
+// A small pass: blocks of NT threads, a vector per thread (kSmallPass: the other
+// passes' chunks), up to half as much an element per thread where d is no
+// multiple of four and a vector's elements need a point each (10 000 elements of
+// two dimensions: gradient 2.6 us by vectors, 2.0 us).  The sum of up to kSseOne
+// elements is one block's, and one launch (100 points of 16: two launches 1.9 times
+// as long).
+constexpr int64_t kSseOne = 4 * SNT;
+int64_t sse_chunk_of(int64_t total, int d) {
+    return total <= 2 * kSmallPass && d % 4 != 0 ? NT : total <= 4 * kSmallPass ? 4 * NT : kSseChunk;
+}
 
 struct SseArgs {
     const float *X, *C;
@@ -1060,7 +1069,7 @@ struct SseArgs {
 
 SseArgs sse_args(const float *X, int64_t n, int d, const float *C, const int32_t *labels) {
     const uint64_t ud = (uint64_t)d;
-    return SseArgs{X, C, labels, n * d, sse_chunk_of(n * d), (uint32_t)d, d > 1 ? (uint32_t)(0x100000000ull / ud + 1) : 0u, ~0ull / ud};
+    return SseArgs{X, C, labels, n * d, sse_chunk_of(n * d, d), (uint32_t)d, d > 1 ? (uint32_t)(0x100000000ull / ud + 1) : 0u, ~0ull / ud};
 }
 
 // Where a chunk lies: its first point (64-bit reciprocal: the estimate is at
@@ -1098,9 +1107,9 @@ template <bool V4> __device__ __forceinline__ uvec<float> sse_c4(const SseArgs &
 // Partial sums of (x - c_label)^2, one per block; of a single block the result.
 // V4: the next chunk's points and labels are in flight while this one's
 // centroid values are fetched and folded.
-template <bool V4>
-__global__ void __launch_bounds__(SNT) k_sse_partial(SseArgs a, float *__restrict__ part) {
-    __shared__ float red[SNT / kWave];
+template <bool V4, int T>
+__global__ void __launch_bounds__(T) k_sse_partial(SseArgs a, float *__restrict__ part) {
+    __shared__ float red[T / kWave];
     uvec<float> acc = {0.f, 0.f, 0.f, 0.f};
     const int64_t step = (int64_t)gridDim.x * a.chunk;
     int64_t e0 = (int64_t)blockIdx.x * a.chunk;
@@ -1108,7 +1117,7 @@ __global__ void __launch_bounds__(SNT) k_sse_partial(SseArgs a, float *__restric
         const uvec<float> q = x - c;
         acc += q * q;
     };
-    if constexpr (V4) {
+    if constexpr (V4 && T == SNT) {
         uvec<float> x[kSseVec];
         int l[kSseVec];
         uint32_t o[kSseVec];
@@ -1139,15 +1148,15 @@ __global__ void __launch_bounds__(SNT) k_sse_partial(SseArgs a, float *__restric
     }
     for (; e0 < a.total; e0 += step) {
         const SseAt at = sse_at(a, e0);
-        const uint32_t nv = at.left >> 2, t = 4 * nv + threadIdx.x;
+        const uint32_t nv = !V4 && a.chunk == T ? 0 : at.left >> 2, t = 4 * nv + threadIdx.x;
 #pragma unroll 2
-        for (uint32_t i = threadIdx.x; i < nv; i += SNT) fold(load16<false>(at.x + 4 * i), sse_c4<V4>(a, at, 4 * i));
+        for (uint32_t i = threadIdx.x; i < nv; i += T) fold(load16<false>(at.x + 4 * i), sse_c4<V4>(a, at, 4 * i));
         if (t < at.left) {
             const float q = at.x[t] - sse_c1(a, at, t);
             acc[0] += q * q;
         }
     }
-    const float s = block_reduce<Red<MX_ADD, float>, SNT>((acc[0] + acc[1]) + (acc[2] + acc[3]), red);
+    const float s = block_reduce<Red<MX_ADD, float>, T>((acc[0] + acc[1]) + (acc[2] + acc[3]), red);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
@@ -1159,13 +1168,13 @@ __global__ void __launch_bounds__(NT) k_sse_final(const float *__restrict__ part
     if (threadIdx.x == 0) out[0] = (float)acc;
 }
 
-template <bool V4, bool PAST>
-__global__ void __launch_bounds__(SNT) k_sse_grad(SseArgs a, const float *__restrict__ gscale, float *__restrict__ G) {
+template <bool V4, bool PAST, int T>
+__global__ void __launch_bounds__(T) k_sse_grad(SseArgs a, const float *__restrict__ gscale, float *__restrict__ G) {
     const float g2 = 2.0f * gscale[0];
     for (int64_t e0 = (int64_t)blockIdx.x * a.chunk; e0 < a.total; e0 += (int64_t)gridDim.x * a.chunk) {
         const SseAt at = sse_at(a, e0);
         float *go = G + e0;
-        if (at.left == kSseChunk) {
+        if (T == SNT && at.left == kSseChunk) {
             uvec<float> x[kSseVec], c[kSseVec];
 #pragma unroll
             for (int u = 0; u < kSseVec; ++u) x[u] = load16<PAST>(at.x + 4 * (threadIdx.x + u * SNT));
@@ -1174,8 +1183,8 @@ __global__ void __launch_bounds__(SNT) k_sse_grad(SseArgs a, const float *__rest
 #pragma unroll
             for (int u = 0; u < kSseVec; ++u) store16(g2 * (x[u] - c[u]), go + 4 * (threadIdx.x + u * SNT));
         } else {
-            const uint32_t nv = at.left >> 2, t = 4 * nv + threadIdx.x;
-            for (uint32_t i = threadIdx.x; i < nv; i += SNT)
+            const uint32_t nv = !V4 && a.chunk == T ? 0 : at.left >> 2, t = 4 * nv + threadIdx.x;
+            for (uint32_t i = threadIdx.x; i < nv; i += T)
                 store16(g2 * (load16<false>(at.x + 4 * i) - sse_c4<V4>(a, at, 4 * i)), go + 4 * i);
             if (t < at.left) go[t] = g2 * (at.x[t] - sse_c1(a, at, t));
         }
@@ -1358,10 +1367,15 @@ mx_status mx_kmeans_sse_f32(const float *X_dev, int64_t n, int d, const float *C
     MX_REQUIRE(ws && ws_bytes >= need && ((uintptr_t)ws & 255) == 0, MX_ERR_WORKSPACE,
                "%s: workspace needs %zu bytes, 256-byte aligned", who, need);
     float *part = (float *)((char *)ws + kCounterBytes);
-    const int nb = (int)std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(n * d, sse_chunk_of(n * d))));
-    const SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
-    hipLaunchKernelGGL(d % 4 == 0 ? k_sse_partial<true> : k_sse_partial<false>, dim3(nb), dim3(SNT), 0, stream, a,
-                       nb == 1 ? sse_dev : part);
+    SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
+    if (a.total <= kSseOne) a.chunk = kSseOne;
+    const int nb = (int)std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(a.total, a.chunk)));
+    const bool small = a.chunk < kSseOne;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(small ? NT : SNT), 0, stream, a, nb == 1 ? sse_dev : part);
+    };
+    if (d % 4 == 0) small ? go(k_sse_partial<true, NT>) : go(k_sse_partial<true, SNT>);
+    else small ? go(k_sse_partial<false, NT>) : go(k_sse_partial<false, SNT>);
     if (nb > 1) hipLaunchKernelGGL(k_sse_final, dim3(1), dim3(NT), 0, stream, part, nb, sse_dev);
     return last_launch(who);
 }
@@ -1375,10 +1389,14 @@ mx_status mx_kmeans_sse_grad_f32(const float *X_dev, int64_t n, int d, const flo
     MX_REQUIRE(X_dev && C_dev && labels_dev && gscale_dev && G_dev, MX_ERR_INVALID, "%s: null pointer", who);
     const SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
     const bool past = n * d * 2 * (int64_t)sizeof(float) > kCacheBytes;
-    const unsigned grid = (unsigned)std::min<int64_t>(65536, ceil_div(n * d, sse_chunk_of(n * d)));
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(SNT), 0, stream, a, gscale_dev, G_dev); };
-    if (d % 4 == 0) past ? go(k_sse_grad<true, true>) : go(k_sse_grad<true, false>);
-    else past ? go(k_sse_grad<false, true>) : go(k_sse_grad<false, false>);
+    const unsigned grid = (unsigned)std::min<int64_t>(65536, ceil_div(n * d, a.chunk));
+    const bool small = a.chunk < kSseChunk;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(small ? NT : SNT), 0, stream, a, gscale_dev, G_dev);
+    };
+    if (small) d % 4 == 0 ? go(k_sse_grad<true, false, NT>) : go(k_sse_grad<false, false, NT>);
+    else if (d % 4 == 0) past ? go(k_sse_grad<true, true, SNT>) : go(k_sse_grad<true, false, SNT>);
+    else past ? go(k_sse_grad<false, true, SNT>) : go(k_sse_grad<false, false, SNT>);
     return last_launch(who);
 }
 

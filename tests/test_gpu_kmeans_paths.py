@@ -118,3 +118,11 @@ def test_gradient_past_the_cache():
     abi.mx_kmeans_sse_grad_f32(torch.from_numpy(X).cuda(), torch.from_numpy(C).cuda(), torch.from_numpy(lab).cuda(),
                                torch.tensor([0.5], device="cuda"), G)
     assert np.array_equal(G.cpu().numpy(), X - C[lab])
+
+
+@pytest.mark.parametrize("n,d", [(683, 3), (682, 3), (1024, 2), (1025, 2), (2047, 1), (2049, 1), (512, 4), (513, 4), (257, 8),
+                                 (87381, 3), (87382, 3), (262144, 1), (262145, 1), (131072, 4), (131073, 4), (262143, 2),
+                                 (262145, 2)])
+def test_small_sse_edges(n, d):
+    """Sums of one block (2048 elements), an element per thread (2^18) and a vector (2^19), and the first past each."""
+    test_sse_and_gradient(n, d, 1)
