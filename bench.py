@@ -53,39 +53,39 @@ FP32_VALU_PEAK_TFLOPS = 157.3  # MI355X FP32 vector
 # taken: once that file changes the figure no longer describes the kernel and
 # the bench reports null.
 TRAFFIC = {
-    # k_gemm_mfma<128,128,4,4,TA,TB>, 2048^3, each transpose: 100.77 MB fetched + 16.78 MB written.
+    # k_gemm_mfma<128,128,4,4,TA,TB>, 2048^3, each transpose: 100.74 MB fetched + 16.78 MB written.
     # Each XCD's L2 fetches the A row panels and B column panels of its own 32 tiles (4 x 8 of them:
     # 12 panels of 1 MiB, the fewest 32 tiles can need), so each A panel is fetched by two XCDs and
     # each B panel by four; the algorithmic minimum is 33.6 MB read + 16.8 MB written (2.34x)
-    "gemm_nn": {"file": "gemm.hip", "bytes": 117518329,
-                "source": "9d864bd422699980a0cb2bb5a66c83d3fa62ace401ef55575768a0cb684a8318"},
-    "gemm_nt": {"file": "gemm.hip", "bytes": 117508090,
-                "source": "9d864bd422699980a0cb2bb5a66c83d3fa62ace401ef55575768a0cb684a8318"},
-    "gemm_tn": {"file": "gemm.hip", "bytes": 117514233,
-                "source": "9d864bd422699980a0cb2bb5a66c83d3fa62ace401ef55575768a0cb684a8318"},
-    # k_seg_span (row-span path, nontemporal loads), 65536 rows / 32.1 M values: 132.46 MB fetched + 0.26 MB
+    "gemm_nn": {"file": "gemm.hip", "bytes": 117517025,
+                "source": "ec0d76388112add1b95513576a3af1d8dfe92d5045531e1d294820495ee0ec31"},
+    "gemm_nt": {"file": "gemm.hip", "bytes": 117506786,
+                "source": "ec0d76388112add1b95513576a3af1d8dfe92d5045531e1d294820495ee0ec31"},
+    "gemm_tn": {"file": "gemm.hip", "bytes": 117512929,
+                "source": "ec0d76388112add1b95513576a3af1d8dfe92d5045531e1d294820495ee0ec31"},
+    # k_seg_span (row-span path, nontemporal loads), 65536 rows / 32.1 M values: 132.43 MB fetched + 0.26 MB
     # written (1.03x algorithmic: 129.19 MB)
-    "seg_span": {"file": "segmented.hip", "bytes": 132718721,
-                 "source": "a3c56bd4f33368dfc7fbafe501633bb8c18c298201b3dc913b0477a524f48603"},
+    "seg_span": {"file": "segmented.hip", "bytes": 132694703,
+                 "source": "5471d8a0b87aff6e90231e21de4911ac3b88e31e11f7af36b072bf82584cec0a"},
     # mx_xvjp (generated from expr.hip) for exp(-(a-b)^2)*0.5 + a*b over 2^26 float32 pairs:
-    # 536.92 MB fetched + 536.87 MB written (1.00x algorithmic)
-    "expr_vjp": {"file": "expr.hip", "bytes": 1073796731,
-                 "source": "e9c60cbd040d338763634b52a9c29e55deaa99904b421b9e6dce4228f185b618"},
+    # 536.94 MB fetched + 536.99 MB written (1.00x algorithmic)
+    "expr_vjp": {"file": "expr.hip", "bytes": 1073925745,
+                 "source": "72ab392dffebd016e2a1d2c5ee2860bbad5b6511fc910bf24a8896f6a243e399"},
     # mx_xseg_add, same body over the nested step's 65 536 ragged rows (2 x 32.1 M values):
-    # 262.30 MB fetched + 0.26 MB written (1.02x algorithmic)
-    "expr_seg": {"file": "expr.hip", "bytes": 262557234,
-                 "source": "e9c60cbd040d338763634b52a9c29e55deaa99904b421b9e6dce4228f185b618"},
-    # k_stencil7, 512 x 512 x 64 float32: 73.15 MB fetched (1.09x: a 16-plane slab re-reads the planes
+    # 261.30 MB fetched + 0.26 MB written (1.02x algorithmic)
+    "expr_seg": {"file": "expr.hip", "bytes": 261565657,
+                 "source": "72ab392dffebd016e2a1d2c5ee2860bbad5b6511fc910bf24a8896f6a243e399"},
+    # k_stencil7, 512 x 512 x 64 float32: 73.16 MB fetched (1.09x: a 16-plane slab re-reads the planes
     # below and above it) + 67.10 MB written
-    "stencil": {"file": "parboil.hip", "bytes": 140279381,
-                "source": "e36e32c421864034d324bbbbb984f2f6d0576c348c596ce47b74d91d3db139a8"},
-    # k_kmeans_fused<32,64,true,false>, 2^20 x 32 points, k = 64: 134.68 MB fetched (X, 1.00x) + 12.11 MB written
+    "stencil": {"file": "parboil.hip", "bytes": 140263158,
+                "source": "b4bccd849aa63dc0ff606221add7470ce4f7f0202bed4ed3f9a0b3ce249742b8"},
+    # k_kmeans_fused<32,64,true,false>, 2^20 x 32 points, k = 64: 134.67 MB fetched (X, 1.00x) + 12.10 MB written
     # (labels, and 768 block partials stored in 32-byte entry groups)
-    "kmeans": {"file": "kmeans.hip", "bytes": 146786934,
-               "source": "ec01a774a80e29f06308a52e4004bd887d9e4bb55e86ac331c1d0a6e1e7d5517"},
-    # k_seg_broadcast (row-span path): 2.66 MB fetched (offsets, gradients) + 128.71 MB written
-    "seg_broadcast": {"file": "segmented.hip", "bytes": 131377964,
-                      "source": "a3c56bd4f33368dfc7fbafe501633bb8c18c298201b3dc913b0477a524f48603"},
+    "kmeans": {"file": "kmeans.hip", "bytes": 146770890,
+               "source": "8628776931a21c68cde289781a5d5dfc5a3698a3a24d5721b9bc3237cfc2483c"},
+    # k_seg_broadcast (row-span path): 2.66 MB fetched (offsets, gradients) + 128.70 MB written
+    "seg_broadcast": {"file": "segmented.hip", "bytes": 131364569,
+                      "source": "5471d8a0b87aff6e90231e21de4911ac3b88e31e11f7af36b072bf82584cec0a"},
 }
 
 
@@ -823,8 +823,9 @@ def bench_kmeans(args):
                      "achieved": round(gbs(4 * n * d + 4 * n, parts["kmeans_step"]), 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(gbs(4 * n * d + 4 * n, parts["kmeans_step"]) / HBM_PEAK_GBS, 4),
                      "traffic": traffic_of("kmeans"),
-                     "limit": "VALU issue: ~1100 vector instructions per 64-point chunk (bfloat16 split, "
-                              "candidate selection, certification, reduce-by-key), three waves per SIMD",
+                     "limit": "VALU issue of ~1100 vector instructions per 64-point chunk (bfloat16 split, candidate "
+                              "selection, certification, reduce-by-key) about half of the kernel, then prologue, "
+                              "epilogue and an uneven last round of chunks",
                      "fp32_equivalent": {"TFLOP/s": round(ach, 2), "of_fp32_mfma_peak": round(ach / FP32_MFMA_PEAK_TFLOPS, 4),
                                          "what": "2nkd flops of the x.c products over the step's time, against the "
                                                  "FP32 matrix peak (the former FP32 16x16x4 kernel's bound)"}},
