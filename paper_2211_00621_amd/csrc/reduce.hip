@@ -25,10 +25,7 @@ namespace {
 constexpr int NT = 256;
 constexpr int U = 4;
 constexpr int kMaxBlocks = 4096;
-// Chunks that one block folds alone, in one launch: 2^14 pairs 3.0 us against
-// 3.6 us by two launches (whose host side is 3 us more); at 2^15 the two are
-// 3.6 us and one block is behind.
-constexpr int64_t kOneBlockChunks = 4;
+constexpr int NT1 = 1024;  // threads of a block that folds a small input alone
 __host__ __device__ constexpr int64_t chunk_of(int64_t nv) { return nv <= kSmallPass ? NT : U * NT; }
 
 // F < 0: plain reduce of a; otherwise element = Bin<F>(a[i], b[i]).
@@ -41,11 +38,51 @@ template <mx_dtype D, int OP, int F> struct Elem {
     }
 };
 
-// direct != 0: the only block; partials is the output
+// A small input by one block, in one launch (the host side of a second is 3 us):
+// up to U vectors per thread and operand, all in flight, since an input that the
+// call before has written past the caches takes a round trip to memory (2^14
+// floats, map then sum: four rounds of a block of 256 threads 5.9 us, now 4.1 us, two
+// launches 5.4 us).
+template <mx_dtype D, int OP, int F, int T>
+__global__ void __launch_bounds__(T) k_reduce_one(const typename DT<D>::In *__restrict__ a,
+                                                  const typename DT<D>::In *__restrict__ b, int n,
+                                                  typename DT<D>::Acc ne, typename DT<D>::Acc *__restrict__ out) {
+    using In = typename DT<D>::In;
+    using Acc = typename DT<D>::Acc;
+    using R = Red<OP, Acc>;
+    using E = Elem<D, OP, F>;
+    constexpr int V = DT<D>::kVec;
+    constexpr bool TWO = F >= 0;
+    __shared__ Acc smem[T / kWave];
+    const int nv = n / V, t = threadIdx.x;
+    uvec<In> va[U], vb[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (t + u * T < nv) {
+            va[u] = load16<false>(a + V * (t + u * T));
+            if constexpr (TWO) vb[u] = load16<false>(b + V * (t + u * T));
+        }
+    const int i = nv * V + t;  // the last n % V elements
+    const In ta = i < n ? a[i] : In(0), tb = TWO && i < n ? b[i] : In(0);
+    Acc acc[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) acc[j] = R::id();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (t + u * T < nv)
+#pragma unroll
+            for (int j = 0; j < V; ++j) acc[j] = R::ap(acc[j], E::at(va[u][j], TWO ? vb[u][j] : In(0)));
+    if (i < n) acc[0] = R::ap(acc[0], E::at(ta, tb));
+    Acc r = acc[0];
+#pragma unroll
+    for (int j = 1; j < V; ++j) r = R::ap(r, acc[j]);
+    r = block_reduce<R, T>(r, smem);
+    if (t == 0) out[0] = R::ap(ne, r);
+}
+
 template <mx_dtype D, int OP, int F>
 __global__ void __launch_bounds__(NT) k_reduce(const typename DT<D>::In *__restrict__ a,
                                                const typename DT<D>::In *__restrict__ b, int64_t n,
-                                               typename DT<D>::Acc ne, int direct,
                                                typename DT<D>::Acc *__restrict__ partials) {
     using In = typename DT<D>::In;
     using Acc = typename DT<D>::Acc;
@@ -62,7 +99,9 @@ __global__ void __launch_bounds__(NT) k_reduce(const typename DT<D>::In *__restr
 #pragma unroll
         for (int j = 0; j < V; ++j) acc[j] = R::ap(acc[j], E::at(va[j], TWO ? vb[j] : In(0)));
     };
-    const int64_t nv = n / V, chunk = direct ? U * NT : chunk_of(nv);
+    const int64_t nv = n / V, chunk = chunk_of(nv), tail = nv * V + threadIdx.x;
+    const bool last = blockIdx.x == gridDim.x - 1 && tail < n;  // one of the last n % V elements
+    const In ta = last ? a[tail] : In(0), tb = TWO && last ? b[tail] : In(0);
     for (int64_t c = (int64_t)blockIdx.x * chunk; c < nv; c += (int64_t)gridDim.x * chunk) {
         const int64_t i = c + threadIdx.x, end = c + chunk < nv ? c + chunk : nv;
 #pragma unroll
@@ -85,13 +124,12 @@ __global__ void __launch_bounds__(NT) k_reduce(const typename DT<D>::In *__restr
 #pragma unroll
         for (int j = 0; j < V; ++j) sum[j] = R::ap(sum[j], acc[j]);
     }
-    const int64_t i = nv * V + threadIdx.x;  // the last n % V elements
-    if (blockIdx.x == gridDim.x - 1 && i < n) sum[0] = R::ap(sum[0], E::at(a[i], TWO ? b[i] : In(0)));
+    if (last) sum[0] = R::ap(sum[0], E::at(ta, tb));
     Acc t = sum[0];
 #pragma unroll
     for (int j = 1; j < V; ++j) t = R::ap(t, sum[j]);
     t = block_reduce<R, NT>(t, smem);
-    if (threadIdx.x == 0) partials[blockIdx.x] = direct ? R::ap(ne, t) : t;
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
 // one block: out = ne (op) (partial_0 (op) ... (op) partial_{nb-1}), strided
@@ -121,13 +159,17 @@ mx_status launch(const void *a, const void *b, int64_t n, const void *ne_host, v
     using Acc = typename DT<D>::Acc;
     Acc ne;
     __builtin_memcpy(&ne, ne_host, sizeof(Acc));
-    const int64_t nv = n / DT<D>::kVec, cap = std::min<int64_t>((int64_t)dev->num_cus * 8, kMaxBlocks);
-    const int64_t grid = nv <= kOneBlockChunks * U * NT ? 1 : std::min(ceil_div(nv, chunk_of(nv)), cap);
-    const int direct = grid == 1;
-    Acc *partials = direct ? (Acc *)out : (Acc *)((char *)ws + kCounterBytes);
-    hipLaunchKernelGGL((k_reduce<D, OP, F>), dim3((unsigned)grid), dim3(NT), 0, s, (const In *)a,
-                       (const In *)b, n, ne, direct, partials);
-    if (direct) return last_launch("reduce");
+    const In *x = (const In *)a, *y = (const In *)b;
+    const int64_t nv = n / DT<D>::kVec;
+    auto one = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), 0, s, x, y, (int)n, ne, (Acc *)out);
+        return last_launch("reduce");
+    };
+    if (nv <= U * NT) return one(k_reduce_one<D, OP, F, NT>, NT);
+    if (nv <= U * NT1) return one(k_reduce_one<D, OP, F, NT1>, NT1);
+    const int64_t grid = std::min<int64_t>(ceil_div(nv, chunk_of(nv)), std::min<int64_t>((int64_t)dev->num_cus * 8, kMaxBlocks));
+    Acc *partials = (Acc *)((char *)ws + kCounterBytes);
+    hipLaunchKernelGGL((k_reduce<D, OP, F>), dim3((unsigned)grid), dim3(NT), 0, s, x, y, n, partials);
     if (mx_status st = last_launch("reduce")) return st;
     hipLaunchKernelGGL((k_reduce_finish<D, OP>), dim3(1), dim3(NT), 0, s, (const Acc *)partials, (int)grid, ne,
                        (Acc *)out);

@@ -153,3 +153,11 @@ def test_read_back(kind, n):
         (ta, ga), (tb, gb) = guarded(n, np.float32, 1), guarded(n, np.float32, 1)
         abi.mx_dot_adjoint_f32(da, db, g, ga, gb)
         assert np.array_equal(whole(ta, n, 1), np.float32(0.5) * b) and np.array_equal(whole(tb, n, 1), np.float32(0.5) * a)
+
+
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("vectors", [255, 256, 257, 1023, 1024, 1025, 2048, 4095, 4096, 4097, 8193])
+@pytest.mark.parametrize("kind", list(TYPES))
+def test_one_block(kind, vectors, more):
+    """Reductions of one block of 256 threads (1024 vectors), of 1024 (4096), and of two launches."""
+    test_chunk_edges(kind, vectors * (2 if kind.endswith("64") else 4) + more, 1)
