@@ -85,7 +85,7 @@ constexpr int kRegs = 16, kMaxInsn = 64, kMaxIn = 4;
 constexpr int NT = 256;          // threads per block of every generated kernel
 constexpr int kGroupsPerIt = 4;  // vector groups per thread and loop iteration
 constexpr int kMaxRedBlocks = 2048;  // eight per CU resident at once: one round, longer-lived threads
-constexpr int kOneBlockChunks = 4;   // chunks folded by a single block, whose call is one launch
+constexpr int kOneThreads = 1024;    // of a block that folds a small input alone, in one launch
 constexpr int kMaxPassBlocks = 65536;
 // 16-byte groups per array and thread that an element-wise pass holds in
 // flight: four were the fastest with two inputs, and with four inputs, a seed
@@ -235,10 +235,12 @@ std::string gen_source(const mx_expr &e) {
     s += f32 ? "typedef float T;\n#define VW 4\n" : "typedef double T;\n#define VW 2\n";
     // element alignment is enough for 16-byte accesses: any slice of an array takes the vector path
     s += "typedef T VT __attribute__((ext_vector_type(VW), aligned(sizeof(T))));\n";
-    s += "#define NT " + std::to_string(NT) + "\n#define GPI " + std::to_string(kGroupsPerIt) + "\n";
+    s += "#define NT " + std::to_string(NT) + "\n#define GPI " + std::to_string(kGroupsPerIt) + "\n#define ONE " +
+         std::to_string(kOneThreads) + "\n";
     s += "#define NIN " + std::to_string(e.nin) + "\n";
     s += "#define CG " + std::to_string(chunk_groups(e.nin)) + "\n";
     s += "#define MX_CHUNK(nv) ((nv) <= " + std::to_string(kSmallPass) + " ? NT : CG * NT)\n";
+    s += "#define MX_RCHUNK(nv) ((nv) <= " + std::to_string(kSmallPass) + " ? NT : GPI * NT)\n";
     s += "#define SU (NIN >= 4 ? 2 : NIN >= 2 ? 4 : 8)\n";  // 16-byte groups per input in flight per lane
     s += "__device__ __forceinline__ T mx_body(" + in_params + ") {\n#pragma clang fp contract(off)\n" + fwd +
          "    return v" + std::to_string(os) + ";\n}\n";
@@ -316,6 +318,11 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xmap(MX_PTRS, T *__restrict_
 }
 
 // Reverse mode: gk[i] = seed_i * d body / d input k (null outputs skipped).
+template <bool PAST> __device__ __forceinline__ void mx_st(VT v, VT *q) {
+    if constexpr (PAST) __builtin_nontemporal_store(v, q);
+    else *q = v;
+}
+template <bool PAST>
 __device__ __forceinline__ void mx_vjp_group(const VT (&a)[4], const VT &go, bool hg, bool hs, T gs, VT *r0, VT *r1,
                                              VT *r2, VT *r3) {
     VT o0, o1, o2, o3;
@@ -327,10 +334,10 @@ __device__ __forceinline__ void mx_vjp_group(const VT (&a)[4], const VT &go, boo
                     NIN > 3 ? a[3][e] : (T)0, seed, d0, d1, d2, d3);
         o0[e] = d0; o1[e] = d1; o2[e] = d2; o3[e] = d3;
     }
-    if (NIN > 0 && r0) __builtin_nontemporal_store(o0, r0);
-    if (NIN > 1 && r1) __builtin_nontemporal_store(o1, r1);
-    if (NIN > 2 && r2) __builtin_nontemporal_store(o2, r2);
-    if (NIN > 3 && r3) __builtin_nontemporal_store(o3, r3);
+    if (NIN > 0 && r0) mx_st<PAST>(o0, r0);
+    if (NIN > 1 && r1) mx_st<PAST>(o1, r1);
+    if (NIN > 2 && r2) mx_st<PAST>(o2, r2);
+    if (NIN > 3 && r3) mx_st<PAST>(o3, r3);
 }
 #define MX_VJP_OUT(i) r0 ? r0 + (i) : r0, r1 ? r1 + (i) : r1, r2 ? r2 + (i) : r2, r3 ? r3 + (i) : r3
 template <bool STREAM>
@@ -345,7 +352,7 @@ __device__ __forceinline__ void mx_vjp_chunk(MX_PTRS, const VT *__restrict__ qg,
         if (hg) go[u] = mx_ld<STREAM>(qg + j + u * NT);
     }
 #pragma unroll
-    for (int u = 0; u < CG; ++u) mx_vjp_group(a[u], go[u], hg, hs, gs, MX_VJP_OUT(j + u * NT));
+    for (int u = 0; u < CG; ++u) mx_vjp_group<true>(a[u], go[u], hg, hs, gs, MX_VJP_OUT(j + u * NT));
 }
 extern "C" __global__ void __launch_bounds__(NT) mx_xvjp(MX_PTRS, const T *__restrict__ gout,
                                                            const T *__restrict__ gscale, T *__restrict__ g0,
@@ -366,7 +373,7 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xvjp(MX_PTRS, const T *__res
                 VT a[4], go;
                 mx_load_group(p0, p1, p2, p3, i, a);
                 if (hg) go = qg[i];
-                mx_vjp_group(a, go, hg, hs, gs, MX_VJP_OUT(i));
+                mx_vjp_group<false>(a, go, hg, hs, gs, MX_VJP_OUT(i));
             }
         }
     }
@@ -416,22 +423,20 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xscatter(MX_PTRS, const long
     return r;
 }
 // One partial per block.  A block folds contiguous chunks of GPI x NT groups of
-// every input, one accumulator per vector lane (the fold order depends on n
-// alone).  Bound by HBM: two inputs of 2^26 float32 took 111 us with a
+// every input (NT of a small one), one accumulator per vector lane (the fold order
+// depends on n alone).  Bound by HBM: two inputs of 2^26 float32 took 111 us with a
 // grid-wide stride and take 87 us (6.2 TB/s).  Plain loads: past the caches
 // the pass takes 79 us, but a reverse pass over the same inputs then finds
 // nothing of them in the memory-side cache (the two 254 us instead of 233 us).
-// The only block of a small call writes the result itself (direct != 0:
-// partial is the output), one launch instead of two.
-extern "C" __global__ void __launch_bounds__(NT) mx_xred_)" + nm + R"((MX_PTRS, long long n, T ne, int direct, T *__restrict__ partial) {
+extern "C" __global__ void __launch_bounds__(NT) mx_xred_)" + nm + R"((MX_PTRS, long long n, T *__restrict__ partial) {
     __shared__ T sh[NT / 64];
-    const long long nv = n / VW;
+    const long long nv = n / VW, chunk = MX_RCHUNK(nv);
     T acc[VW];
 #pragma unroll
     for (int e = 0; e < VW; ++e) acc[e] = )" + id + R"(;
-    for (long long c = (long long)blockIdx.x * (GPI * NT); c < nv; c += (long long)gridDim.x * (GPI * NT)) {
-        const long long j = c + threadIdx.x;
-        if (c + GPI * NT <= nv) {
+    for (long long c = (long long)blockIdx.x * chunk; c < nv; c += (long long)gridDim.x * chunk) {
+        const long long j = c + threadIdx.x, end = c + chunk < nv ? c + chunk : nv;
+        if (end - c == GPI * NT) {
             VT a[GPI][4];
 #pragma unroll
             for (int u = 0; u < GPI; ++u) mx_load_group(p0, p1, p2, p3, j + u * NT, a[u]);
@@ -440,7 +445,7 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xred_)" + nm + R"((MX_PTRS, 
 #pragma unroll
                 for (int e = 0; e < VW; ++e) acc[e] = mx_op_)" + nm + R"((acc[e], mx_body_at(a[u], e));
         } else {
-            for (long long i = j; i < nv; i += NT) {
+            for (long long i = j; i < end; i += NT) {
                 VT a[4];
                 mx_load_group(p0, p1, p2, p3, i, a);
 #pragma unroll
@@ -453,7 +458,42 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xred_)" + nm + R"((MX_PTRS, 
 #pragma unroll
     for (int e = 1; e < VW; ++e) acc[0] = mx_op_)" + nm + R"((acc[0], acc[e]);
     const T r = mx_block_)" + nm + R"((acc[0], sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = direct ? mx_op_)" + nm + R"((ne, r) : r;
+    if (threadIdx.x == 0) partial[blockIdx.x] = r;
+}
+// A small input by one block of blockDim.x threads, in one launch: up to GPI groups
+// per thread and input, all in flight, since an input that the call before has
+// written past the caches takes a round trip to memory (2^14 floats, map then two
+// inputs' body and sum: four rounds of 256 threads 8.3 us, two launches 5.9 us,
+// now 6.3 us).
+extern "C" __global__ void __launch_bounds__(ONE) mx_xone_)" + nm + R"((MX_PTRS, long long n, T ne, T *__restrict__ out) {
+    __shared__ T sh[ONE / 64];
+    const int nv = (int)(n / VW), t = threadIdx.x, S = blockDim.x;
+    VT a[GPI][4];
+#pragma unroll
+    for (int u = 0; u < GPI; ++u)
+        if (t + u * S < nv) mx_load_group(p0, p1, p2, p3, t + u * S, a[u]);
+    const long long i = (long long)nv * VW + t;  // the last n % VW elements
+    T acc[VW];
+#pragma unroll
+    for (int e = 0; e < VW; ++e) acc[e] = )" + id + R"(;
+#pragma unroll
+    for (int u = 0; u < GPI; ++u)
+        if (t + u * S < nv)
+#pragma unroll
+            for (int e = 0; e < VW; ++e) acc[e] = mx_op_)" + nm + R"((acc[e], mx_body_at(a[u], e));
+    if (i < n) acc[0] = mx_op_)" + nm + R"((acc[0], mx_body_i(p0, p1, p2, p3, i));
+    T r = acc[0];
+#pragma unroll
+    for (int e = 1; e < VW; ++e) r = mx_op_)" + nm + R"((r, acc[e]);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) r = mx_op_)" + nm + R"((r, __shfl_xor(r, o, 64));
+    if ((t & 63) == 0) sh[t >> 6] = r;
+    __syncthreads();
+    if (t == 0) {
+        r = sh[0];
+        for (int w = 1; w < S / 64; ++w) r = mx_op_)" + nm + R"((r, sh[w]);
+        *out = mx_op_)" + nm + R"((ne, r);
+    }
 }
 // the partials in block order (thread t takes t, t + NT, ...), then ne op total
 extern "C" __global__ void __launch_bounds__(NT) mx_xfin_)" + nm + R"((const T *__restrict__ partial, int nb, T ne, T *__restrict__ out) {
@@ -560,7 +600,7 @@ extern "C" __global__ void __launch_bounds__(NT) mx_xseg_)" + nm + R"((MX_PTRS, 
 // ---------------------------------------------------------------- compiled modules
 struct Compiled {
     hipModule_t mod = nullptr;
-    hipFunction_t map = nullptr, vjp = nullptr, scatter = nullptr, red[4] = {}, fin[4] = {}, seg[4] = {};
+    hipFunction_t map = nullptr, vjp = nullptr, scatter = nullptr, red[4] = {}, one[4] = {}, fin[4] = {}, seg[4] = {};
 };
 
 std::mutex g_mu;
@@ -586,6 +626,7 @@ mx_status compile(const mx_expr &e, const Compiled **out) {
     const char *nm[4] = {"add", "mul", "min", "max"};
     for (int o = 0; o < 4; ++o) {
         MX_TRY_HIP(hipModuleGetFunction(&c->red[o], c->mod, (std::string("mx_xred_") + nm[o]).c_str()));
+        MX_TRY_HIP(hipModuleGetFunction(&c->one[o], c->mod, (std::string("mx_xone_") + nm[o]).c_str()));
         MX_TRY_HIP(hipModuleGetFunction(&c->fin[o], c->mod, (std::string("mx_xfin_") + nm[o]).c_str()));
         MX_TRY_HIP(hipModuleGetFunction(&c->seg[o], c->mod, (std::string("mx_xseg_") + nm[o]).c_str()));
     }
@@ -595,8 +636,8 @@ mx_status compile(const mx_expr &e, const Compiled **out) {
 }
 
 mx_status launch(hipFunction_t f, int64_t blocks, hipStream_t s, void **args, const char *what,
-                 unsigned lds = 0) {
-    MX_TRY_HIP(hipModuleLaunchKernel(f, (unsigned)blocks, 1, 1, NT, 1, 1, lds, s, args, nullptr));
+                 unsigned lds = 0, unsigned threads = NT) {
+    MX_TRY_HIP(hipModuleLaunchKernel(f, (unsigned)blocks, 1, 1, threads, 1, 1, lds, s, args, nullptr));
     (void)what;
     return MX_OK;
 }
@@ -617,8 +658,8 @@ int64_t pass_blocks(int64_t n, int vw, int nin) {
 
 // the partial pass's grid depends only on n, so the result does not depend on the device
 int64_t reduce_blocks(int64_t n, int vw) {
-    const int64_t b = ceil_div(n > 0 ? n : 1, (int64_t)NT * vw * kGroupsPerIt);
-    return b > kMaxRedBlocks ? kMaxRedBlocks : b <= kOneBlockChunks ? 1 : b;
+    const int64_t nv = n / vw, b = ceil_div(nv, nv <= kSmallPass ? NT : NT * kGroupsPerIt);
+    return b > kMaxRedBlocks ? kMaxRedBlocks : b;
 }
 
 // Debug mode of the indexed-write loop: every index in range and no slot hit
@@ -741,16 +782,20 @@ mx_status mx_expr_map_reduce(mx_expr *e, mx_redop op, const void *const *in_dev,
     for (int k = 0; k < e->nin && n > 0; ++k) p[k] = in_dev[k];
     long long nn = n;
     void *partial = (char *)ws + kCounterBytes;
-    const int64_t nb = n > 0 ? reduce_blocks(n, e->dtype == MX_F32 ? 4 : 2) : 0;
-    int nbi = (int)nb, direct = nb == 1;
+    const int vw = e->dtype == MX_F32 ? 4 : 2;
+    const int64_t nv = n / vw, nb = n > 0 ? reduce_blocks(n, vw) : 0;
+    int nbi = (int)nb;
     float ne32 = 0.f;
     double ne64 = 0.0;
     void *ne = e->dtype == MX_F32 ? (void *)&ne32 : (void *)&ne64;
     __builtin_memcpy(ne, ne_host, dtype_size(e->dtype));
+    if (n > 0 && nv <= kGroupsPerIt * kOneThreads) {
+        void *args[] = {&p[0], &p[1], &p[2], &p[3], &nn, ne, &out_dev};
+        return launch(c->one[op], 1, stream, args, who, 0, nv <= kGroupsPerIt * NT ? NT : kOneThreads);
+    }
     if (nb > 0) {
-        void *args[] = {&p[0], &p[1], &p[2], &p[3], &nn, ne, &direct, direct ? &out_dev : &partial};
+        void *args[] = {&p[0], &p[1], &p[2], &p[3], &nn, &partial};
         if (mx_status st = launch(c->red[op], nb, stream, args, who)) return st;
-        if (direct) return MX_OK;
     }
     void *args[] = {&partial, &nbi, ne, &out_dev};
     return launch(c->fin[op], 1, stream, args, who);

@@ -117,3 +117,11 @@ def test_small_pass_edges(name, dtype, vectors, more):
     """Passes of one vector per thread, up to 2^17 vectors, and the first past them."""
     width = 4 if dtype == abi.MX_F32 else 2
     test_chunk_edges(name, dtype, vectors * width + more % width, 1)
+
+
+@pytest.mark.parametrize("vectors,more", [(255, 1), (1023, 0), (1024, 3), (1025, 0), (4095, 1), (4096, 3), (4097, 0), (8193, 1)])
+@pytest.mark.parametrize("dtype", [abi.MX_F32, abi.MX_F64])
+@pytest.mark.parametrize("name", ["one", "four"])
+def test_one_block(name, dtype, vectors, more):
+    """Sums of one block of 256 threads (1024 vectors), of 1024 (4096), and of two launches."""
+    test_small_pass_edges(name, dtype, vectors, more)
