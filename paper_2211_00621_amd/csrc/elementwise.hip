@@ -39,19 +39,23 @@ __host__ __device__ constexpr int64_t chunk_of(int64_t nv) { return nv <= kSmall
 //   2^20  2.6, 2.3, 2.5;  7.0, 7.1, 6.8       2^21  4.5, 3.4, 4.0;  12.0, 10.9, 12.4
 //   2^22  8.4, 8.5, 8.5;  18.7, 17.8, 20.2    2^24  36, 35, 29;  71.5, 69.6, 77.1
 // and of the dot's adjoint alone: 2^20 3.6, 3.3, 3.1; 2^21 7.2, 4.9, 5.4; 2^23 20.5,
-// 20.5, 20.1; 2^24 49, 48, 39.5.  So the stores of small passes go past the caches,
-// those of larger ones into the memory-side cache alone, where the next call finds
+// 20.5, 20.1; 2^24 49, 48, 39.5.  A map of 2^14, read back by a sum of one block: 4.2,
+// 4.0, 4.7; of 2^15, by many: 5.3, 5.5, 5.25.  So the stores of the smallest passes are
+// plain, those of small ones go past the caches, those of larger ones into the memory-side cache alone, where the next call finds
 // them; past its size, and for gradients, whose reader is seldom the next call,
 // past half of it, past all caches; and so do the loads of a pass larger than it.
-enum Mode { STORES_PAST, STORES_THROUGH, ALL_PAST };
+enum Mode { STORES_NEAR, STORES_PAST, STORES_THROUGH, ALL_PAST };
+constexpr int64_t kNearMax = 1 << 20;
 constexpr int64_t kThroughMin = 16 << 20;
 Mode pass_mode(int64_t bytes, bool gradient) {
     if (bytes > kCacheBytes) return ALL_PAST;
+    if (bytes <= kNearMax) return STORES_NEAR;
     return bytes > kThroughMin && bytes < (gradient ? kCacheBytes / 2 : kCacheBytes) ? STORES_THROUGH : STORES_PAST;
 }
 template <Mode M> constexpr bool kPast = M == ALL_PAST;
 template <Mode M, class T> __device__ __forceinline__ void put(uvec<T> v, T *p) {
     if constexpr (M == STORES_THROUGH) store16_through(v, p);
+    else if constexpr (M == STORES_NEAR) store16_near(v, p);
     else store16(v, p);
 }
 
@@ -168,6 +172,7 @@ __global__ void __launch_bounds__(NT) k_dot_adjoint(const float *__restrict__ a,
 // ---------------------------------------------------------------- dispatch
 template <class Go> void by_mode(Mode m, Go go) {
     switch (m) {
+    case STORES_NEAR: return go(std::integral_constant<Mode, STORES_NEAR>{});
     case STORES_PAST: return go(std::integral_constant<Mode, STORES_PAST>{});
     case STORES_THROUGH: return go(std::integral_constant<Mode, STORES_THROUGH>{});
     case ALL_PAST: return go(std::integral_constant<Mode, ALL_PAST>{});

@@ -1184,8 +1184,11 @@ __global__ void __launch_bounds__(T) k_sse_grad(SseArgs a, const float *__restri
             for (int u = 0; u < kSseVec; ++u) store16(g2 * (x[u] - c[u]), go + 4 * (threadIdx.x + u * SNT));
         } else {
             const uint32_t nv = !V4 && a.chunk == T ? 0 : at.left >> 2, t = 4 * nv + threadIdx.x;
-            for (uint32_t i = threadIdx.x; i < nv; i += T)
-                store16(g2 * (load16<false>(at.x + 4 * i) - sse_c4<V4>(a, at, 4 * i)), go + 4 * i);
+            for (uint32_t i = threadIdx.x; i < nv; i += T) {
+                const uvec<float> v = g2 * (load16<false>(at.x + 4 * i) - sse_c4<V4>(a, at, 4 * i));
+                if constexpr (T == NT) store16_near(v, go + 4 * i);
+                else store16(v, go + 4 * i);
+            }
             if (t < at.left) go[t] = g2 * (at.x[t] - sse_c1(a, at, t));
         }
     }

@@ -97,6 +97,9 @@ template <class T> __device__ __forceinline__ void store16(uvec<T> v, T *p) {
     __builtin_nontemporal_store(v, reinterpret_cast<uvec<T> *>(p));
 }
 
+// The same left in the L2 cache of its XCD.
+template <class T> __device__ __forceinline__ void store16_near(uvec<T> v, T *p) { *reinterpret_cast<uvec<T> *>(p) = v; }
+
 // The same past the L2 caches but into the memory-side cache, for a wave whose
 // lanes write consecutive vectors: the scope bit of a buffer store, whose
 // descriptor is at the first lane's vector.

@@ -70,22 +70,24 @@ template <int OP> __device__ __forceinline__ void block_argreduce(float &bv, int
 // alignment, all loads of a chunk in flight, for its threads' best pairs and
 // writes zeros to gx on the way; one pair per block.  Bound by HBM: 2^26 elements
 // (537 MB in and out) 99 us with the finish (5.4 TB/s), 111 us with one vector
-// in flight and a grid-wide stride; 2^22 9.5 us, 11.3 us.
+// in flight and a grid-wide stride; 2^22 9.5 us, 11.3 us.  A small pass goes by the
+// chunks of the others, and its zeros stay near.
 constexpr int C = 4;
+__host__ __device__ constexpr int64_t chunk_of(int64_t nv) { return nv <= kSmallPass ? NT : C * NT; }
 template <int OP>
 __global__ void __launch_bounds__(NT) k_arg_partial(const float *__restrict__ x, int64_t n, float *__restrict__ gx,
                                                     float *__restrict__ pv, int64_t *__restrict__ pi) {
     float bv = ident<OP>();
     int64_t bi = kNone;
     const uvec<float> zero = {0.f, 0.f, 0.f, 0.f};
-    const int64_t nv = n / 4;
+    const int64_t nv = n / 4, chunk = chunk_of(nv);
     auto scan = [&](const uvec<float> &q, int64_t j) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) take<OP>(q[e], 4 * j + e, bv, bi);
     };
-    for (int64_t c = (int64_t)blockIdx.x * (C * NT); c < nv; c += (int64_t)gridDim.x * (C * NT)) {
-        const int64_t j = c + threadIdx.x;
-        if (c + C * NT <= nv) {
+    for (int64_t c = (int64_t)blockIdx.x * chunk; c < nv; c += (int64_t)gridDim.x * chunk) {
+        const int64_t j = c + threadIdx.x, end = c + chunk < nv ? c + chunk : nv;
+        if (end - c == C * NT) {
             uvec<float> q[C];
 #pragma unroll
             for (int u = 0; u < C; ++u) q[u] = load16<false>(x + 4 * (j + u * NT));
@@ -95,9 +97,9 @@ __global__ void __launch_bounds__(NT) k_arg_partial(const float *__restrict__ x,
                 store16(zero, gx + 4 * (j + u * NT));
             }
         } else {
-            for (int64_t i = j; i < nv; i += NT) {
+            for (int64_t i = j; i < end; i += NT) {
                 scan(load16<false>(x + 4 * i), i);
-                store16(zero, gx + 4 * i);
+                store16_near(zero, gx + 4 * i);
             }
         }
     }
@@ -257,7 +259,7 @@ mx_status mx_reduce_adjoint_f32(mx_redop op, const float *x_dev, int64_t n, cons
     const size_t need = mx_workspace_bytes(MX_WS_REDUCE, n, 0);
     MX_REQUIRE(ws && ws_bytes >= need && ((uintptr_t)ws & 255) == 0, MX_ERR_WORKSPACE,
                "%s: workspace needs %zu bytes, 256-byte aligned", who, need);
-    int64_t grid = ceil_div(n, (int64_t)4 * C * NT);
+    int64_t grid = ceil_div(n, 4 * chunk_of(n / 4));
     int64_t cap = (int64_t)d->num_cus * 8;
     if (cap > kMaxArgBlocks) cap = kMaxArgBlocks;
     if (grid > cap) grid = cap;

@@ -35,3 +35,9 @@ def test_arg_chunks(op, n, shift):
             h = big.cpu().numpy()
             assert np.array_equal(h[shift:shift + n], ref), (op, n, at)
             assert np.all(h[:shift] == 7) and np.all(h[shift + n:] == 7)
+
+
+@pytest.mark.parametrize("n", [2047, 2049, (1 << 19) - 1, (1 << 19) + 3, (1 << 19) + 4])
+def test_small_pass_edges(n):
+    """Chunks of 256 vectors up to 2^17 of them, and the first past it."""
+    test_arg_chunks(abi.MX_MAX, n, 1)
