@@ -1142,7 +1142,8 @@ k_bcast_blocks(const float *__restrict__ gout, const int64_t *__restrict__ offse
 // trips (offsets, values, store).  A group of G lanes takes one row, every load
 // of a row of up to U G vectors in flight at once; longer rows are then taken by a
 // wave each, and past kWaveCap by the whole block, U vectors per thread in
-// flight, so that a single long row streams as in the kernels this one replaces.
+// flight, so that a single long row streams as in the kernels this one replaces; of
+// small inputs whose rows are past a group on average a block takes one row.
 //
 // us before and now (sum, launches replayed from a graph): 300 rows, 23 001
 // values 10.1, 2.5; 1000 rows, 12 357 values 18.8, 2.5; 65 536 rows of mean
@@ -1168,19 +1169,20 @@ template <class In, class Vec> __device__ __forceinline__ Vec load_vec(const In 
 
 template <mx_dtype D, int OP, int NTB, int G, int U>
 __global__ void __launch_bounds__(NTB) k_seg_groups(const typename DT<D>::In *__restrict__ values,
-                                                    const int64_t *__restrict__ offsets, int64_t nseg,
+                                                    const int64_t *__restrict__ offsets, int64_t nseg, int rows,
                                                     typename DT<D>::Acc ne, typename DT<D>::Acc *__restrict__ out) {
     using In = typename DT<D>::In;
     using Acc = typename DT<D>::Acc;
     using Vec = typename DT<D>::Vec;
     using R = Red<OP, Acc>;
-    constexpr int V = DT<D>::kVec, ROWS = NTB / G, NW = NTB / kWave;
+    constexpr int V = DT<D>::kVec, ROWS = NTB / G, NW = NTB / kWave;  // rows <= ROWS
+    static_assert(ROWS <= 64, "a bit for each row");
     __shared__ int64_t soff[ROWS + 1];
     __shared__ Acc part[NW];
     __shared__ unsigned long long longer;  // rows past what a group takes
     const int t = threadIdx.x;
-    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
-    const int nrows = (int)(nseg - r0 < ROWS ? nseg - r0 : ROWS);
+    const int64_t r0 = (int64_t)blockIdx.x * rows;
+    const int nrows = (int)(nseg - r0 < rows ? nseg - r0 : rows);
     if (t <= nrows) soff[t] = offsets[r0 + t];
     if (t == 0) longer = 0;
     __syncthreads();
@@ -1533,9 +1535,13 @@ mx_status launch_seg(bool plain, const void *values, int64_t nval, const int64_t
         const bool wave = nval <= kWaveAvg * nseg && nseg <= kWaveRows;
         if (small || (seg_span_path(nseg, nval, d) && (nval <= kMidAvg * nseg || wave))) {
             MX_REQUIRE(ceil_div(nseg, NT / 16) <= 0x7fffffff, MX_ERR_SHAPE, "mx_segmented_reduce: too many rows");
+            // a block per row where most are the whole block's (16 rows of 6000 float64 by one
+            // block 17.8 us, now 3.8 us)
+            const bool alone = small && nval > nseg * (kWave * 4 * DT<D>::kVec);
             auto go = [&](auto kernel, int threads, int group) {
-                hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(nseg, threads / group)), dim3(threads), 0, s,
-                                   (const In *)values, off, nseg, ne, (Acc *)out);
+                const int rows = alone ? 1 : threads / group;
+                hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(nseg, rows)), dim3(threads), 0, s, (const In *)values,
+                                   off, nseg, rows, ne, (Acc *)out);
             };
             if (small && nval <= kShortAvg * nseg) go(k_seg_groups<D, OP, NTS, 16, 4>, NTS, 16);
             else if (small) go(k_seg_groups<D, OP, NTS, kWave, 4>, NTS, kWave);

@@ -130,3 +130,21 @@ def test_long_rows_by_waves_and_blocks(case, dt, monkeypatch):
     test_group_reduce(case, dt)
     if dt == np.float32:
         test_group_reverses(case)
+
+
+FEW_LONG = {
+    # rows past a group on average, one to a block: by its first wave, by the whole block, empty ones, a single row
+    "few": np.array([0, 3000, 1, 1024, 1025, 4097, 0, 9001, 511, 513, 6000, 2049]),
+    "even": np.full(16, 6000),
+    "single": np.array([1025]),
+    # at that line for vectors of four and of two, and just below it
+    "line4": np.array([1024, 1024, 1025]), "below4": np.array([1024, 1024, 1024]),
+    "line2": np.array([512, 512, 513]), "below2": np.array([512, 512, 512]),
+}
+
+
+@pytest.mark.parametrize("case", list(FEW_LONG))
+@pytest.mark.parametrize("dt", [np.float32, np.float64, np.int32, np.int64])
+def test_few_long_rows(case, dt, monkeypatch):
+    monkeypatch.setitem(globals(), "lengths", FEW_LONG.__getitem__)
+    test_group_reduce(case, dt)
