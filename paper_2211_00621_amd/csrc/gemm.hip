@@ -750,12 +750,16 @@ template <int MI, int NI, int WM, int WN, int KG> mx_status launch_split(const G
 #undef SHAPE
 }
 // Past three rounds of blocks no wave without a slice of K: 10^6 x 1 x 32 took
-// 167 us with eight waves a tile, 63 us with one.  Before, the idle waves cost
-// nothing, and their instruction fetches serve the one that works (1000 x 8 x 64
-// 2.6 us with eight, 3.3 us with two).
+// 167 us with eight waves a tile, 63 us with one.  Of more than two slices that holds
+// where both operands' rows run along K (787 343 x 1 x 93, B transposed, 94 us with
+// eight waves, 64 us with four); elsewhere a tile's rows lie far apart, and the idle
+// waves keep fewer tiles open at once (A transposed 105 us with eight, 175 us with
+// four).  In fewer rounds the idle waves cost nothing, and their instruction fetches
+// serve the one that works (1000 x 8 x 64 2.6 us with eight, 3.3 us with two).
 template <int MI, int NI, int KS> mx_status launch_direct(const GemmArgs &a) {
     if constexpr (KS > 1)
-        if (a.K <= KS / 2 * BK && ceil_div(a.M, 16 * MI) * ceil_div(a.N, 16 * NI) > 3 * a.num_cus)
+        if (a.K <= (!a.ta && a.tb ? KS / 2 : std::min(KS / 2, 2)) * BK &&
+            ceil_div(a.M, 16 * MI) * ceil_div(a.N, 16 * NI) > 3 * a.num_cus)
             return launch_direct<MI, NI, KS / 2>(a);
 #define SHAPE MI, NI, KS
     MX_GEMM_LAUNCH(16 * MI, 16 * NI, 64 * KS, k_gemm_direct);
@@ -773,12 +777,14 @@ template <int MI, int NI, int KS> mx_status launch_direct(const GemmArgs &a) {
 // ahead).  The 16 x 16 tiles share a CU by several, so their rounds need not be
 // whole; the direct 32 x 32 tiles read too much memory past one round.
 //
-// Products of K <= 256, where no wave of a direct tile has two slices: past the
-// first rounds the fixed part becomes `more` a round, since the direct tiles,
-// of as many waves as K has slices, share a CU by up to 32, and the twelve waves
-// of 32 x 64 and 64 x 32 mostly wait (10^6 x 8 by 16 x 16, 32 x 32, 64 x 32 and 64 x 64
-// tiles, us: K = 8 74, 76, 157 and 103; K = 32 84, 79, 184 and 127; K = 256 237,
-// 315, 349 and 366; 1000 x 1000 x 64 9, 7, 8 and 6).
+// Products of K <= 256, where no wave of a direct tile has two slices and the
+// groups of a split tile's waves have one or none: past the first rounds the fixed
+// part becomes `more` a round.  The direct tiles share a CU by up to 32; the blocks
+// of twelve and sixteen waves mostly wait, and hardly overlap, which up to K = 128
+// the larger feel from their first round on (10^6 x 8 by 16 x 16, 32 x 32, 64 x 32 and
+// 64 x 64 tiles, us: K = 8 74, 76, 157 and 103; K = 32 84, 79, 184 and 127; K = 256
+// 237, 315, 349 and 366; 2853 x 3201 x 12, A transposed, by 32 x 32, 64 x 64, 96 x 64
+// and 128 x 128 20, 25, 32 and 23, of which `fixed` alone picked the third).
 struct GemmShape {
     const char *name;  // MX_GEMM_TILE in the environment forces a shape, for tuning and tests
     int bm, bn;
@@ -787,20 +793,20 @@ struct GemmShape {
     double first = 0., more = 0.;  // rounds at `fixed`, and the fixed part of those after them
 };
 const GemmShape kShapes[] = {
-    {"16x16", 16, 16, 0.95, 2.3, launch_direct<1, 1, 8>, 3., .3},
-    {"32x32", 32, 32, 1.4, 5.5, launch_direct<2, 2, 4>, 3., .45},
+    {"16x16", 16, 16, 0.95, 2.3, launch_direct<1, 1, 8>, 3., .1},
+    {"32x32", 32, 32, 1.4, 5.5, launch_direct<2, 2, 4>, 3., .2},
     {"32x64", 32, 64, 1.5, 10.5, launch_split<2, 2, 1, 2, 6>, 1., 2.4},
     {"64x32", 64, 32, 1.5, 10.5, launch_split<2, 2, 2, 1, 6>, 1., 2.4},
-    {"64x64", 64, 64, 1.8, 19., launch_split<2, 2, 2, 2, 2>},
-    {"80x64", 80, 64, 2.2, 23.5, launch_split<5, 1, 1, 4, 4>},
-    {"64x80", 64, 80, 2.2, 24., launch_split<1, 5, 4, 1, 4>},
-    {"96x64", 96, 64, 2.5, 27.5, launch_split<3, 2, 2, 2, 3>},
-    {"64x96", 64, 96, 2.5, 27.5, launch_split<2, 3, 2, 2, 3>},
-    {"128x64", 128, 64, 3., 34., launch_split<2, 2, 4, 2, 2>},
-    {"64x128", 64, 128, 3., 34., launch_split<2, 2, 2, 4, 2>},
-    {"128x96", 128, 96, 4., 49.5, launch_split<2, 3, 4, 2, 2>},
-    {"128x128", 128, 128, 5., 65.5, launch_split<2, 2, 4, 4, 1>},
-    {"128x128w16", 128, 128, 5., 62., launch_pipelined},
+    {"64x64", 64, 64, 1.8, 19., launch_split<2, 2, 2, 2, 2>, 1., 1.4},
+    {"80x64", 80, 64, 2.2, 23.5, launch_split<5, 1, 1, 4, 4>, 0., 3.6},
+    {"64x80", 64, 80, 2.2, 24., launch_split<1, 5, 4, 1, 4>, 0., 3.6},
+    {"96x64", 96, 64, 2.5, 27.5, launch_split<3, 2, 2, 2, 3>, 0., 3.6},
+    {"64x96", 64, 96, 2.5, 27.5, launch_split<2, 3, 2, 2, 3>, 0., 3.6},
+    {"128x64", 128, 64, 3., 34., launch_split<2, 2, 4, 2, 2>, 0., 4.},
+    {"64x128", 64, 128, 3., 34., launch_split<2, 2, 2, 4, 2>, 0., 4.},
+    {"128x96", 128, 96, 4., 49.5, launch_split<2, 3, 4, 2, 2>, 0., 4.},
+    {"128x128", 128, 128, 5., 65.5, launch_split<2, 2, 4, 4, 1>, 1., 3.},
+    {"128x128w16", 128, 128, 5., 62., launch_pipelined, 1., 2.9},
 };
 constexpr int kNumShapes = sizeof kShapes / sizeof kShapes[0], kPipelined = kNumShapes - 1;
 
@@ -831,7 +837,7 @@ const GemmShape &gemm_choice(const GemmArgs &a) {
         else if (i > 0) rounds = ceil(rounds);
         const double per_k = i == 1 && rounds > 1. ? 9. : s.per_k;
         double fixed = s.fixed * rounds;
-        if (a.K <= 256 && s.more > 0. && rounds > s.first) fixed = s.fixed * s.first + s.more * (rounds - s.first);
+        if (a.K <= (s.first > 0. ? 256 : 128) && s.more > 0. && rounds > s.first) fixed = s.fixed * s.first + s.more * (rounds - s.first);
         const double us = fixed + rounds * per_k * (double)a.K * 1e-3;
         if (us < best_us) {
             best_us = us;
