@@ -352,8 +352,8 @@ __global__ void __launch_bounds__(NT) k_stencil7(const float *__restrict__ in, f
 // per pair of sample and voxel.
 //
 // Work split: VW groups of WS waves cover 64 V voxels each, V per lane; a group's
-// waves take the samples of a tile by fours in turn and their sums are added in
-// wave order through LDS (which V, WS and VW: mx_mriq_f32).
+// waves take the samples of a tile by U in turn and their sums are added in wave
+// order through LDS (which V, WS, VW and U: mx_mriq_f32).
 constexpr int kMriTile = 1024;
 constexpr float kMriRaw = 250.f;
 
@@ -372,7 +372,7 @@ template <int K> __device__ __forceinline__ void sincos_group(const float (&u)[K
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int V, int WS, int VW>
+template <int V, int WS, int VW, int U>
 __global__ void __launch_bounds__(WS *VW *kWave) k_mriq(const float *__restrict__ kx, const float *__restrict__ ky,
                                                     const float *__restrict__ kz, const float *__restrict__ phi,
                                                     int64_t nk, const float *__restrict__ x,
@@ -380,7 +380,6 @@ __global__ void __launch_bounds__(WS *VW *kWave) k_mriq(const float *__restrict_
                                                     int64_t nv, float *__restrict__ qr, float *__restrict__ qi) {
     static_assert(WS == 1 || VW == 1, "the sums of one group of waves");
     constexpr int BT = WS * VW * kWave;
-    constexpr int U = 4;  // samples at a time
     __shared__ float4 ks[kMriTile];
     __shared__ float red[WS > 1 ? BT * V * 2 : 1];
     __shared__ float kmax[BT / kWave];
@@ -724,15 +723,18 @@ mx_status mx_mriq_f32(const float *kx_dev, const float *ky_dev, const float *kz_
     // the chip is full.  us at 2048 samples, (voxels per lane, waves): 2^18
     // voxels (4,4) 106, (2,4) 116, (1,16) 124, and 160 for two voxels per lane,
     // one wave and no raised priority; 2^16: 46, 32, 34; 2^14: 44, 27, 12.  Few samples
-    // have none for the waves to share: two voxels per lane and a wave each (one
-    // sample, 2^20 voxels: 8.6 us by (4,4); 24 samples 12.4 us, 48 16.8 us against 16.6).
-#define MX_MRIQ(V, WS, VW)                                                                                         \
-    hipLaunchKernelGGL((k_mriq<V, WS, VW>), dim3((unsigned)ceil_div(nv, (int64_t)kWave * V * VW)), dim3(WS * VW * kWave), \
+    // have none for the waves to share: two voxels per lane and a wave each (2^20
+    // voxels, us against (4,4): 24 samples 9.0, 12.4; 41 13.0, 16.0; 100 24.2, 26.1;
+    // 2^18: 17 3.9, 4.5; 100 8.3, 8.6), and one or two are taken singly, since a group of
+    // four would be mostly padding (one sample, 2^20 voxels: 4.4 us, 5.0 us by fours).
+#define MX_MRIQ(V, WS, VW, U)                                                                                         \
+    hipLaunchKernelGGL((k_mriq<V, WS, VW, U>), dim3((unsigned)ceil_div(nv, (int64_t)kWave * V * VW)), dim3(WS * VW * kWave), \
                        0, stream, kx_dev, ky_dev, kz_dev, phi_dev, nk, x_dev, y_dev, z_dev, nv, qr_dev, qi_dev)
-    if (nk <= 16 || (nk <= 40 && nv >= 1 << 19)) MX_MRIQ(2, 1, 4);
-    else if (nv >= 3 << 16) MX_MRIQ(4, 4, 1);
-    else if (nv > 1 << 15) MX_MRIQ(2, 4, 1);
-    else MX_MRIQ(1, 16, 1);
+    if (nk <= 2) MX_MRIQ(2, 1, 4, 1);
+    else if (nk <= 16 || (nk <= 100 && nv >= 3 << 16)) MX_MRIQ(2, 1, 4, 4);
+    else if (nv >= 3 << 16) MX_MRIQ(4, 4, 1, 4);
+    else if (nv > 1 << 15) MX_MRIQ(2, 4, 1, 4);
+    else MX_MRIQ(1, 16, 1, 4);
 #undef MX_MRIQ
     return last_launch(who);
 }

@@ -63,3 +63,10 @@ def test_mriq_few_samples(nv, nk):
     """Too few samples for the waves of a block to share: a wave for each two voxels of its lanes."""
     test_mriq_splits(nv, nk, 1.0)
     test_mriq_splits(nv, nk, 40.0)
+
+
+@pytest.mark.parametrize("nk,nv", [(1, 1000), (2, 513), (3, 513), (2, 200001), (100, 3 << 16), (101, 3 << 16), (100, (3 << 16) - 1)])
+def test_mriq_samples_singly_and_by_wave(nk, nv):
+    """One or two samples without padding to four, and the most that a wave takes alone where the voxels fill the chip."""
+    test_mriq_splits(nv, nk, 1.0)
+    test_mriq_splits(nv, nk, 40.0)
