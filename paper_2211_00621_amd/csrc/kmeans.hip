@@ -1048,16 +1048,16 @@ __global__ void __launch_bounds__(NT) k_kmeans_divide_plain(const float *__restr
 constexpr int SNT = 512;  // 1024 blocks (the partials' room) of it fill every CU
 constexpr int kSseVec = 2;
 constexpr int kSseChunk = 4 * kSseVec * SNT;  // elements
-// A small pass: blocks of NT threads, a vector per thread (kSmallPass: the other
-// passes' chunks), up to half as much an element per thread where d is no
-// multiple of four and a vector's elements need a point each (10 000 elements of
-// two dimensions: gradient 2.6 us by vectors, 2.0 us).  The sum of up to kSseOne
-// elements is one block's, and one launch (100 points of 16: two launches 1.9 times
-// as long).
+// Up to kSseSmall elements a vector per thread, or where d is no multiple of four
+// and the elements of a vector need a point each, an element: of the sum up to
+// kSmallPass elements, of the gradient up to kSseEach.  These passes are all latency,
+// of the launch, of instructions fetched for the first time and of the chain of
+// label and centroid, so they have kernels of their own with one path and no loop.
+// us with a grid-wide stride, in the chunks of the larger passes, now: gradient of
+// 300 000 x 2 3.2, 3.9, 3.0, sum of 5000 x 64 4.2, 4.7, 4.2.  The sum of up to kSseOne elements is one
+// block's, and one launch (100 points of 16: two launches 1.9 times as long).
 constexpr int64_t kSseOne = 4 * SNT;
-int64_t sse_chunk_of(int64_t total, int d) {
-    return total <= 2 * kSmallPass && d % 4 != 0 ? NT : total <= 4 * kSmallPass ? 4 * NT : kSseChunk;
-}
+constexpr int64_t kSseSmall = 4 * kSmallPass, kSseEach = 8 * kSmallPass;
 
 struct SseArgs {
     const float *X, *C;
@@ -1069,7 +1069,7 @@ struct SseArgs {
 
 SseArgs sse_args(const float *X, int64_t n, int d, const float *C, const int32_t *labels) {
     const uint64_t ud = (uint64_t)d;
-    return SseArgs{X, C, labels, n * d, sse_chunk_of(n * d, d), (uint32_t)d, d > 1 ? (uint32_t)(0x100000000ull / ud + 1) : 0u, ~0ull / ud};
+    return SseArgs{X, C, labels, n * d, kSseChunk, (uint32_t)d, d > 1 ? (uint32_t)(0x100000000ull / ud + 1) : 0u, ~0ull / ud};
 }
 
 // Where a chunk lies: its first point (64-bit reciprocal: the estimate is at
@@ -1107,9 +1107,8 @@ template <bool V4> __device__ __forceinline__ uvec<float> sse_c4(const SseArgs &
 // Partial sums of (x - c_label)^2, one per block; of a single block the result.
 // V4: the next chunk's points and labels are in flight while this one's
 // centroid values are fetched and folded.
-template <bool V4, int T>
-__global__ void __launch_bounds__(T) k_sse_partial(SseArgs a, float *__restrict__ part) {
-    __shared__ float red[T / kWave];
+template <bool V4> __global__ void __launch_bounds__(SNT) k_sse_partial(SseArgs a, float *__restrict__ part) {
+    __shared__ float red[SNT / kWave];
     uvec<float> acc = {0.f, 0.f, 0.f, 0.f};
     const int64_t step = (int64_t)gridDim.x * a.chunk;
     int64_t e0 = (int64_t)blockIdx.x * a.chunk;
@@ -1117,7 +1116,7 @@ __global__ void __launch_bounds__(T) k_sse_partial(SseArgs a, float *__restrict_
         const uvec<float> q = x - c;
         acc += q * q;
     };
-    if constexpr (V4 && T == SNT) {
+    if constexpr (V4) {
         uvec<float> x[kSseVec];
         int l[kSseVec];
         uint32_t o[kSseVec];
@@ -1148,15 +1147,54 @@ __global__ void __launch_bounds__(T) k_sse_partial(SseArgs a, float *__restrict_
     }
     for (; e0 < a.total; e0 += step) {
         const SseAt at = sse_at(a, e0);
-        const uint32_t nv = !V4 && a.chunk == T ? 0 : at.left >> 2, t = 4 * nv + threadIdx.x;
+        const uint32_t nv = at.left >> 2, t = 4 * nv + threadIdx.x;
 #pragma unroll 2
-        for (uint32_t i = threadIdx.x; i < nv; i += T) fold(load16<false>(at.x + 4 * i), sse_c4<V4>(a, at, 4 * i));
+        for (uint32_t i = threadIdx.x; i < nv; i += SNT) fold(load16<false>(at.x + 4 * i), sse_c4<V4>(a, at, 4 * i));
         if (t < at.left) {
             const float q = at.x[t] - sse_c1(a, at, t);
             acc[0] += q * q;
         }
     }
-    const float s = block_reduce<Red<MX_ADD, float>, T>((acc[0] + acc[1]) + (acc[2] + acc[3]), red);
+    const float s = block_reduce<Red<MX_ADD, float>, SNT>((acc[0] + acc[1]) + (acc[2] + acc[3]), red);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+// The small passes' element e: its centroid value, and for a vector (V4: of one point)
+__device__ __forceinline__ float sse_small1(const SseArgs &a, uint32_t e) {
+    const uint32_t p = e / a.d;
+    return a.C[(int64_t)a.labels[p] * a.d + (e - p * a.d)];
+}
+template <bool V4> __device__ __forceinline__ uvec<float> sse_small4(const SseArgs &a, uint32_t e) {
+    if constexpr (V4) {
+        const uint32_t p = e / a.d;
+        return load16<false>(a.C + (int64_t)a.labels[p] * a.d + (e - p * a.d));
+    } else {
+        return uvec<float>{sse_small1(a, e), sse_small1(a, e + 1), sse_small1(a, e + 2), sse_small1(a, e + 3)};
+    }
+}
+
+// VEC: a vector per thread, the last total % 4 elements by the first threads of the
+// last block (there are none of V4); otherwise an element per thread
+template <bool V4, bool VEC>
+__global__ void __launch_bounds__(NT) k_sse_partial_small(SseArgs a, float *__restrict__ part) {
+    __shared__ float red[NT / kWave];
+    const uint32_t i = blockIdx.x * NT + threadIdx.x, total = (uint32_t)a.total;
+    float s = 0.f;
+    if constexpr (VEC) {
+        if (4 * i + 4 <= total) {
+            const uvec<float> q = load16<false>(a.X + 4 * i) - sse_small4<V4>(a, 4 * i);
+            s = (q[0] * q[0] + q[1] * q[1]) + (q[2] * q[2] + q[3] * q[3]);
+        }
+        const uint32_t e = (total & ~3u) + threadIdx.x;
+        if (!V4 && blockIdx.x == gridDim.x - 1 && e < total) {
+            const float q = a.X[e] - sse_small1(a, e);
+            s += q * q;
+        }
+    } else if (i < total) {
+        const float q = a.X[i] - sse_small1(a, i);
+        s = q * q;
+    }
+    s = block_reduce<Red<MX_ADD, float>, NT>(s, red);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
@@ -1168,13 +1206,28 @@ __global__ void __launch_bounds__(NT) k_sse_final(const float *__restrict__ part
     if (threadIdx.x == 0) out[0] = (float)acc;
 }
 
-template <bool V4, bool PAST, int T>
-__global__ void __launch_bounds__(T) k_sse_grad(SseArgs a, const float *__restrict__ gscale, float *__restrict__ G) {
+// V4: a vector per thread, otherwise an element
+template <bool V4>
+__global__ void __launch_bounds__(NT) k_sse_grad_small(SseArgs a, const float *__restrict__ gscale,
+                                                       float *__restrict__ G) {
+    const uint32_t e = (blockIdx.x * NT + threadIdx.x) * (V4 ? 4 : 1);
+    if (e >= (uint32_t)a.total) return;
+    if constexpr (V4) {
+        const uvec<float> x = load16<false>(a.X + e), c = sse_small4<V4>(a, e);
+        store16_near(2.0f * gscale[0] * (x - c), G + e);
+    } else {
+        const float x = a.X[e], c = sse_small1(a, e);
+        G[e] = 2.0f * gscale[0] * (x - c);
+    }
+}
+
+template <bool V4, bool PAST>
+__global__ void __launch_bounds__(SNT) k_sse_grad(SseArgs a, const float *__restrict__ gscale, float *__restrict__ G) {
     const float g2 = 2.0f * gscale[0];
     for (int64_t e0 = (int64_t)blockIdx.x * a.chunk; e0 < a.total; e0 += (int64_t)gridDim.x * a.chunk) {
         const SseAt at = sse_at(a, e0);
         float *go = G + e0;
-        if (T == SNT && at.left == kSseChunk) {
+        if (at.left == kSseChunk) {
             uvec<float> x[kSseVec], c[kSseVec];
 #pragma unroll
             for (int u = 0; u < kSseVec; ++u) x[u] = load16<PAST>(at.x + 4 * (threadIdx.x + u * SNT));
@@ -1183,12 +1236,9 @@ __global__ void __launch_bounds__(T) k_sse_grad(SseArgs a, const float *__restri
 #pragma unroll
             for (int u = 0; u < kSseVec; ++u) store16(g2 * (x[u] - c[u]), go + 4 * (threadIdx.x + u * SNT));
         } else {
-            const uint32_t nv = !V4 && a.chunk == T ? 0 : at.left >> 2, t = 4 * nv + threadIdx.x;
-            for (uint32_t i = threadIdx.x; i < nv; i += T) {
-                const uvec<float> v = g2 * (load16<false>(at.x + 4 * i) - sse_c4<V4>(a, at, 4 * i));
-                if constexpr (T == NT) store16_near(v, go + 4 * i);
-                else store16(v, go + 4 * i);
-            }
+            const uint32_t nv = at.left >> 2, t = 4 * nv + threadIdx.x;
+            for (uint32_t i = threadIdx.x; i < nv; i += SNT)
+                store16(g2 * (load16<false>(at.x + 4 * i) - sse_c4<V4>(a, at, 4 * i)), go + 4 * i);
             if (t < at.left) go[t] = g2 * (at.x[t] - sse_c1(a, at, t));
         }
     }
@@ -1371,14 +1421,18 @@ mx_status mx_kmeans_sse_f32(const float *X_dev, int64_t n, int d, const float *C
                "%s: workspace needs %zu bytes, 256-byte aligned", who, need);
     float *part = (float *)((char *)ws + kCounterBytes);
     SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
-    if (a.total <= kSseOne) a.chunk = kSseOne;
-    const int nb = (int)std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(a.total, a.chunk)));
-    const bool small = a.chunk < kSseOne;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(nb), dim3(small ? NT : SNT), 0, stream, a, nb == 1 ? sse_dev : part);
-    };
-    if (d % 4 == 0) small ? go(k_sse_partial<true, NT>) : go(k_sse_partial<true, SNT>);
-    else small ? go(k_sse_partial<false, NT>) : go(k_sse_partial<false, SNT>);
+    const bool v4 = d % 4 == 0, vec = v4 || a.total > kSmallPass;
+    int nb;
+    if (a.total > kSseOne && a.total <= kSseSmall) {
+        nb = (int)ceil_div(a.total, vec ? 4 * NT : NT);
+        auto kernel = v4 ? k_sse_partial_small<true, true> : vec ? k_sse_partial_small<false, true> : k_sse_partial_small<false, false>;
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(NT), 0, stream, a, part);
+    } else {
+        if (a.total <= kSseOne) a.chunk = kSseOne;
+        nb = (int)std::min<int64_t>(1024, std::max<int64_t>(1, ceil_div(a.total, a.chunk)));
+        hipLaunchKernelGGL(v4 ? k_sse_partial<true> : k_sse_partial<false>, dim3(nb), dim3(SNT), 0, stream, a,
+                           nb == 1 ? sse_dev : part);
+    }
     if (nb > 1) hipLaunchKernelGGL(k_sse_final, dim3(1), dim3(NT), 0, stream, part, nb, sse_dev);
     return last_launch(who);
 }
@@ -1391,15 +1445,17 @@ mx_status mx_kmeans_sse_grad_f32(const float *X_dev, int64_t n, int d, const flo
     if (n == 0) return MX_OK;
     MX_REQUIRE(X_dev && C_dev && labels_dev && gscale_dev && G_dev, MX_ERR_INVALID, "%s: null pointer", who);
     const SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
-    const bool past = n * d * 2 * (int64_t)sizeof(float) > kCacheBytes;
-    const unsigned grid = (unsigned)std::min<int64_t>(65536, ceil_div(n * d, a.chunk));
-    const bool small = a.chunk < kSseChunk;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(small ? NT : SNT), 0, stream, a, gscale_dev, G_dev);
-    };
-    if (small) d % 4 == 0 ? go(k_sse_grad<true, false, NT>) : go(k_sse_grad<false, false, NT>);
-    else if (d % 4 == 0) past ? go(k_sse_grad<true, true, SNT>) : go(k_sse_grad<true, false, SNT>);
-    else past ? go(k_sse_grad<false, true, SNT>) : go(k_sse_grad<false, false, SNT>);
+    const bool v4 = d % 4 == 0;
+    if (a.total <= (v4 ? kSseSmall : kSseEach)) {
+        hipLaunchKernelGGL(v4 ? k_sse_grad_small<true> : k_sse_grad_small<false>, dim3((unsigned)ceil_div(a.total, v4 ? 4 * NT : NT)),
+                           dim3(NT), 0, stream, a, gscale_dev, G_dev);
+        return last_launch(who);
+    }
+    const bool past = a.total * 2 * (int64_t)sizeof(float) > kCacheBytes;
+    const unsigned grid = (unsigned)std::min<int64_t>(65536, ceil_div(a.total, a.chunk));
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(SNT), 0, stream, a, gscale_dev, G_dev); };
+    if (v4) past ? go(k_sse_grad<true, true>) : go(k_sse_grad<true, false>);
+    else past ? go(k_sse_grad<false, true>) : go(k_sse_grad<false, false>);
     return last_launch(who);
 }
 

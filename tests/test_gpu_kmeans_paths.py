@@ -126,3 +126,11 @@ def test_gradient_past_the_cache():
 def test_small_sse_edges(n, d):
     """Sums of one block (2048 elements), an element per thread (2^18) and a vector (2^19), and the first past each."""
     test_sse_and_gradient(n, d, 1)
+
+
+@pytest.mark.parametrize("n,d", [(43690, 3), (43691, 3), (65536, 2), (131073, 1), (74898, 7), (74899, 7), (131072, 4),
+                                 (524289, 1), (349525, 3), (349526, 3), (16384, 32), (1048577, 1)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_sse_last_of_the_small_passes(n, d, shift):
+    """Sums of 2^17 and 2^19 elements and gradients of 2^19 and 2^20, the last that small passes take, and the next ones."""
+    test_sse_and_gradient(n, d, shift)
