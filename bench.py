@@ -57,35 +57,35 @@ TRAFFIC = {
     # Each XCD's L2 fetches the A row panels and B column panels of its own 32 tiles (4 x 8 of them:
     # 12 panels of 1 MiB, the fewest 32 tiles can need), so each A panel is fetched by two XCDs and
     # each B panel by four; the algorithmic minimum is 33.6 MB read + 16.8 MB written (2.34x)
-    "gemm_nn": {"file": "gemm.hip", "bytes": 117517025,
-                "source": "ec0d76388112add1b95513576a3af1d8dfe92d5045531e1d294820495ee0ec31"},
-    "gemm_nt": {"file": "gemm.hip", "bytes": 117506786,
-                "source": "ec0d76388112add1b95513576a3af1d8dfe92d5045531e1d294820495ee0ec31"},
-    "gemm_tn": {"file": "gemm.hip", "bytes": 117512929,
-                "source": "ec0d76388112add1b95513576a3af1d8dfe92d5045531e1d294820495ee0ec31"},
+    "gemm_nn": {"file": "gemm.hip", "bytes": 117521340,
+                "source": "86fb3dded6dd0590afcc95a406e41c116e171bff85a9881ecaaaf40b5ae7c688"},
+    "gemm_nt": {"file": "gemm.hip", "bytes": 117511100,
+                "source": "86fb3dded6dd0590afcc95a406e41c116e171bff85a9881ecaaaf40b5ae7c688"},
+    "gemm_tn": {"file": "gemm.hip", "bytes": 117517244,
+                "source": "86fb3dded6dd0590afcc95a406e41c116e171bff85a9881ecaaaf40b5ae7c688"},
     # k_seg_span (row-span path, nontemporal loads), 65536 rows / 32.1 M values: 132.43 MB fetched + 0.26 MB
     # written (1.03x algorithmic: 129.19 MB)
-    "seg_span": {"file": "segmented.hip", "bytes": 132694703,
-                 "source": "5471d8a0b87aff6e90231e21de4911ac3b88e31e11f7af36b072bf82584cec0a"},
+    "seg_span": {"file": "segmented.hip", "bytes": 132693423,
+                 "source": "a945cdf3c5395c6d3d741c778250b604b9ef32c12af9bb7c77d5b069cfbbdc2e"},
     # mx_xvjp (generated from expr.hip) for exp(-(a-b)^2)*0.5 + a*b over 2^26 float32 pairs:
-    # 536.94 MB fetched + 536.99 MB written (1.00x algorithmic)
-    "expr_vjp": {"file": "expr.hip", "bytes": 1073925745,
-                 "source": "72ab392dffebd016e2a1d2c5ee2860bbad5b6511fc910bf24a8896f6a243e399"},
+    # 536.97 MB fetched + 536.94 MB written (1.00x algorithmic)
+    "expr_vjp": {"file": "expr.hip", "bytes": 1073911625,
+                 "source": "969593739b0a34d7ef496de0ae2de6015755a13b2de28e4b415e09ba7d91443a"},
     # mx_xseg_add, same body over the nested step's 65 536 ragged rows (2 x 32.1 M values):
-    # 261.30 MB fetched + 0.26 MB written (1.02x algorithmic)
-    "expr_seg": {"file": "expr.hip", "bytes": 261565657,
-                 "source": "72ab392dffebd016e2a1d2c5ee2860bbad5b6511fc910bf24a8896f6a243e399"},
-    # k_stencil7, 512 x 512 x 64 float32: 73.16 MB fetched (1.09x: a 16-plane slab re-reads the planes
+    # 261.47 MB fetched + 0.26 MB written (1.02x algorithmic)
+    "expr_seg": {"file": "expr.hip", "bytes": 261734395,
+                 "source": "969593739b0a34d7ef496de0ae2de6015755a13b2de28e4b415e09ba7d91443a"},
+    # k_stencil7, 512 x 512 x 64 float32: 73.15 MB fetched (1.09x: a 16-plane slab re-reads the planes
     # below and above it) + 67.10 MB written
-    "stencil": {"file": "parboil.hip", "bytes": 140263158,
-                "source": "b4bccd849aa63dc0ff606221add7470ce4f7f0202bed4ed3f9a0b3ce249742b8"},
-    # k_kmeans_fused<32,64,true,false>, 2^20 x 32 points, k = 64: 134.67 MB fetched (X, 1.00x) + 12.10 MB written
+    "stencil": {"file": "parboil.hip", "bytes": 140251804,
+                "source": "2307808bbcf2fc76d1527fd038c116ad875612bd1d56b29b77a96c73240e4f1e"},
+    # k_kmeans_fused<32,64,true,false>, 2^20 x 32 points, k = 64: 134.68 MB fetched (X, 1.00x) + 12.10 MB written
     # (labels, and 768 block partials stored in 32-byte entry groups)
-    "kmeans": {"file": "kmeans.hip", "bytes": 146770890,
-               "source": "8628776931a21c68cde289781a5d5dfc5a3698a3a24d5721b9bc3237cfc2483c"},
-    # k_seg_broadcast (row-span path): 2.66 MB fetched (offsets, gradients) + 128.70 MB written
-    "seg_broadcast": {"file": "segmented.hip", "bytes": 131364569,
-                      "source": "5471d8a0b87aff6e90231e21de4911ac3b88e31e11f7af36b072bf82584cec0a"},
+    "kmeans": {"file": "kmeans.hip", "bytes": 146779458,
+               "source": "e22cc64d8f13ab1cb6a8fc35401742ca7ee313215dfdce6c3e501aae31a67bda"},
+    # k_seg_broadcast (row-span path): 2.66 MB fetched (offsets, gradients) + 128.71 MB written
+    "seg_broadcast": {"file": "segmented.hip", "bytes": 131369416,
+                      "source": "a945cdf3c5395c6d3d741c778250b604b9ef32c12af9bb7c77d5b069cfbbdc2e"},
 }
 
 
