@@ -1049,15 +1049,17 @@ constexpr int SNT = 512;  // 1024 blocks (the partials' room) of it fill every C
 constexpr int kSseVec = 2;
 constexpr int kSseChunk = 4 * kSseVec * SNT;  // elements
 // Up to kSseSmall elements a vector per thread, or where d is no multiple of four
-// and the elements of a vector need a point each, an element: of the sum up to
-// kSmallPass elements, of the gradient up to kSseEach.  These passes are all latency,
-// of the launch, of instructions fetched for the first time and of the chain of
-// label and centroid, so they have kernels of their own with one path and no loop.
-// us with a grid-wide stride, in the chunks of the larger passes, now: gradient of
-// 300 000 x 2 3.2, 3.9, 3.0, sum of 5000 x 64 4.2, 4.7, 4.2.  The sum of up to kSseOne elements is one
-// block's, and one launch (100 points of 16: two launches 1.9 times as long).
+// and the elements of a vector need a point each, an element, of the sum up to
+// kSmallPass elements.  These passes are all latency, of the launch, of instructions
+// fetched for the first time and of the chain of label and centroid, so they have
+// kernels of their own with one path and no loop.  us with a grid-wide stride, in
+// the chunks of the larger passes, now: gradient of 300 000 x 2 3.2, 3.9, 3.0, sum of
+// 5000 x 64 4.2, 4.7, 4.2, of 18 181 x 33 5.3, 5.8, 5.0.  The sum of up to kSseOne
+// elements is one block's, and one launch (100 points of 16: two launches 1.9 times
+// as long).
 constexpr int64_t kSseOne = 4 * SNT;
-constexpr int64_t kSseSmall = 4 * kSmallPass, kSseEach = 8 * kSmallPass;
+constexpr int64_t kSseSmall = 8 * kSmallPass;
+static_assert(kSseSmall <= 1024 * 4 * NT && kSmallPass <= 1024 * NT, "a partial per block");
 
 struct SseArgs {
     const float *X, *C;
@@ -1099,6 +1101,9 @@ template <bool V4> __device__ __forceinline__ uvec<float> sse_c4(const SseArgs &
     if constexpr (V4) {
         const uint32_t r = at.r0 + off, q = sse_point(a, r);
         return load16<false>(a.C + (int64_t)at.lab[q] * a.d + (r - q * a.d));
+    } else if (a.d == 1) {  // four labels together: gradient of 1.5 M x 1 5.5 us one by one, now 4.1 us
+        const uvec<int32_t> l = load16<false>(at.lab + off);
+        return uvec<float>{a.C[l[0]], a.C[l[1]], a.C[l[2]], a.C[l[3]]};
     } else {
         return uvec<float>{sse_c1(a, at, off), sse_c1(a, at, off + 1), sse_c1(a, at, off + 2), sse_c1(a, at, off + 3)};
     }
@@ -1446,7 +1451,7 @@ mx_status mx_kmeans_sse_grad_f32(const float *X_dev, int64_t n, int d, const flo
     MX_REQUIRE(X_dev && C_dev && labels_dev && gscale_dev && G_dev, MX_ERR_INVALID, "%s: null pointer", who);
     const SseArgs a = sse_args(X_dev, n, d, C_dev, labels_dev);
     const bool v4 = d % 4 == 0;
-    if (a.total <= (v4 ? kSseSmall : kSseEach)) {
+    if (a.total <= kSseSmall) {
         hipLaunchKernelGGL(v4 ? k_sse_grad_small<true> : k_sse_grad_small<false>, dim3((unsigned)ceil_div(a.total, v4 ? 4 * NT : NT)),
                            dim3(NT), 0, stream, a, gscale_dev, G_dev);
         return last_launch(who);

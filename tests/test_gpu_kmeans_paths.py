@@ -134,3 +134,10 @@ def test_small_sse_edges(n, d):
 def test_sse_last_of_the_small_passes(n, d, shift):
     """Sums of 2^17 and 2^19 elements and gradients of 2^19 and 2^20, the last that small passes take, and the next ones."""
     test_sse_and_gradient(n, d, shift)
+
+
+@pytest.mark.parametrize("n,d", [(262144, 4), (262145, 4), (131072, 8), (209715, 5), (1500003, 1), (1048580, 1)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_sse_last_vectors_of_the_small_passes_and_labels_by_four(n, d, shift):
+    """Sums and gradients of 2^20 elements by vectors and the next ones; points of one dimension in larger passes."""
+    test_sse_and_gradient(n, d, shift)
