@@ -79,10 +79,10 @@ TRAFFIC = {
     # below and above it) + 67.10 MB written
     "stencil": {"file": "parboil.hip", "bytes": 140251804,
                 "source": "2307808bbcf2fc76d1527fd038c116ad875612bd1d56b29b77a96c73240e4f1e"},
-    # k_kmeans_fused<32,64,true,false>, 2^20 x 32 points, k = 64: 134.68 MB fetched (X, 1.00x) + 12.10 MB written
+    # k_kmeans_fused<32,64,true,false>, 2^20 x 32 points, k = 64: 134.65 MB fetched (X, 1.00x) + 12.10 MB written
     # (labels, and 768 block partials stored in 32-byte entry groups)
-    "kmeans": {"file": "kmeans.hip", "bytes": 146779458,
-               "source": "e22cc64d8f13ab1cb6a8fc35401742ca7ee313215dfdce6c3e501aae31a67bda"},
+    "kmeans": {"file": "kmeans.hip", "bytes": 146749380,
+               "source": "c96f9f4b8688d5a9d7d3b1dc834b436d7829735d5ccc2da54208246fbe09d251"},
     # k_seg_broadcast (row-span path): 2.66 MB fetched (offsets, gradients) + 128.71 MB written
     "seg_broadcast": {"file": "segmented.hip", "bytes": 131369416,
                       "source": "a945cdf3c5395c6d3d741c778250b604b9ef32c12af9bb7c77d5b069cfbbdc2e"},
